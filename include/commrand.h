@@ -131,7 +131,7 @@ cr_status cr_build_batches(const cr_batch_cfg *cfg, const int32_t *train_ids, in
                            int32_t *out_perm, int64_t *out_n_batches, void *stream);
 
 /* cr_build_batches for callers that cannot allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc): the same result, bit for bit, with the sort buffers, digit histograms and
+ * harnesses that forbid hipMalloc): the same result, bit for bit, with the sort buffers, bucket counts and
  * community tables in a fixed 8 MiB device array that belongs to the library instead of a caller workspace.  The call
  * allocates and frees nothing, on the host or on the device.
  *   limits : n_train <= CR_STATIC_MAX_TRAIN and n_comm <= CR_STATIC_MAX_COMM, otherwise CR_ERR_CAPACITY (use

@@ -1,70 +1,261 @@
 // Root node partitioning (Algorithm 1 Step-1; Section 4.1; Table 1): the epoch's permutation of the
-// training set under NORAND-ROOTS, COMM-RAND-MIX and RAND-ROOTS.  Every shuffle is a stable
-// least-significant-digit radix sort by a Philox key, started from ascending ids, so equal keys
-// keep the smaller id first and the result does not depend on scheduling.
+// training set under NORAND-ROOTS, COMM-RAND-MIX and RAND-ROOTS.  Every shuffle is a sort by a Philox key,
+// equal keys keep the smaller id first, so the result does not depend on scheduling.
+//
+// The keys are uniform random numbers, so an element's place is known to within a few positions before anything is
+// sorted: with `count` elements in its super-block, which starts at `first`, it belongs near
+//     p = first + (upper key word * count) >> 32,
+// and p ascends with (super-block, key).  A shuffle is therefore ONE distribution pass into buckets of equal stretches
+// of p and a sort of every bucket in LDS (about 512 elements into 512 bins, one each on average), instead of a
+// radix pass per key byte: 1.22 M training nodes in 100 000 communities (MIX-12.5 %) 2136 -> 125 us, the same
+// nodes under RAND-ROOTS 1456 -> 49 us.
 #include <mutex>
 
 #include "cr_common.h"
 
 namespace cr {
 
-constexpr int SORT_TILE = 2048;   // keys per single-wave workgroup
+constexpr int MAX_BUCKETS = 4096;       // LDS counters of the distribution kernels (16 KB)
+constexpr int MIN_SHIFT = 9;            // a bucket spans at least 512 positions: one per LDS bin of the bucket sort
+constexpr int BIN_SHIFT = 10;           // ... and is sorted 1024 positions at a time
+constexpr int SORT_CAP = 2048;          // elements of such a stretch that fit LDS (mean 1024, deviation 32)
+constexpr int DIST_TILE = 4096;         // elements a distribution workgroup takes at least
+constexpr int DIST_BLOCKS = 256;        // ... and the most such workgroups (one per compute unit)
 
-// digit histogram of one tile -> hist[digit * nblk + block]
-__global__ __launch_bounds__(64) void radix_hist_kernel(const uint64_t *__restrict__ keys, int n, int shift, int nblk,
-                                                        int32_t *__restrict__ hist)
+// one shuffle: what is sorted and how it is cut
+struct ShufflePlan {
+    int n;                  // elements
+    int shift;              // bucket = p >> shift
+    int n_buckets;          // buckets the positions 0..n-1 fall into (<= MAX_BUCKETS)
+    int n_tiles, tile;      // distribution workgroups and their elements
+};
+
+__host__ static ShufflePlan shuffle_plan(int n)
 {
-    __shared__ int cnt[256];
-    for (int i = threadIdx.x; i < 256; i += 64) cnt[i] = 0;
-    __syncthreads();
-    const int start = blockIdx.x * SORT_TILE;
-    const int stop = min(n, start + SORT_TILE);
-    for (int i = start + threadIdx.x; i < stop; i += 64) atomicAdd(&cnt[(int)((keys[i] >> shift) & 255u)], 1);
-    __syncthreads();
-    for (int d = threadIdx.x; d < 256; d += 64) hist[d * nblk + blockIdx.x] = cnt[d];
+    ShufflePlan s;
+    s.n = n;
+    s.shift = MIN_SHIFT;
+    while (((n - 1) >> s.shift) >= MAX_BUCKETS) ++s.shift;
+    s.n_buckets = n > 0 ? ((n - 1) >> s.shift) + 1 : 1;
+    const int64_t want = ceil_div(n, DIST_TILE);
+    s.n_tiles = (int)(want < 1 ? 1 : (want > DIST_BLOCKS ? DIST_BLOCKS : want));
+    s.tile = (int)ceil_div(n > 0 ? n : 1, s.n_tiles);
+    return s;
 }
 
-// in-place exclusive scan of the histogram table (one workgroup)
-__global__ __launch_bounds__(1024) void radix_scan_kernel(int32_t *hist, int n)
+// What is shuffled.  Nodes: element i is train[i], and its super-block's stretch of the permutation comes from its
+// community (`stretch`, NULL: one super-block, RAND-ROOTS).  Communities: element i is community i, taking part when the
+// training set has a node of it; *n_present of them do.
+struct ShuffleArgs {
+    const int32_t *train;
+    const int32_t *node_comm;       // [n] community of train[i] (with `stretch`)
+    const int2 *stretch;            // [n_comm] (first position, length) of the community's super-block
+    const int32_t *present;         // [n_comm] training nodes of every community
+    const int32_t *n_present;
+    uint64_t seed;
+    uint32_t epoch;
+    ShufflePlan plan;
+    uint32_t *pos;                  // [n] p of every element (ABSENT: takes no part)
+    int32_t *counts;                // [n_tiles][n_buckets]
+    int32_t *totals;                // [n_buckets]
+    uint2 *pairs;                   // [n] (p, id), bucket by bucket
+    int32_t *out;                   // [n] ids in order
+};
+constexpr uint32_t ABSENT = 0xFFFFFFFFu;
+
+template <bool COMMUNITIES>
+__device__ __forceinline__ uint64_t element_key(const ShuffleArgs &a, uint32_t id)
 {
-    __shared__ int lds[17];
-    scan_chunked(hist, hist, nullptr, n, lds);
+    return shuffle_key(a.seed, a.epoch, COMMUNITIES ? DOMAIN_COMMUNITY : DOMAIN_NODE, id);
 }
 
-// stable scatter: the wave walks its tile 64 keys at a time; within a chunk a key's rank among the
-// keys with the same digit comes from eight ballots
-__global__ __launch_bounds__(64) void radix_scatter_kernel(const uint64_t *__restrict__ keys_in,
-                                                           const uint32_t *__restrict__ vals_in, int n, int shift, int nblk,
-                                                           const int32_t *__restrict__ offs, uint64_t *__restrict__ keys_out,
-                                                           uint32_t *__restrict__ vals_out)
+// positions of a tile's elements, and how many fall into every bucket
+template <bool COMMUNITIES>
+__global__ __launch_bounds__(1024) void shuffle_count_kernel(ShuffleArgs a)
 {
-    __shared__ int cursor[256];
-    for (int d = threadIdx.x; d < 256; d += 64) cursor[d] = offs[d * nblk + blockIdx.x];
+    __shared__ int cnt[MAX_BUCKETS];
+    const ShufflePlan &pl = a.plan;
+    for (int b = threadIdx.x; b < pl.n_buckets; b += 1024) cnt[b] = 0;
     __syncthreads();
-    const int start = blockIdx.x * SORT_TILE;
-    const int stop = min(n, start + SORT_TILE);
-    const int lane = lane_id();
-    for (int c = start; c < stop; c += 64) {
-        const int i = c + lane;
-        const bool have = i < stop;
-        uint64_t key = 0;
-        uint32_t val = 0;
-        if (have) { key = keys_in[i]; val = vals_in[i]; }
-        const uint32_t d = (uint32_t)((key >> shift) & 255u);
-        uint64_t peers = __ballot(have);
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const uint64_t m = __ballot(have && ((d >> b) & 1u));
-            peers &= ((d >> b) & 1u) ? m : ~m;
+    const int64_t start = (int64_t)blockIdx.x * pl.tile, stop = min((int64_t)pl.n, start + pl.tile);
+    for (int64_t i = start + threadIdx.x; i < stop; i += 1024) {
+        uint32_t p;
+        if constexpr (COMMUNITIES) {
+            const uint32_t hi = (uint32_t)(element_key<true>(a, (uint32_t)i) >> 32);
+            p = a.present[i] > 0 ? __umulhi(hi, (uint32_t)*a.n_present) : ABSENT;
+        } else {
+            const int v = a.train[i];
+            const uint32_t hi = (uint32_t)(element_key<false>(a, (uint32_t)v) >> 32);
+            const int2 st = a.stretch ? a.stretch[a.node_comm[i]] : make_int2(0, pl.n);
+            p = (uint32_t)st.x + __umulhi(hi, (uint32_t)st.y);
         }
-        const uint64_t below = peers & ((1ull << lane) - 1ull);
-        int pos = 0;
-        if (have) pos = cursor[d] + __popcll(below);
-        __syncthreads();
-        if (have && below == 0) cursor[d] += __popcll(peers);
-        __syncthreads();
-        if (have) { keys_out[pos] = key; vals_out[pos] = val; }
+        a.pos[i] = p;
+        if (p != ABSENT) atomicAdd(&cnt[p >> pl.shift], 1);
     }
+    __syncthreads();
+    int32_t *row = a.counts + (int64_t)blockIdx.x * pl.n_buckets;
+    for (int b = threadIdx.x; b < pl.n_buckets; b += 1024) row[b] = cnt[b];
+}
+
+// counts[tile][bucket] -> elements of the bucket in the tiles in front; totals[bucket].  A workgroup takes 64 buckets, its
+// sixteen waves a sixteenth of the tiles each.
+__global__ __launch_bounds__(1024) void shuffle_prefix_kernel(ShufflePlan pl, int32_t *counts, int32_t *totals)
+{
+    __shared__ int part[16][64];
+    constexpr int PER = DIST_BLOCKS / 16;
+    const int lane = lane_id(), wave = threadIdx.x / WAVE;
+    const int b = blockIdx.x * 64 + lane;
+    const bool have = b < pl.n_buckets;
+    const int t0 = wave * PER;
+    int x[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) x[k] = (have && t0 + k < pl.n_tiles) ? counts[(int64_t)(t0 + k) * pl.n_buckets + b] : 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) sum += x[k];
+    part[wave][lane] = sum;
+    __syncthreads();
+    int run = 0;
+    for (int w = 0; w < wave; ++w) run += part[w][lane];
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        if (have && t0 + k < pl.n_tiles) counts[(int64_t)(t0 + k) * pl.n_buckets + b] = run;
+        run += x[k];
+    }
+    if (have && wave == 15) totals[b] = run;
+}
+
+// (p, id) of a tile's elements into their buckets; the order inside a bucket does not matter, the bucket is sorted
+__global__ __launch_bounds__(1024) void shuffle_scatter_kernel(ShuffleArgs a, int communities)
+{
+    __shared__ int cursor[MAX_BUCKETS];
+    __shared__ int lds[17];
+    constexpr int PER = MAX_BUCKETS / 1024;
+    const ShufflePlan &pl = a.plan;
+    const int32_t *row = a.counts + (int64_t)blockIdx.x * pl.n_buckets;
+    const int b0 = (int)threadIdx.x * PER;
+    int x[PER], y[PER], sum = 0;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        x[k] = b0 + k < pl.n_buckets ? a.totals[b0 + k] : 0;
+        y[k] = b0 + k < pl.n_buckets ? row[b0 + k] : 0;
+        sum += x[k];
+    }
+    int total;
+    int run = block_exclusive_scan_1024(sum, lds, total);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        cursor[b0 + k] = run + y[k];
+        run += x[k];
+    }
+    __syncthreads();
+    const int64_t start = (int64_t)blockIdx.x * pl.tile, stop = min((int64_t)pl.n, start + pl.tile);
+    for (int64_t i = start + threadIdx.x; i < stop; i += 1024) {
+        const uint32_t p = a.pos[i];
+        if (p == ABSENT) continue;
+        a.pairs[atomicAdd(&cursor[p >> pl.shift], 1)] = make_uint2(p, (uint32_t)(communities ? i : a.train[i]));
+    }
+}
+
+// Whether element (pa, ka, ia) comes before (pb, kb, ib).  Equal p does not mean equal key, but p ascends with the
+// (super-block, key) pair, so p first and the key inside p is the same order.
+__device__ __forceinline__ bool comes_before(uint32_t pa, uint64_t ka, uint32_t ia, uint32_t pb, uint64_t kb, uint32_t ib)
+{
+    return pa != pb ? pa < pb : (ka != kb ? ka < kb : ia < ib);
+}
+
+// A bucket per workgroup.  A stretch of 1024 positions of it (the whole bucket, unless there are more than 4 M elements)
+// is counted into one bin per position, laid out bin by bin in LDS with the elements' full keys, and every element finds
+// its rank among the one or two of its own bin.  A stretch that does not fit LDS -- which a uniform key does not produce,
+// only ids that are given more than once -- sends the bucket through a merge network in memory instead.
+template <bool COMMUNITIES>
+__global__ __launch_bounds__(256) void shuffle_sort_kernel(ShuffleArgs a)
+{
+    __shared__ uint64_t keys[SORT_CAP];
+    __shared__ uint32_t ids[SORT_CAP];
+    __shared__ uint16_t bin_of[SORT_CAP];
+    __shared__ int bin_end[1 << BIN_SHIFT];
+    __shared__ int lds[17];
+    const ShufflePlan &pl = a.plan;
+    const int tid = threadIdx.x, bucket = blockIdx.x;
+    // first element: the buckets in front, added up by the workgroup
+    int before = 0, m;
+    for (int b = tid; b < bucket; b += 256) before += a.totals[b];
+    block_exclusive_scan<4>(before, lds, before);
+    m = a.totals[bucket];
+    uint2 *pairs = a.pairs + before;
+    int32_t *out = a.out + before;
+    const int n_bins = 1 << min(pl.shift, BIN_SHIFT);
+    const int n_stretches = 1 << max(0, pl.shift - BIN_SHIFT);
+    int done = 0;
+    for (int st = 0; st < n_stretches && done < m; ++st) {
+        const uint32_t tag = ((uint32_t)bucket << max(0, pl.shift - BIN_SHIFT)) + (uint32_t)st;      // p / 1024 (or the bucket)
+        const int tag_shift = min(pl.shift, BIN_SHIFT);
+        __syncthreads();
+        for (int i = tid; i < n_bins; i += 256) bin_end[i] = 0;
+        __syncthreads();
+        for (int i = tid; i < m; i += 256) {
+            const uint32_t p = pairs[i].x;
+            if ((p >> tag_shift) == tag) atomicAdd(&bin_end[p & (n_bins - 1)], 1);
+        }
+        __syncthreads();
+        // bin starts (a thread owns consecutive bins)
+        constexpr int PER = (1 << BIN_SHIFT) / 256;
+        int x[PER], sum = 0, total;
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            x[k] = tid * PER + k < n_bins ? bin_end[tid * PER + k] : 0;
+            sum += x[k];
+        }
+        int run = block_exclusive_scan<4>(sum, lds, total);
+        if (total > SORT_CAP) break;                                   // (uniform)
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if (tid * PER + k < n_bins) bin_end[tid * PER + k] = run;  // advanced to the bin's end below
+            run += x[k];
+        }
+        __syncthreads();
+        for (int i = tid; i < m; i += 256) {
+            const uint2 e = pairs[i];
+            if ((e.x >> tag_shift) != tag) continue;
+            const int bin = (int)(e.x & (n_bins - 1));
+            const int at = atomicAdd(&bin_end[bin], 1);
+            ids[at] = e.y;
+            keys[at] = element_key<COMMUNITIES>(a, e.y);
+            bin_of[at] = (uint16_t)bin;
+        }
+        __syncthreads();
+        for (int i = tid; i < total; i += 256) {
+            const int bin = bin_of[i];
+            const int lo = bin > 0 ? bin_end[bin - 1] : 0, hi = bin_end[bin];
+            const uint64_t k = keys[i];
+            const uint32_t id = ids[i];
+            int rank = lo;
+            for (int j = lo; j < hi; ++j) rank += (keys[j] < k || (keys[j] == k && (ids[j] < id || (ids[j] == id && j < i)))) ? 1 : 0;
+            out[done + rank] = (int32_t)id;
+        }
+        done += total;
+    }
+    if (done >= m) return;
+    // merge network over the bucket's pairs in memory: every exchange moves the earlier element to the lower index, so
+    // the places past m act as elements behind all others and are never touched
+    __syncthreads();
+    auto exchange = [&](int i, int j) {
+        if (j >= m) return;
+        const uint2 x = pairs[i], y = pairs[j];
+        if (comes_before(y.x, element_key<COMMUNITIES>(a, y.y), y.y, x.x, element_key<COMMUNITIES>(a, x.y), x.y)) { pairs[i] = y; pairs[j] = x; }
+    };
+    for (int64_t size = 2; size < 2 * (int64_t)m; size *= 2) {
+        const int half = (int)(size / 2);
+        for (int i = tid; i < m; i += 256)
+            if ((i & (size - 1)) < half) exchange(i, (int)min((int64_t)m, (i & ~(size - 1)) + size - 1 - (i & (size - 1))));
+        __syncthreads();
+        for (int d = half / 2; d > 0; d /= 2) {
+            for (int i = tid; i < m; i += 256)
+                if ((i & d) == 0) exchange(i, (int)min((int64_t)m, (int64_t)i + d));
+            __syncthreads();
+        }
+    }
+    for (int i = tid; i < m; i += 256) out[i] = (int32_t)pairs[i].y;
 }
 
 __global__ __launch_bounds__(256) void zero_i32_kernel(int32_t *p, int64_t n)
@@ -72,55 +263,111 @@ __global__ __launch_bounds__(256) void zero_i32_kernel(int32_t *p, int64_t n)
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) p[i] = 0;
 }
 
-__global__ __launch_bounds__(256) void mark_present_kernel(const int32_t *__restrict__ train, int n_train,
-                                                           const int32_t *__restrict__ comm, int32_t *present)
+// Training nodes per community, and how many communities have one (both zeroed before); the communities are kept for
+// the distribution of the nodes, which needs them again.  Training nodes are thinly spread (1 % of the papers-like
+// graph), so every look-up is a memory line of its own: 1.22 M of them are 156 MB and most of this kernel's 28 us,
+// and what a second look-up would cost (the distribution's counting pass: 22.3 us with it, 8.0 with the kept ones).
+// Training ids ascend and communities are stretches of ids in the graphs this is used on, so a wave takes consecutive
+// ids, all of its look-ups in flight at once, and adds to a community's counter once per run of ids: adds to one
+// address are served one after another (one add per 256 ids on *n_present alone made the kernel take 64 us).
+constexpr int COUNT_CHUNKS = 8;         // chunks of 64 ids a wave takes in a row
+__global__ __launch_bounds__(256) void count_communities_kernel(const int32_t *__restrict__ train, int n_train, const int32_t *__restrict__ comm,
+                                                                int32_t *__restrict__ count, int32_t *__restrict__ n_present,
+                                                                int32_t *__restrict__ node_comm)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n_train) present[comm[train[i]]] = 1;
+    __shared__ int found;
+    if (threadIdx.x == 0) found = 0;
+    __syncthreads();
+    const int lane = lane_id();
+    const int64_t first = ((int64_t)blockIdx.x * 4 + threadIdx.x / WAVE) * (COUNT_CHUNKS * 64) + lane;
+    int c[COUNT_CHUNKS];
+#pragma unroll
+    for (int k = 0; k < COUNT_CHUNKS; ++k) c[k] = train[min(first + k * 64, (int64_t)n_train - 1)];
+#pragma unroll
+    for (int k = 0; k < COUNT_CHUNKS; ++k) c[k] = comm[c[k]];
+    int mine = 0, at = -1, held = 0;                     // community of the open run (the same in all lanes) and its ids so far
+    auto add = [&](int community, int len) {
+        if (atomicAdd(&count[community], len) == 0) ++mine;
+    };
+#pragma unroll
+    for (int k = 0; k < COUNT_CHUNKS; ++k) {
+        if (first + k * 64 < n_train) node_comm[first + k * 64] = c[k];
+        else c[k] = -1;
+        const int c0 = __builtin_amdgcn_readfirstlane(c[k]);
+        if (c0 != at && held > 0) {
+            if (lane == 0) add(at, held);
+            held = 0;
+        }
+        at = c0;
+        if (__ballot(c[k] != c0) == 0) {                 // one community throughout
+            held = c0 >= 0 ? held + 64 : 0;
+            continue;
+        }
+        const int left = __shfl_up(c[k], 1);
+        const bool head = lane == 0 || left != c[k];
+        const uint64_t after = __ballot(head) & (lane < 63 ? ~0ull << (lane + 1) : 0ull);
+        const int len = (after ? __ffsll((unsigned long long)after) - 1 : 64) - lane;
+        if (head && c[k] >= 0) add(c[k], len + (lane == 0 ? held : 0));
+        at = -1;
+        held = 0;
+    }
+    if (held > 0 && lane == 0) add(at, held);
+    if (mine) atomicAdd(&found, mine);
+    __syncthreads();
+    if (threadIdx.x == 0 && found) atomicAdd(n_present, found);
 }
 
-// communities: key = Philox key of the community; absent ones sort behind every present one
-__global__ __launch_bounds__(256) void community_keys_kernel(const int32_t *__restrict__ present, int n_comm, uint64_t seed,
-                                                             uint32_t epoch, uint64_t *keys, uint64_t *absent, uint32_t *vals)
+// Training nodes of the communities of a bucket (their order is known by now), added up.
+__global__ __launch_bounds__(256) void bucket_nodes_kernel(ShufflePlan pl, const int32_t *__restrict__ totals, const int32_t *__restrict__ order,
+                                                           const int32_t *__restrict__ count, int32_t *__restrict__ nodes_of_bucket)
 {
-    const int c = blockIdx.x * 256 + threadIdx.x;
-    if (c >= n_comm) return;
-    keys[c] = shuffle_key(seed, epoch, DOMAIN_COMMUNITY, (uint32_t)c);
-    absent[c] = present[c] ? 0ull : 1ull;
-    vals[c] = (uint32_t)c;
+    __shared__ int lds[17];
+    int before = 0, sum = 0;
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += 256) before += totals[b];
+    block_exclusive_scan<4>(before, lds, before);
+    const int m = totals[blockIdx.x];
+    for (int i = threadIdx.x; i < m; i += 256) sum += count[order[before + i]];
+    __syncthreads();
+    block_exclusive_scan<4>(sum, lds, sum);
+    if (threadIdx.x == 0) nodes_of_bucket[blockIdx.x] = sum;
 }
 
-// carry a one-bit key through an earlier permutation
-__global__ __launch_bounds__(256) void gather_flag_kernel(const uint32_t *__restrict__ vals, int n,
-                                                          const uint64_t *__restrict__ flag_by_id, uint64_t *keys)
+// nodes_before[r] = training nodes of the communities in front of rank r (one entry more than there are communities)
+__global__ __launch_bounds__(256) void nodes_before_kernel(ShufflePlan pl, const int32_t *__restrict__ totals, const int32_t *__restrict__ order,
+                                                           const int32_t *__restrict__ count, const int32_t *__restrict__ nodes_of_bucket,
+                                                           int n_train, const int32_t *__restrict__ n_present, int32_t *__restrict__ nodes_before)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) keys[i] = flag_by_id[vals[i]];
+    __shared__ int lds[17];
+    int before = 0, carry = 0;
+    for (int b = threadIdx.x; b < (int)blockIdx.x; b += 256) {
+        before += totals[b];
+        carry += nodes_of_bucket[b];
+    }
+    block_exclusive_scan<4>(before, lds, before);
+    __syncthreads();
+    block_exclusive_scan<4>(carry, lds, carry);
+    const int m = totals[blockIdx.x];
+    for (int t = 0; t < m; t += 256) {
+        const int i = t + (int)threadIdx.x;
+        const int x = i < m ? count[order[before + i]] : 0;
+        __syncthreads();
+        int total;
+        const int run = carry + block_exclusive_scan<4>(x, lds, total);
+        if (i < m) nodes_before[before + i] = run;
+        carry += total;
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) nodes_before[*n_present] = n_train;
 }
 
-__global__ __launch_bounds__(256) void block_of_kernel(const uint32_t *__restrict__ sorted_comm, int n_comm, int mix,
-                                                       int32_t *block_of)
+// the stretch of the permutation that a community's super-block (`mix` communities in a row) takes
+__global__ __launch_bounds__(256) void stretch_kernel(const int32_t *__restrict__ order, const int32_t *__restrict__ nodes_before,
+                                                      const int32_t *__restrict__ n_present, int mix, int2 *__restrict__ stretch)
 {
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r < n_comm) block_of[sorted_comm[r]] = r / mix;
-}
-
-__global__ __launch_bounds__(256) void node_keys_kernel(const int32_t *__restrict__ train, int n, uint64_t seed, uint32_t epoch,
-                                                        uint64_t *keys, uint32_t *vals)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    const uint32_t v = (uint32_t)train[i];
-    keys[i] = shuffle_key(seed, epoch, DOMAIN_NODE, v);
-    vals[i] = v;
-}
-
-__global__ __launch_bounds__(256) void super_block_keys_kernel(const uint32_t *__restrict__ vals, int n,
-                                                               const int32_t *__restrict__ comm,
-                                                               const int32_t *__restrict__ block_of, uint64_t *keys)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i < n) keys[i] = (uint64_t)(uint32_t)block_of[comm[vals[i]]];
+    const int r = (int)blockIdx.x * 256 + (int)threadIdx.x, n = *n_present;
+    if (r >= n) return;
+    const int first = r - r % mix;
+    const int lo = nodes_before[first], hi = nodes_before[(int)min((int64_t)first + mix, (int64_t)n)];
+    stretch[order[r]] = make_int2(lo, hi - lo);
 }
 
 __global__ __launch_bounds__(256) void copy_i32_kernel(const int32_t *__restrict__ in, int n, int32_t *out)
@@ -129,50 +376,43 @@ __global__ __launch_bounds__(256) void copy_i32_kernel(const int32_t *__restrict
     if (i < n) out[i] = in[i];
 }
 
-struct SortBuffers {
-    uint64_t *keys[2];
-    uint32_t *vals[2];
-    int32_t *hist;
-    int cur = 0;
-};
-
-// sorts (keys[cur], vals[cur]) by bits [0, bits) of the key; the result ends up in [cur]
-static void radix_sort(SortBuffers &b, int n, int bits, hipStream_t s)
+template <bool COMMUNITIES>
+static void launch_shuffle(const ShuffleArgs &a, hipStream_t s)
 {
-    if (n <= 0) return;
-    const int nblk = (int)ceil_div(n, SORT_TILE);
-    for (int shift = 0; shift < bits; shift += 8) {
-        const int o = b.cur ^ 1;
-        hipLaunchKernelGGL(radix_hist_kernel, dim3(nblk), dim3(64), 0, s, b.keys[b.cur], n, shift, nblk, b.hist);
-        hipLaunchKernelGGL(radix_scan_kernel, dim3(1), dim3(1024), 0, s, b.hist, 256 * nblk);
-        hipLaunchKernelGGL(radix_scatter_kernel, dim3(nblk), dim3(64), 0, s, b.keys[b.cur], b.vals[b.cur], n, shift, nblk,
-                           b.hist, b.keys[o], b.vals[o]);
-        b.cur = o;
-    }
+    const ShufflePlan &pl = a.plan;
+    hipLaunchKernelGGL(shuffle_count_kernel<COMMUNITIES>, dim3(pl.n_tiles), dim3(1024), 0, s, a);
+    hipLaunchKernelGGL(shuffle_prefix_kernel, dim3((unsigned)ceil_div(pl.n_buckets, 64)), dim3(1024), 0, s, pl, a.counts, a.totals);
+    hipLaunchKernelGGL(shuffle_scatter_kernel, dim3(pl.n_tiles), dim3(1024), 0, s, a, COMMUNITIES ? 1 : 0);
+    hipLaunchKernelGGL(shuffle_sort_kernel<COMMUNITIES>, dim3(pl.n_buckets), dim3(256), 0, s, a);
 }
 
 struct BatchPlan {
-    uint64_t *keys[2];
-    uint32_t *vals[2];
-    int32_t *hist;
-    int32_t *present;
-    uint64_t *absent;
-    int32_t *block_of;
+    uint32_t *pos;
+    uint2 *pairs;
+    int32_t *node_comm;
+    int32_t *counts, *totals;
+    int32_t *present;           // [n_comm] training nodes per community, followed by the number of communities that have one
+    int32_t *order, *nodes_of_bucket, *nodes_before;
+    int2 *stretch;
     size_t bytes;
 };
 
 static void plan_batches(int64_t n_train, int32_t n_comm, void *ws, BatchPlan &p)
 {
-    const size_t n = (size_t)(n_train > n_comm ? n_train : n_comm) + 1;
+    const int n = (int)(n_train > n_comm ? n_train : n_comm);
+    const ShufflePlan a = shuffle_plan((int)n_train), b = shuffle_plan(n_comm);
+    const int64_t cells_a = (int64_t)a.n_tiles * a.n_buckets, cells_b = (int64_t)b.n_tiles * b.n_buckets;
     Carver c(ws);
-    p.keys[0] = c.take<uint64_t>(n);
-    p.keys[1] = c.take<uint64_t>(n);
-    p.vals[0] = c.take<uint32_t>(n);
-    p.vals[1] = c.take<uint32_t>(n);
-    p.hist = c.take<int32_t>(256 * (size_t)ceil_div((int64_t)n, SORT_TILE) + 1);
-    p.present = c.take<int32_t>((size_t)n_comm);
-    p.absent = c.take<uint64_t>((size_t)n_comm);
-    p.block_of = c.take<int32_t>((size_t)n_comm);
+    p.pos = c.take<uint32_t>((size_t)n);
+    p.pairs = c.take<uint2>((size_t)n);
+    p.node_comm = c.take<int32_t>((size_t)n_train);
+    p.counts = c.take<int32_t>((size_t)(cells_a > cells_b ? cells_a : cells_b));
+    p.totals = c.take<int32_t>((size_t)(a.n_buckets > b.n_buckets ? a.n_buckets : b.n_buckets));
+    p.present = c.take<int32_t>((size_t)n_comm + 1);
+    p.order = c.take<int32_t>((size_t)n_comm);
+    p.nodes_of_bucket = c.take<int32_t>((size_t)b.n_buckets);
+    p.nodes_before = c.take<int32_t>((size_t)n_comm + 1);
+    p.stretch = c.take<int2>((size_t)n_comm);
     p.bytes = c.bytes();
 }
 
@@ -205,38 +445,31 @@ static cr_status build_batches_impl(const cr_batch_cfg *cfg, const int32_t *trai
     hipStream_t s = static_cast<hipStream_t>(stream);
     const int n = (int)n_train;
     const dim3 blk(256);
-    const dim3 grid_n((unsigned)ceil_div(n, 256)), grid_c((unsigned)ceil_div(n_comm, 256));
     if (cfg->policy == CR_ROOTS_NORAND) {
-        hipLaunchKernelGGL(copy_i32_kernel, grid_n, blk, 0, s, train_ids, n, out_perm);
+        hipLaunchKernelGGL(copy_i32_kernel, dim3((unsigned)ceil_div(n, 256)), blk, 0, s, train_ids, n, out_perm);
         CR_LAUNCH_CHECK();
         return CR_OK;
     }
-    SortBuffers b;
-    b.keys[0] = p.keys[0]; b.keys[1] = p.keys[1]; b.vals[0] = p.vals[0]; b.vals[1] = p.vals[1]; b.hist = p.hist;
-    const bool comm_rand = cfg->policy == CR_ROOTS_COMM_RAND && cfg->mix_count < n_comm;
-    if (comm_rand) {
-        // order of the communities present in the training set: by (key, id), absent ones last
-        hipLaunchKernelGGL(zero_i32_kernel, grid_c, blk, 0, s, p.present, (int64_t)n_comm);
-        hipLaunchKernelGGL(mark_present_kernel, grid_n, blk, 0, s, train_ids, n, comm, p.present);
-        b.cur = 0;
-        hipLaunchKernelGGL(community_keys_kernel, grid_c, blk, 0, s, p.present, n_comm, cfg->seed, cfg->epoch, b.keys[0], p.absent, b.vals[0]);
-        radix_sort(b, n_comm, 64, s);
-        hipLaunchKernelGGL(gather_flag_kernel, grid_c, blk, 0, s, b.vals[b.cur], n_comm, p.absent, b.keys[b.cur]);
-        radix_sort(b, n_comm, 1, s);
-        hipLaunchKernelGGL(block_of_kernel, grid_c, blk, 0, s, b.vals[b.cur], n_comm, cfg->mix_count, p.block_of);
+    ShuffleArgs a;
+    a.train = train_ids; a.node_comm = p.node_comm; a.stretch = nullptr; a.present = p.present; a.n_present = p.present + n_comm;
+    a.seed = cfg->seed; a.epoch = cfg->epoch;
+    a.pos = p.pos; a.counts = p.counts; a.totals = p.totals; a.pairs = p.pairs;
+    if (cfg->policy == CR_ROOTS_COMM_RAND && cfg->mix_count < n_comm) {
+        // the communities present in the training set, in shuffled order; every one's super-block with its stretch
+        hipLaunchKernelGGL(zero_i32_kernel, dim3((unsigned)(ceil_div(n_comm + 1ll, 256) > 1024 ? 1024 : ceil_div(n_comm + 1ll, 256))), blk, 0, s, p.present, n_comm + 1ll);
+        hipLaunchKernelGGL(count_communities_kernel, dim3((unsigned)ceil_div(n, 4 * 64 * COUNT_CHUNKS)), blk, 0, s, train_ids, n, comm, p.present, p.present + n_comm, p.node_comm);
+        a.plan = shuffle_plan(n_comm);
+        a.out = p.order;
+        launch_shuffle<true>(a, s);
+        const dim3 buckets((unsigned)a.plan.n_buckets);
+        hipLaunchKernelGGL(bucket_nodes_kernel, buckets, blk, 0, s, a.plan, p.totals, p.order, p.present, p.nodes_of_bucket);
+        hipLaunchKernelGGL(nodes_before_kernel, buckets, blk, 0, s, a.plan, p.totals, p.order, p.present, p.nodes_of_bucket, n, p.present + n_comm, p.nodes_before);
+        hipLaunchKernelGGL(stretch_kernel, dim3((unsigned)ceil_div(n_comm, 256)), blk, 0, s, p.order, p.nodes_before, p.present + n_comm, cfg->mix_count, p.stretch);
+        a.stretch = p.stretch;
     }
-    // shuffle inside the super-blocks: sort by node key, then stably by super-block number
-    b.cur = 0;
-    hipLaunchKernelGGL(node_keys_kernel, grid_n, blk, 0, s, train_ids, n, cfg->seed, cfg->epoch, b.keys[0], b.vals[0]);
-    radix_sort(b, n, 64, s);
-    if (comm_rand) {
-        hipLaunchKernelGGL(super_block_keys_kernel, grid_n, blk, 0, s, b.vals[b.cur], n, comm, p.block_of, b.keys[b.cur]);
-        int bits = 1;
-        const int64_t n_blocks = ceil_div(n_comm, cfg->mix_count);
-        while ((1ll << bits) < n_blocks) ++bits;
-        radix_sort(b, n, bits, s);
-    }
-    hipLaunchKernelGGL(copy_i32_kernel, grid_n, blk, 0, s, reinterpret_cast<const int32_t *>(b.vals[b.cur]), n, out_perm);
+    a.plan = shuffle_plan(n);
+    a.out = out_perm;
+    launch_shuffle<false>(a, s);
     CR_LAUNCH_CHECK();
     return CR_OK;
 }

@@ -62,3 +62,29 @@ def test_unordered_membership_absent_communities_and_tiny_sets(torch_mod):
     for epoch in range(4):
         want = oracle.build_batches(1, 1, 1, epoch, two, comm, 37)
         assert np.array_equal(run_gpu(torch_mod, 1, 1, 1, epoch, two, comm, 37), want)
+
+
+# one bucket, the edge of a bucket (512 positions), several tiles with a ragged last one, and more elements than 4096 buckets of
+# 1024 positions hold (a bucket is then sorted in several stretches)
+@pytest.mark.parametrize("n_train,n_comm,cases", [(511, 3, ((2, 1), (1, 1))), (513, 40, ((2, 1), (1, 7))), (4097, 4000, ((1, 1), (1, 13))),
+                                                  (70_001, 9001, ((2, 1), (1, 1), (1, 1125))), (4_300_000, 700, ((2, 1),))])
+def test_bucket_edges(torch_mod, n_train, n_comm, cases):
+    rng = np.random.default_rng(n_train)
+    n_nodes = n_train + n_train // 3
+    comm = np.sort(rng.integers(0, n_comm, size=n_nodes)).astype(np.int32)
+    train = np.sort(rng.permutation(n_nodes)[:n_train]).astype(np.int32)
+    for policy, mix in cases:
+        print(f"case buckets n_train={n_train} n_comm={n_comm} policy={policy} mix={mix}", flush=True)
+        want = oracle.build_batches(policy, mix, 3, 2, train, comm, n_comm)
+        assert np.array_equal(run_gpu(torch_mod, policy, mix, 3, 2, train, comm, n_comm, 1024), want), (policy, mix)
+
+
+def test_ids_given_many_times(torch_mod):
+    """More equal keys than a bucket's LDS holds: not what the call is for, but it has always given the sorted order."""
+    rng = np.random.default_rng(4)
+    comm = np.sort(rng.integers(0, 5, size=9000)).astype(np.int32)
+    train = np.sort(np.concatenate([np.full(3001, 4321), rng.integers(0, 9000, size=2500)])).astype(np.int32)
+    for policy, mix in ((2, 1), (1, 2)):
+        print(f"case repeated ids policy={policy}", flush=True)
+        want = oracle.build_batches(policy, mix, 3, 2, train, comm, 5)
+        assert np.array_equal(run_gpu(torch_mod, policy, mix, 3, 2, train, comm, 5, 1024), want)
