@@ -60,6 +60,7 @@ struct SelectArgs {
     int64_t out_indptr_stride;
     int32_t *out_ids;            // [G][out_stride]
     int64_t out_stride;
+    int32_t rows_per_wave;       // destination rows a wave of select_quad_kernel takes (at most QUAD_ROWS)
     uint32_t exact_select;       // verification aid: no pre-filter thresholds, every ranking on full (key, slot) pairs
 };
 
@@ -691,7 +692,9 @@ __device__ __forceinline__ bool keys_apart(float hi, float m_hi, float lo, float
     return lo - hi > slack;
 }
 
-constexpr int QUAD_ROWS = 32;            // destination rows per wave
+constexpr int QUAD_ROWS = 32;            // destination rows per wave, ...
+constexpr int QUAD_MIN_ROWS = 2;         // ... and as few as this
+constexpr int QUAD_FILL_WAVES = 8192;    // until there are this many waves (eight per SIMD)
 constexpr int QUAD_MAX_DEG = 4 * WAVE;   // longest row a pass holds
 
 struct alignas(16) QuadRow {
@@ -1114,7 +1117,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 2 ?
     uint32_t *rowstat = rowstat_s[MODE == 2 ? wv : 0];
     const int g = blockIdx.y;
     const int n_dst = group_n_dst(a.prev_hdr, g, a.n_roots_total, a.batch_size);
-    const int row0 = (int)(blockIdx.x * 4 + wv) * QUAD_ROWS;
+    const int row0 = (int)(blockIdx.x * 4 + wv) * a.rows_per_wave;
     if (row0 >= n_dst) return;
     const int lane = lane_id();
 
@@ -1123,7 +1126,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 2 ?
     int64_t mbase = 0;
     int mdeg = 0;
     int32_t *mout = nullptr;
-    if (lane < QUAD_ROWS && row0 + lane < n_dst) {
+    if (lane < a.rows_per_wave && row0 + lane < n_dst) {
         mv = a.dst_ids[(int64_t)g * a.dst_stride + row0 + lane];
         mbase = a.g_indptr[mv];
         const int64_t d = a.g_indptr[mv + 1] - mbase;
@@ -1996,7 +1999,15 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         }
         sa.exact_select = (cfg->flags & CR_SAMPLE_EXACT_RANKING) ? 1u : 0u;
         const dim3 sel_grid((unsigned)ceil_div(cap_dst, 4 * SEL_ROWS), n_batches);
-        const dim3 quad_grid((unsigned)ceil_div(cap_dst, 4 * QUAD_ROWS), n_batches);
+        // Fewer rows per wave where 32 of them leave the chip short of waves: a wave's passes and long rows are taken one
+        // after another, so a hop of a thousand roots, or of rows of hundreds of neighbours, lasts as long as its slowest
+        // wave.  The packing of short rows into passes is looser then, which costs nothing on a chip that is not full.
+        // Eight batches of the reddit-like graph at p = 0.9 (256 and 2816 waves of 32 rows): whole sampling 845 -> 649 us
+        // (668 with at least 4 rows per wave); 32 products-like batches 1356 -> 1325; a group of one 64-root batch
+        // 120 -> 113 us with its training step.  Half or twice the number of waves asked for measures the same.
+        sa.rows_per_wave = QUAD_ROWS;
+        while (sa.rows_per_wave > QUAD_MIN_ROWS && ceil_div(cap_dst, sa.rows_per_wave) * n_batches < QUAD_FILL_WAVES) sa.rows_per_wave /= 2;
+        const dim3 quad_grid((unsigned)ceil_div(cap_dst, 4 * sa.rows_per_wave), n_batches);
         // Input-side block in global ids, every row keeps min(fanout, degree) neighbours: counts and row pointers first
         // (they need no selection), then the selection writes the chosen ids straight into the block.
         const bool direct_out = l == 0 && (cfg->flags & CR_SAMPLE_INPUT_GLOBAL_IDS) && !sa.strict_p1;
