@@ -1236,7 +1236,8 @@ struct ScanArgs {
     int64_t n_roots_total;
     int32_t batch_size;
     int32_t mode;          // 0: row counts -> indptr ; 1: new-node counts -> offsets ; 2: source counts -> t_indptr ;
-                           // 3: n_fixed values per batch, no header involved
+                           // 3: n_fixed values per batch, no header involved ;
+                           // 4: as 0, the counts min(fanout, degree) taken here (blocks of one tile)
     const int32_t *in;
     int64_t in_stride;
     int32_t *out;
@@ -1248,6 +1249,10 @@ struct ScanArgs {
     const int32_t *tile_before;   // optional (one batch only): sum of everything in front of each tile, computed beforehand
     int32_t cap_src;              // mode 1: entries the frontier array holds
     int64_t *async_status;        // mode 1: status words of the caller's context, or NULL
+    const int64_t *g_indptr;      // mode 4
+    const int32_t *dst_ids;
+    int64_t dst_stride;
+    int32_t fanout;
 };
 
 // out[0..n] = exclusive prefix sums of in[0..n) per batch (blockIdx.y).  A workgroup owns one tile of 256 x 16
@@ -1307,7 +1312,15 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(ScanArgs a)
 #pragma unroll
     for (int k = 0; k < SCAN_ITEMS; ++k) {
         const int j = k * SCAN_THREADS + (int)threadIdx.x;
-        tile[j + j / SCAN_ITEMS] = first + j < n ? in[first + j] : 0;
+        int v = 0;
+        if (a.mode != 4) {
+            v = first + j < n ? in[first + j] : 0;
+        } else if (j < n) {
+            const int32_t node = a.dst_ids[(int64_t)g * a.dst_stride + j];
+            const int64_t d = a.g_indptr[node + 1] - a.g_indptr[node];
+            v = (int)(d < a.fanout ? d : a.fanout);
+        }
+        tile[j + j / SCAN_ITEMS] = v;
     }
     __syncthreads();
     int *mine = tile + (int)threadIdx.x * (SCAN_ITEMS + 1);
@@ -1337,7 +1350,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(ScanArgs a)
     if (threadIdx.x == 0 && n <= first + SCAN_TILE) {        // the last tile
         const int total = before + tile_total;
         out[n] = total;
-        if (a.mode == 0) {
+        if (a.mode == 0 || a.mode == 4) {
             hdr[CR_HDR_N_DST] = n_dst;
             hdr[CR_HDR_NNZ] = total;
             // a block sampled below a frontier that was cut short is as invalid as that frontier
@@ -1582,6 +1595,10 @@ struct DedupArgs {
     int32_t *t_tmp;           // [G][cap_nnz] destination rows in arrival order
     int32_t *t_pos;           // [G][cap_nnz] where each edge landed in t_tmp
     int64_t tt_stride;        // stride of t_tmp / t_pos
+    int32_t *first;           // [G][cap_nnz] first appearance of every edge's neighbour (frontier in LDS; in t_pos' room)
+    int64_t first_stride;
+    int32_t *edge_rows;       // [G][cap_nnz] destination row of every edge, for the transpose in LDS, or NULL
+    int64_t edge_rows_stride;
 };
 
 // maps a thread to (row, j): gw lanes per row
@@ -1684,6 +1701,7 @@ __global__ __launch_bounds__(256) void relabel_kernel(DedupArgs a)
     a.indices[(int64_t)g * a.indices_stride + rstart + j] = (int32_t)local;
     if (a.gather_ids) a.gather_ids[(int64_t)g * a.indices_stride + rstart + j] = u;
     if (a.tcount) atomicAdd(&a.tcount[(int64_t)g * a.t_stride + local], 1);
+    if (a.edge_rows) a.edge_rows[(int64_t)g * a.edge_rows_stride + rstart + j] = row;
 }
 
 // input-side block left in global ids: compact the chosen neighbours into CSR order, copy the
@@ -1749,6 +1767,468 @@ __global__ __launch_bounds__(256) void t_rank_kernel(DedupArgs a)
     a.t_indices[(int64_t)g * a.indices_stride + s0 + rank] = row;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Frontier of a hop in LDS.  The tables above live in memory, where an atomic of one XCD is resolved behind the caches
+// all XCDs share; insert / mark / assign / relabel / reset, the scans between them and the clearing of a table were 335 us of
+// a group of 32 products-like batches (second hop).  Here the ids of a hop (destination nodes and chosen neighbours) are split
+// into parts of about LIST_MEAN entries; a workgroup reads all of the batch's ids, keeps those of its part in an LDS list and
+// finds every id's first appearance with an LDS table.  What bounds it is asking every id once per part (a dozen
+// instructions each, and an L2 read), so the asking is kept to shifts and xors and the parts to 32.
+// Then one kernel numbers the first appearances (a bit per edge in LDS) and relabels, and one transposes the block, each source
+// range in its own workgroup.  A hop that is one part (the hop at the roots) does all three in one workgroup and launch.
+// The chosen neighbours are stored as the block's edges are (row pointers are known before the selection); position n_dst + e
+// is that of edge e.  Order, labels and transposes are those of the tables, bit for bit.
+// ---------------------------------------------------------------------------------------------
+constexpr int HOP_THREADS = 1024;
+constexpr int LIST_CAP = 11264;                 // ids of one part (11 per thread)
+constexpr int LIST_PER = LIST_CAP / HOP_THREADS;
+constexpr int LIST_MEAN = 9216;                 // ids a part is sized for; the rest is for ids that repeat
+constexpr int PART_TABLE = 16384;
+constexpr int PARTS_MAX = 32;
+constexpr int PARTS_MIN = 8;                    // (a group of 32 batches then fills the 256 compute units)
+constexpr int NUMBER_WORDS = 5120;              // 64 edges each (a multiple of HOP_THREADS words)
+constexpr int T_SOURCES = 11264;                // sources of one transposed range (at least LIST_CAP)
+constexpr int T_LIST = 14336;                   // edges of one transposed range
+constexpr int T_MEAN = 9216;
+constexpr int T_PARTS_MAX = 40;
+constexpr int T_RANK_MAX = 1024;                // longest segment whose entries count their rank; longer ones are sorted
+constexpr size_t DEDUP_LDS_BYTES = (size_t)(2 * LIST_CAP + PART_TABLE) * 4;
+constexpr size_t NUMBER_LDS_BYTES = (size_t)NUMBER_WORDS * 12;
+constexpr size_t T_LDS_BYTES = (size_t)(T_SOURCES + 1 + 2 * T_LIST + 32) * 4;
+static_assert(PARTS_MAX * LIST_MEAN <= NUMBER_WORDS * 64, "the numbering pass holds a bit per edge");
+static_assert(T_SOURCES <= (1 << 14) && T_SOURCES >= LIST_CAP, "a list entry holds the source in 14 bits; a hop of one part is one range");
+static_assert(DEDUP_LDS_BYTES + 256 <= 160 * 1024 && T_LDS_BYTES + 256 <= 160 * 1024, "LDS of a compute unit");
+
+// a bijection of the 32-bit integers whose every output bit depends on every input bit (the finaliser of MurmurHash3)
+__device__ __forceinline__ uint32_t mix32(uint32_t h)
+{
+    h ^= h >> 16; h *= 0x85EBCA6Bu;
+    h ^= h >> 13; h *= 0xC2B2AE35u;
+    return h ^ (h >> 16);
+}
+
+// Which of `parts` (a power of two, at most 32) parts an id belongs to: its bits folded onto five.  Every id of the hop
+// is asked once per part, and 32-bit products run at a quarter of the rate of shifts and xors on this chip: with mix32 here the
+// asking was 60 % of the kernel.  Ids that all fold onto one value are not lost, they overflow the part's list.
+__device__ __forceinline__ uint32_t id_part(uint32_t id, uint32_t parts)
+{
+    const uint32_t x = id ^ (id >> 15);
+    return xor3(x, x >> 5, x >> 10) & (parts - 1u);
+}
+
+struct HopShared {
+    int count, overflow, below, n_long;
+    int scan[17];
+};
+
+// A workgroup goes over src[0..n) and appends (value - `minus`, index + `plus`) of the entries that `mine` accepts to
+// two LDS lists of `cap` entries; *count keeps counting past their end.  The loop is what a hop costs per part: the bounds
+// are checked in the last round only, and a wave takes its place in the lists once per U entries of every lane.
+template <int U, typename Mine>
+__device__ __forceinline__ void collect(const int32_t *src, int n, Mine &&mine, int minus, int plus, uint32_t *values, uint32_t *places, int cap, int *count)
+{
+    const int tid = threadIdx.x, lane = lane_id();
+    auto round = [&](int i0, auto checked) {
+        constexpr bool CHECKED = decltype(checked)::value;
+        int32_t x[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) x[k] = src[CHECKED ? min(i0 + k * HOP_THREADS + tid, n - 1) : i0 + k * HOP_THREADS + tid];
+        bool take[U];
+        int total = 0;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            take[k] = mine(x[k], !CHECKED || i0 + k * HOP_THREADS + tid < n);
+            total += __popcll(__ballot(take[k]));
+        }
+        if (total == 0) return;
+        int at = 0;
+        if (lane == 0) at = atomicAdd(count, total);
+        at = __builtin_amdgcn_readfirstlane(at);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const uint64_t m = __ballot(take[k]);
+            if (take[k]) {
+                const int slot = lanes_below(m, at);
+                if (slot < cap) {
+                    values[slot] = (uint32_t)(x[k] - minus);
+                    places[slot] = (uint32_t)(i0 + k * HOP_THREADS + tid + plus);
+                }
+            }
+            at += __popcll(m);
+        }
+    };
+    int i0 = 0;
+    for (; i0 + U * HOP_THREADS <= n; i0 += U * HOP_THREADS) round(i0, std::false_type{});
+    if (i0 < n) round(i0, std::true_type{});
+}
+
+// first[e] = smallest position (destination rows first, then edges) at which edge e's neighbour appears, for the edges whose
+// neighbour belongs to this part
+__device__ __forceinline__ void hop_first(const DedupArgs &a, int g, int n_dst, int nnz, uint32_t part, uint32_t parts, uint32_t *lds, HopShared &sh)
+{
+    uint32_t *lid = lds, *lpos = lds + LIST_CAP, *table = lds + 2 * LIST_CAP;
+    const int tid = threadIdx.x;
+    const int32_t *dst = a.dst_ids + (int64_t)g * a.dst_stride, *sel = a.sel + (int64_t)g * a.sel_stride;
+    int32_t *first = a.first + (int64_t)g * a.first_stride;
+    const int total = n_dst + nnz;
+    auto id_at = [&](int i) { return (uint32_t)(i < n_dst ? dst[i] : sel[i - n_dst]); };
+    for (int i = tid; i < PART_TABLE; i += HOP_THREADS) table[i] = ~0u;
+    if (tid == 0) { sh.count = 0; sh.overflow = 0; }
+    __syncthreads();
+    auto mine = [&](int32_t id, bool have) { return have && id_part((uint32_t)id, parts) == part; };
+    collect<4>(dst, n_dst, mine, 0, 0, lid, lpos, LIST_CAP, &sh.count);
+    collect<16>(sel, nnz, mine, 0, n_dst, lid, lpos, LIST_CAP, &sh.count);
+    __syncthreads();
+    const int count = sh.count;
+    if (count <= LIST_CAP) {
+        // An id's entries agree on the one that got the table's slot first and leave the smallest position there.  A lane
+        // goes through its entries on its own, so a wave takes as many rounds as its slowest lane has probes in all (~30),
+        // not the longest probe of every entry in turn (~90).
+        uint32_t pos[LIST_PER], is_first = 0;
+#pragma unroll
+        for (int k = 0; k < LIST_PER; ++k) pos[k] = lpos[tid + k * HOP_THREADS];
+        {
+            int i = tid, k = 0;
+            uint32_t id = lid[i], h = mix32(id), s = h & (PART_TABLE - 1);
+            while (__ballot(i < count) != 0) {                 // (ends: the table has more slots than the list has entries)
+                if (i < count) {
+                    const uint32_t old = atomicCAS(&table[s], ~0u, (uint32_t)i);
+                    const bool got = old == ~0u, same = lid[got ? (uint32_t)i : old] == id && !got;
+                    if (got) is_first |= 1u << k;
+                    if (same) lid[i] = old;                    // (nobody asks for the id of an entry the table does not name)
+                    if (got || same) {
+                        i += HOP_THREADS;
+                        ++k;
+                        id = lid[min(i, LIST_CAP - 1)];
+                        h = mix32(id);
+                        s = h & (PART_TABLE - 1);
+                    } else {
+                        s = (s + ((h >> 14) | 1u)) & (PART_TABLE - 1);
+                    }
+                }
+            }
+        }
+        __syncthreads();                                       // (every own position has been read)
+#pragma unroll
+        for (int k = 0; k < LIST_PER; ++k)
+            if (tid + k * HOP_THREADS < count && !((is_first >> k) & 1u)) atomicMin(&lpos[lid[tid + k * HOP_THREADS]], pos[k]);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < LIST_PER; ++k) {
+            const int i = tid + k * HOP_THREADS;
+            if (i < count && (int)pos[k] >= n_dst) first[(int)pos[k] - n_dst] = (int32_t)lpos[((is_first >> k) & 1u) ? (uint32_t)i : lid[i]];
+        }
+        return;
+    }
+    // More entries than the list holds (an id that very many rows share): a table of (id, position) filled straight from the
+    // ids; more distinct ids than it holds: the part in 2, 4, .. slices, by bits of the hash that nothing else uses.
+    uint32_t *keys = lds, *vals = lds + PART_TABLE;
+    static_assert(2 * PART_TABLE <= 2 * LIST_CAP + PART_TABLE, "the fallback's table fits the list's room");
+    for (int bits = 0; bits <= 18; ++bits) {          // (18: at most 2^14 ids are left per slice, each with a slot of its own)
+        bool done = true;
+        for (uint32_t slice = 0; slice < (1u << bits) && done; ++slice) {
+            auto in_slice = [&](uint32_t id, uint32_t h) { return id_part(id, parts) == part && ((h >> 14) & ((1u << bits) - 1u)) == slice; };
+            __syncthreads();
+            for (int i = tid; i < PART_TABLE; i += HOP_THREADS) { keys[i] = ~0u; vals[i] = ~0u; }
+            if (tid == 0) sh.overflow = 0;
+            __syncthreads();
+            for (int i = tid; i < total; i += HOP_THREADS) {
+                const uint32_t id = id_at(i), h = mix32(id);
+                if (!in_slice(id, h)) continue;
+                uint32_t s = h & (PART_TABLE - 1), probes = 0;
+                for (; probes < PART_TABLE; ++probes, s = (s + 1) & (PART_TABLE - 1)) {
+                    const uint32_t old = atomicCAS(&keys[s], ~0u, id);
+                    if (old == ~0u || old == id) break;
+                }
+                if (probes < PART_TABLE) atomicMin(&vals[s], (uint32_t)i);
+                else sh.overflow = 1;
+            }
+            __syncthreads();
+            done = sh.overflow == 0;             // (uniform: read between barriers)
+            if (!done) break;
+            for (int i = n_dst + tid; i < total; i += HOP_THREADS) {
+                const uint32_t id = id_at(i), h = mix32(id);
+                if (!in_slice(id, h)) continue;
+                uint32_t s = h & (PART_TABLE - 1);
+                while (keys[s] != id) s = (s + 1) & (PART_TABLE - 1);
+                first[i - n_dst] = (int32_t)vals[s];
+            }
+        }
+        if (done) return;
+    }
+}
+
+// Positions of the first appearances in the frontier, and the relabelled edges of one stretch of the block: the workgroup
+// marks the first appearances of all edges up to the end of its stretch (an edge's first appearance never lies behind
+// it), so the stretches need nothing from each other.  Returns the frontier's length (last stretch only).
+__device__ __forceinline__ int hop_number(const DedupArgs &a, int g, int n_dst, int nnz, int chunk, int chunks, uint32_t *lds, HopShared &sh)
+{
+    unsigned long long *bits = reinterpret_cast<unsigned long long *>(lds);
+    int *pre = reinterpret_cast<int *>(lds + 2 * NUMBER_WORDS);
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / WAVE;
+    const int32_t *dst = a.dst_ids + (int64_t)g * a.dst_stride, *sel = a.sel + (int64_t)g * a.sel_stride;
+    const int32_t *first = a.first + (int64_t)g * a.first_stride;
+    int32_t *src = a.src_ids + (int64_t)g * a.src_stride, *indices = a.indices + (int64_t)g * a.indices_stride;
+    const int32_t *indptr = a.indptr + (int64_t)g * a.indptr_stride;
+    const int r0 = (int)((int64_t)n_dst * chunk / chunks), r1 = (int)((int64_t)n_dst * (chunk + 1) / chunks);
+    const int e0 = chunk == 0 ? 0 : indptr[r0], e1 = chunk == chunks - 1 ? nnz : indptr[r1];
+    const int w1 = (e1 + 63) / 64;
+    constexpr int U = 16, NW = HOP_THREADS / WAVE;
+    for (int w = wave; w < w1; w += U * NW) {
+        int32_t f[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) f[k] = first[min((w + k * NW) * 64 + lane, nnz - 1)];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int e = (w + k * NW) * 64 + lane;
+            const uint64_t m = __ballot(e < nnz && f[k] == n_dst + e);
+            if (lane == 0 && w + k * NW < w1) bits[w + k * NW] = m;
+        }
+    }
+    __syncthreads();
+    constexpr int PER = NUMBER_WORDS / HOP_THREADS;
+    int x[PER], sum = 0, total;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        x[k] = tid * PER + k < w1 ? __popcll(bits[tid * PER + k]) : 0;
+        sum += x[k];
+    }
+    int run = block_exclusive_scan_1024(sum, sh.scan, total);
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        pre[tid * PER + k] = run;
+        run += x[k];
+    }
+    __syncthreads();
+    for (int i = r0 + tid; i < r1; i += HOP_THREADS) src[i] = dst[i];
+#pragma unroll 4
+    for (int e = e0 + tid; e < e1; e += HOP_THREADS) {
+        const int f = first[e];
+        const int32_t u = sel[e];
+        int local = f;
+        if (f >= n_dst) {
+            const int q = f - n_dst;
+            local = n_dst + pre[q >> 6] + __popcll(bits[q >> 6] & ((1ull << (q & 63)) - 1ull));
+            if (q == e && local < a.cap_src) src[local] = u;           // (a frontier cut short: the block is marked invalid)
+        }
+        if (local >= a.cap_src) local = 0;                             // only in a block that is marked invalid
+        indices[e] = local;
+        if (a.gather_ids) a.gather_ids[(int64_t)g * a.indices_stride + e] = u;
+    }
+    // the destination row of every edge of the stretch takes the place of its neighbour's id (which no other stretch reads)
+    if (a.edge_rows) {
+        __syncthreads();
+        const int gw_bits = __builtin_ctz(a.gw), lanes = (r1 - r0) << gw_bits;
+#pragma unroll 4
+        for (int t = tid; t < lanes; t += HOP_THREADS) {
+            const int row = r0 + (t >> gw_bits), e = indptr[row] + (t & (a.gw - 1));
+            if (e < indptr[row + 1]) a.edge_rows[(int64_t)g * a.edge_rows_stride + e] = row;
+        }
+    }
+    int n_src = 0;
+    if (chunk == chunks - 1) {
+        const int need = n_dst + total;
+        n_src = min(need, a.cap_src);
+        if (tid == 0) {
+            int32_t *hdr = a.hdr + (int64_t)g * CR_HDR_WORDS;
+            hdr[CR_HDR_N_SRC] = n_src;
+            if (need > a.cap_src) {            // only possible with capacities below the bound
+                atomicOr(&hdr[CR_HDR_STATUS], CR_ASYNC_FRONTIER_OVERFLOW);
+                if (a.async_status) {
+                    atomicOr(reinterpret_cast<unsigned long long *>(a.async_status), (unsigned long long)CR_ASYNC_FRONTIER_OVERFLOW);
+                    atomicMax(reinterpret_cast<long long *>(a.async_status + 1), (long long)need);
+                }
+            }
+        }
+    }
+    return n_src;
+}
+
+// sorts x[0..n) ascending (n workgroup-uniform): a merge network whose every exchange moves the smaller value to the lower
+// index, so the places from n on act as values behind all others
+__device__ __forceinline__ void merge_network(int32_t *x, int n)
+{
+    auto exchange = [&](int i, int j) {
+        if (j >= n) return;
+        const int32_t p = x[i], q = x[j];
+        if (q < p) { x[i] = q; x[j] = p; }
+    };
+    for (int size = 2; size < 2 * n; size *= 2) {
+        __syncthreads();
+        for (int i = threadIdx.x; i < n; i += HOP_THREADS)
+            if ((i & (size - 1)) < size / 2) exchange(i, i ^ (size - 1));
+        for (int d = size / 4; d > 0; d /= 2) {
+            __syncthreads();
+            for (int i = threadIdx.x; i < n; i += HOP_THREADS)
+                if ((i & d) == 0) exchange(i, i + d);
+        }
+    }
+    __syncthreads();
+}
+
+// Transposed block of one range of sources: row pointers and, per source, the destination rows that use it, ascending.
+__device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_dst, int n_src, int nnz, int part, int parts, uint32_t *lds, HopShared &sh)
+{
+    int *start = reinterpret_cast<int *>(lds);                                  // [T_SOURCES + 1]
+    int32_t *list = reinterpret_cast<int32_t *>(lds) + T_SOURCES + 1;           // [T_LIST] row << 14 | source, as they come
+    int32_t *sorted = list + T_LIST;                                            // [T_LIST] ... source by source
+    int *longs = reinterpret_cast<int *>(sorted + T_LIST);                      // [32] sources with long segments
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / WAVE;
+    const int32_t *indices = a.indices + (int64_t)g * a.indices_stride;
+    int32_t *t_indptr = a.t_indptr + (int64_t)g * a.t_indptr_stride, *t_indices = a.t_indices + (int64_t)g * a.indices_stride;
+    const int range = (n_src + parts - 1) / parts;
+    const int lo = min(n_src, part * range), hi = min(n_src, lo + range), n = hi - lo;
+    if (part == parts - 1 && tid == 0) t_indptr[n_src] = nnz;
+    if (n <= 0) return;                                                        // (uniform)
+    for (int i = tid; i <= n; i += HOP_THREADS) start[i] = 0;
+    if (tid == 0) { sh.count = 0; sh.below = 0; sh.n_long = 0; }
+    __syncthreads();
+    // the range's edges: source and place of every edge into the lists (the lists' two arrays, for now), then the row in its
+    // place's stead, both packed into one word
+    const int32_t *edge_rows = a.edge_rows + (int64_t)g * a.edge_rows_stride;
+    int below = 0;
+    collect<16>(indices, nnz, [&](int32_t s, bool have) {
+        below += have && s < lo ? 1 : 0;
+        return have && (uint32_t)(s - lo) < (uint32_t)n;
+    }, lo, 0, reinterpret_cast<uint32_t *>(sorted), reinterpret_cast<uint32_t *>(list), T_LIST, &sh.count);
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) below += __shfl_xor(below, off);
+    if (lane == 0) atomicAdd(&sh.below, below);
+    __syncthreads();
+    const int count = sh.count, base = sh.below;
+    // starts of the segments from their lengths (a thread owns consecutive sources)
+    auto scan_starts = [&]() {
+        constexpr int PER = T_SOURCES / HOP_THREADS;
+        int sum = 0, total;
+        const int s0 = tid * PER;
+        int x[PER];
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            x[k] = s0 + k < n ? start[s0 + k] : 0;
+            sum += x[k];
+        }
+        int run = block_exclusive_scan_1024(sum, sh.scan, total);
+#pragma unroll
+        for (int k = 0; k < PER; ++k) {
+            if (s0 + k < n) {
+                start[s0 + k] = run;
+                t_indptr[lo + s0 + k] = base + run;
+            }
+            run += x[k];
+        }
+        if (tid == 0) start[n] = total;
+        __syncthreads();
+    };
+    if (count <= T_LIST) {
+#pragma unroll 4
+        for (int i = tid; i < count; i += HOP_THREADS) list[i] = (edge_rows[list[i]] << 14) | sorted[i];      // (rows < 2^17)
+        __syncthreads();
+        // (rolled loops: unrolled over the list, this function was 40 KB of code, most of which ran once per workgroup straight
+        // from memory)
+        for (int i = tid; i < count; i += HOP_THREADS) atomicAdd(&start[list[i] & 16383], 1);
+        __syncthreads();
+        scan_starts();
+        for (int i = tid; i < count; i += HOP_THREADS) {
+            const int32_t x = list[i];
+            sorted[atomicAdd(&start[x & 16383], 1)] = x;                       // start[s] becomes the segment's end
+        }
+        __syncthreads();
+        for (int i = tid; i < count; i += HOP_THREADS) {
+            const int32_t x = sorted[i];
+            const int s = x & 16383, s0 = s > 0 ? start[s - 1] : 0, s1 = start[s];
+            if (s1 - s0 > T_RANK_MAX) {
+                if (i == s0) longs[atomicAdd(&sh.n_long, 1)] = s;              // (at most T_LIST / T_RANK_MAX of them)
+                continue;
+            }
+            // (most segments hold one or two rows; the longer ones are read four at a time, or a wave waits out one LDS round
+            // trip per row of its longest segment)
+            int rank = 0;
+            for (int q = s0; q < s1; q += 4) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int32_t y = sorted[min(q + u, s1 - 1)];
+                    rank += (q + u < s1 && (y < x || (y == x && q + u < i))) ? 1 : 0;
+                }
+            }
+            t_indices[base + s0 + rank] = x >> 14;
+        }
+        __syncthreads();
+        for (int l = 0; l < sh.n_long; ++l) {
+            const int s = longs[l], s0 = s > 0 ? start[s - 1] : 0, len = start[s] - s0;
+            merge_network(sorted + s0, len);
+            for (int q = tid; q < len; q += HOP_THREADS) t_indices[base + s0 + q] = sorted[s0 + q] >> 14;
+        }
+        return;
+    }
+    // more edges than the lists hold: lengths and rows in two more passes, the rows in memory
+#pragma unroll 4
+    for (int e = tid; e < nnz; e += HOP_THREADS) {
+        const int s = indices[e] - lo;
+        if ((uint32_t)s < (uint32_t)n) atomicAdd(&start[s], 1);
+    }
+    __syncthreads();
+    scan_starts();
+    int32_t *tmp = a.t_tmp + (int64_t)g * a.tt_stride + base;
+#pragma unroll 4
+    for (int e = tid; e < nnz; e += HOP_THREADS) {
+        const int s = indices[e] - lo, row = edge_rows[e];
+        if ((uint32_t)s < (uint32_t)n) tmp[atomicAdd(&start[s], 1)] = row;     // start[s] becomes the segment's end
+    }
+    __syncthreads();
+    for (int s = wave; s < n; s += HOP_THREADS / WAVE) {
+        const int s0 = s > 0 ? start[s - 1] : 0, len = start[s] - s0;
+        if (len > T_RANK_MAX) continue;
+        for (int q = lane; q < len; q += WAVE) {
+            const int row = tmp[s0 + q];
+            int rank = 0;
+            for (int r = 0; r < len; ++r) rank += (tmp[s0 + r] < row || (tmp[s0 + r] == row && r < q)) ? 1 : 0;
+            t_indices[base + s0 + rank] = row;
+        }
+    }
+    for (int s = 0; s < n; ++s) {                                              // (uniform)
+        const int s0 = s > 0 ? start[s - 1] : 0, len = start[s] - s0;
+        if (len <= T_RANK_MAX) continue;
+        merge_network(tmp + s0, len);
+        for (int q = tid; q < len; q += HOP_THREADS) t_indices[base + s0 + q] = tmp[s0 + q];
+    }
+}
+
+#define CR_HOP()                                                                      \
+    extern __shared__ __attribute__((aligned(16))) uint32_t hop_lds[];                \
+    __shared__ HopShared sh;                                                          \
+    const int g = blockIdx.y;                                                         \
+    const int n_dst = group_n_dst(a.prev_hdr, g, a.n_roots_total, a.batch_size);      \
+    const int nnz = a.hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_NNZ]
+
+__global__ __launch_bounds__(HOP_THREADS) void hop_first_kernel(DedupArgs a)
+{
+    CR_HOP();
+    hop_first(a, g, n_dst, nnz, blockIdx.x, gridDim.x, hop_lds, sh);
+}
+
+__global__ __launch_bounds__(HOP_THREADS) void hop_number_kernel(DedupArgs a)
+{
+    CR_HOP();
+    hop_number(a, g, n_dst, nnz, (int)blockIdx.x, (int)gridDim.x, hop_lds, sh);
+}
+
+__global__ __launch_bounds__(HOP_THREADS) void hop_transpose_kernel(DedupArgs a)
+{
+    CR_HOP();
+    hop_transpose(a, g, n_dst, a.hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_N_SRC], nnz, (int)blockIdx.x, (int)gridDim.x, hop_lds, sh);
+}
+
+// the three of them for a hop that is one part
+__global__ __launch_bounds__(HOP_THREADS) void hop_kernel(DedupArgs a)
+{
+    CR_HOP();
+    hop_first(a, g, n_dst, nnz, 0u, 1u, hop_lds, sh);
+    __syncthreads();
+    const int n_src = hop_number(a, g, n_dst, nnz, 0, 1, hop_lds, sh);
+    __syncthreads();
+    if (a.t_indptr) hop_transpose(a, g, n_dst, n_src, nnz, 0, 1, hop_lds, sh);
+}
+
 // one thread per 32 adjacency entries: find the row of the first one, then walk
 __global__ __launch_bounds__(256) void edge_classes_kernel(const int64_t *__restrict__ indptr, const int32_t *__restrict__ indices,
                                                            const int32_t *__restrict__ comm, int64_t n_nodes, int64_t n_entries,
@@ -1789,6 +2269,18 @@ struct SamplePlan {
     unsigned long long *newmask, *table;
     size_t bytes;
 };
+
+// the hop kernels' LDS, more than a launch gets without asking
+static bool hop_lds_ready()
+{
+    static const bool ready = [] {
+        const int most = (int)(T_LDS_BYTES > DEDUP_LDS_BYTES ? T_LDS_BYTES : DEDUP_LDS_BYTES);
+        return hipFuncSetAttribute(reinterpret_cast<const void *>(&hop_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, most) == hipSuccess &&
+               hipFuncSetAttribute(reinterpret_cast<const void *>(&hop_first_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)DEDUP_LDS_BYTES) == hipSuccess &&
+               hipFuncSetAttribute(reinterpret_cast<const void *>(&hop_transpose_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)T_LDS_BYTES) == hipSuccess;
+    }();
+    return ready;
+}
 
 static cr_status make_plan(const cr_sample_cfg *cfg, int64_t n_nodes, int32_t batch_size, int32_t n_batches,
                            void *ws, SamplePlan &p)
@@ -1972,6 +2464,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
     const uint32_t q_in = (uint32_t)llround(cfg->p_intra * 65536.0);
     const uint32_t q_out = 65536u - q_in;
     const dim3 blk(256);
+    bool table_clear = false;      // (direct-address table)
     for (int l = p.L - 1; l >= 0; --l) {
         const cr_block_set &b = layers[l];
         const int f = cfg->fanout[l];
@@ -2010,20 +2503,42 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         const dim3 quad_grid((unsigned)ceil_div(cap_dst, 4 * sa.rows_per_wave), n_batches);
         // Input-side block in global ids, every row keeps min(fanout, degree) neighbours: counts and row pointers first
         // (they need no selection), then the selection writes the chosen ids straight into the block.
-        const bool direct_out = l == 0 && (cfg->flags & CR_SAMPLE_INPUT_GLOBAL_IDS) && !sa.strict_p1;
+        const bool global_ids = l == 0 && (cfg->flags & CR_SAMPLE_INPUT_GLOBAL_IDS), tr = !global_ids && b.t_indptr != nullptr;
+        const bool direct_out = global_ids && !sa.strict_p1;
+        // Frontier in LDS: hops of at most 32 parts of ids (294912) whose row pointers are known before the selection, that is
+        // all but the strict setting.  Measured against the tables in memory (all kernels of the hop except its selection):
+        // 32 x 67 K ids (products-like, second hop) 335 -> 90 us, 32 x 6 K ids (its root hop, one workgroup per batch and
+        // one launch instead of nine) 95 -> 33 us, 8 x 280 K ids (reddit-like input hop, 32 parts) 310 -> 177 us.  The cost
+        // grows with ids times parts, the tables' with ids: beyond this the ratio that is left is used up (the 1.1 M ids of
+        // a relabelled products-like input hop would be read 128 times), and the tables serve.  The transpose reads every
+        // edge once per range of sources and is cut off at forty ranges for the same reason.
+        const int64_t hop_items = (int64_t)cap_dst + p.cap_nnz[l];
+        // (workgroups per batch that a hop is cut into at least: small groups are cut finer, or most compute units sit idle)
+        const int hop_chunks = n_batches >= 32 ? PARTS_MIN : (n_batches <= 8 ? 32 : 256 / n_batches);
+        int64_t t_parts = ceil_div(p.cap_nnz[l], T_MEAN);
+        if (t_parts < ceil_div(b.cap_src, T_SOURCES)) t_parts = ceil_div(b.cap_src, T_SOURCES);
+        if (t_parts < hop_chunks) t_parts = hop_chunks;
+        const bool lds_transpose = tr && t_parts <= T_PARTS_MAX && cap_dst < (1 << 17) && hop_lds_ready();
+        const bool lds_hop = !global_ids && !sa.strict_p1 && hop_items <= (int64_t)PARTS_MAX * LIST_MEAN && p.max_nnz_t >= p.cap_nnz[l] &&
+                             (!tr || lds_transpose) && hop_lds_ready();
+        const bool one_part = lds_hop && hop_items <= LIST_CAP;
         ScanArgs sc;
         sc.tile_before = nullptr;
         sc.prev_hdr = prev_hdr; sc.n_roots_total = n_roots_total; sc.batch_size = batch_size;
         sc.mode = 0; sc.in = p.cnt; sc.in_stride = p.max_dst; sc.out = b.indptr; sc.out_stride = b.cap_dst + 1;
         sc.out_copy = nullptr; sc.copy_stride = 0; sc.hdr = b.hdr;
         sc.cap_src = b.cap_src; sc.async_status = async_status();
+        sc.g_indptr = graph->indptr; sc.dst_ids = dst_ids; sc.dst_stride = dst_stride; sc.fanout = f;
         const dim3 scan_grid((unsigned)ceil_div(cap_dst, SCAN_TILE), n_batches);
         sa.out_indptr = nullptr; sa.out_indptr_stride = 0; sa.out_ids = nullptr; sa.out_stride = 0;
-        if (direct_out) {
-            hipLaunchKernelGGL(row_counts_kernel, dim3((unsigned)ceil_div(cap_dst, 256), n_batches), blk, 0, s, graph->indptr, dst_ids, dst_stride,
-                               prev_hdr, n_roots_total, batch_size, f, p.cnt, (int64_t)p.max_dst);
+        if (direct_out || lds_hop) {
+            if (cap_dst <= SCAN_TILE) sc.mode = 4;
+            else
+                hipLaunchKernelGGL(row_counts_kernel, dim3((unsigned)ceil_div(cap_dst, 256), n_batches), blk, 0, s, graph->indptr, dst_ids, dst_stride,
+                                   prev_hdr, n_roots_total, batch_size, f, p.cnt, (int64_t)p.max_dst);
             hipLaunchKernelGGL(scan_kernel, scan_grid, dim3(SCAN_THREADS), 0, s, sc);
-            sa.out_indptr = b.indptr; sa.out_indptr_stride = b.cap_dst + 1; sa.out_ids = b.gather_ids; sa.out_stride = b.cap_nnz;
+            sa.out_indptr = b.indptr; sa.out_indptr_stride = b.cap_dst + 1;
+            sa.out_ids = direct_out ? b.gather_ids : p.sel; sa.out_stride = direct_out ? b.cap_nnz : p.max_nnz;
         }
         if (q_in == q_out) hipLaunchKernelGGL(select_quad_kernel<0>, quad_grid, blk, 0, s, sa);
         else if (q_out == 0 && graph->edge_intra) hipLaunchKernelGGL(select_quad_kernel<1>, quad_grid, blk, 0, s, sa);
@@ -2060,7 +2575,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
             hipLaunchKernelGGL(order_pass_kernel<true>, og, blk, 0, s, oa);
         }
 
-        if (!direct_out) hipLaunchKernelGGL(scan_kernel, scan_grid, dim3(SCAN_THREADS), 0, s, sc);
+        if (!direct_out && !lds_hop) hipLaunchKernelGGL(scan_kernel, scan_grid, dim3(SCAN_THREADS), 0, s, sc);
 
         DedupArgs da;
         da.prev_hdr = prev_hdr; da.n_roots_total = n_roots_total; da.batch_size = batch_size; da.fanout = f;
@@ -2072,7 +2587,9 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         da.indptr = b.indptr; da.indptr_stride = b.cap_dst + 1; da.indices = b.indices; da.indices_stride = b.cap_nnz; da.gather_ids = b.gather_ids;
         da.newcnt = p.cnt; da.newoff = p.newoff; da.newmask = p.newmask; da.row_stride = p.max_dst; da.off_stride = p.max_dst + 1;
         const dim3 grid((unsigned)ceil_div((int64_t)cap_dst * da.gw, 256), n_batches);
-        if (l == 0 && (cfg->flags & CR_SAMPLE_INPUT_GLOBAL_IDS)) {
+        da.first = p.t_pos; da.first_stride = p.max_nnz_t + 1;
+        da.edge_rows = !lds_transpose ? nullptr : (lds_hop ? p.sel : p.t_pos); da.edge_rows_stride = lds_hop ? p.max_nnz : p.max_nnz_t + 1;
+        if (global_ids) {
             da.tcount = nullptr; da.tfill = nullptr; da.t_stride = 0; da.t_indptr = nullptr; da.t_indptr_stride = 0;
             da.t_indices = nullptr; da.t_tmp = nullptr; da.t_pos = nullptr; da.tt_stride = 0;
             if (direct_out) hipLaunchKernelGGL(frontier_head_kernel, dim3((unsigned)ceil_div(cap_dst, 256), n_batches), blk, 0, s, da);
@@ -2080,28 +2597,40 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
             continue;
         }
 
-        if (!p.direct) {
-            const int64_t table_size = 1ll << p.table_bits[l];
-            hipLaunchKernelGGL(fill_u64_kernel, dim3((unsigned)(ceil_div(table_size, 512) < 4096 ? ceil_div(table_size, 512) : 4096), n_batches), blk, 0, s,
-                               p.table, p.table_stride, table_size, EMPTY);
-        } else if (root) {   // once per call; every hop puts the entries it touched back
-            hipLaunchKernelGGL(fill_u64_kernel, dim3((unsigned)(ceil_div(p.table_stride, 512) < 4096 ? ceil_div(p.table_stride, 512) : 4096), n_batches), blk, 0, s,
-                               p.table, p.table_stride, p.table_stride, 0x7FFFFFFF7FFFFFFFull);
-        }
-
-        const bool tr = b.t_indptr != nullptr;
-        da.tcount = tr ? p.tcount : nullptr; da.tfill = p.tfill; da.t_stride = p.max_src_t + 1;
+        da.tcount = tr && !lds_transpose ? p.tcount : nullptr; da.tfill = p.tfill; da.t_stride = p.max_src_t + 1;
         da.t_indptr = b.t_indptr; da.t_indptr_stride = b.cap_src + 1; da.t_indices = b.t_indices;
         da.t_tmp = p.t_tmp; da.t_pos = p.t_pos; da.tt_stride = p.max_nnz_t + 1;
-        hipLaunchKernelGGL(insert_kernel, grid, blk, 0, s, da);
-        hipLaunchKernelGGL(mark_new_kernel, grid, blk, 0, s, da);
-        sc.mode = 1; sc.in = p.cnt; sc.in_stride = p.max_dst; sc.out = p.newoff; sc.out_stride = p.max_dst + 1;
-        hipLaunchKernelGGL(scan_kernel, scan_grid, dim3(SCAN_THREADS), 0, s, sc);
-        hipLaunchKernelGGL(assign_kernel, grid, blk, 0, s, da);
-        hipLaunchKernelGGL(relabel_kernel, grid, blk, 0, s, da);
-        if (p.direct)
-            hipLaunchKernelGGL(reset_kernel, dim3((unsigned)ceil_div(p.cap_src[l], 1024), n_batches), blk, 0, s, da);
-        if (tr) {
+        if (one_part) {
+            hipLaunchKernelGGL(hop_kernel, dim3(1, n_batches), dim3(HOP_THREADS), T_LDS_BYTES > DEDUP_LDS_BYTES ? T_LDS_BYTES : DEDUP_LDS_BYTES, s, da);
+            continue;
+        }
+        if (lds_hop) {
+            int parts = PARTS_MIN;
+            while (parts * (int64_t)LIST_MEAN < hop_items) parts *= 2;
+            hipLaunchKernelGGL(hop_first_kernel, dim3((unsigned)parts, n_batches), dim3(HOP_THREADS), DEDUP_LDS_BYTES, s, da);
+            hipLaunchKernelGGL(hop_number_kernel, dim3((unsigned)hop_chunks, n_batches), dim3(HOP_THREADS), NUMBER_LDS_BYTES, s, da);
+        } else {
+            if (!p.direct) {
+                const int64_t table_size = 1ll << p.table_bits[l];
+                hipLaunchKernelGGL(fill_u64_kernel, dim3((unsigned)(ceil_div(table_size, 512) < 4096 ? ceil_div(table_size, 512) : 4096), n_batches), blk, 0, s,
+                                   p.table, p.table_stride, table_size, EMPTY);
+            } else if (!table_clear) {   // once per call; every hop puts the entries it touched back
+                table_clear = true;
+                hipLaunchKernelGGL(fill_u64_kernel, dim3((unsigned)(ceil_div(p.table_stride, 512) < 4096 ? ceil_div(p.table_stride, 512) : 4096), n_batches), blk, 0, s,
+                                   p.table, p.table_stride, p.table_stride, 0x7FFFFFFF7FFFFFFFull);
+            }
+            hipLaunchKernelGGL(insert_kernel, grid, blk, 0, s, da);
+            hipLaunchKernelGGL(mark_new_kernel, grid, blk, 0, s, da);
+            sc.mode = 1; sc.in = p.cnt; sc.in_stride = p.max_dst; sc.out = p.newoff; sc.out_stride = p.max_dst + 1;
+            hipLaunchKernelGGL(scan_kernel, scan_grid, dim3(SCAN_THREADS), 0, s, sc);
+            hipLaunchKernelGGL(assign_kernel, grid, blk, 0, s, da);
+            hipLaunchKernelGGL(relabel_kernel, grid, blk, 0, s, da);
+            if (p.direct)
+                hipLaunchKernelGGL(reset_kernel, dim3((unsigned)ceil_div(p.cap_src[l], 1024), n_batches), blk, 0, s, da);
+        }
+        if (lds_transpose) {
+            hipLaunchKernelGGL(hop_transpose_kernel, dim3((unsigned)t_parts, n_batches), dim3(HOP_THREADS), T_LDS_BYTES, s, da);
+        } else if (tr) {
             sc.mode = 2; sc.in = p.tcount; sc.in_stride = p.max_src_t + 1; sc.out = b.t_indptr; sc.out_stride = b.cap_src + 1;
             sc.out_copy = p.tfill; sc.copy_stride = p.max_src_t + 1;
             hipLaunchKernelGGL(scan_kernel, dim3((unsigned)ceil_div(b.cap_src, SCAN_TILE), n_batches), dim3(SCAN_THREADS), 0, s, sc);

@@ -34,3 +34,49 @@ def test_rows_per_wave(torch_mod, batch_size, n_batches, p):
     print(f"case rows per wave: {n_batches} batches of {batch_size}, p={p}", flush=True)
     layers, nb = run_gpu(torch_mod, dg, roots, [4, 7], p, False, 3, 1, 2, batch_size)
     compare(layers, nb, graph, roots, [4, 7], p, False, 3, 1, 2, batch_size, f"rows per wave p={p}")
+
+
+def fixed_rows(n_nodes, rows):
+    """Graph whose node i has the neighbours rows(i) (ascending, distinct)."""
+    r = [np.sort(np.asarray(rows(i), dtype=np.int32)) for i in range(n_nodes)]
+    indptr = np.zeros(n_nodes + 1, dtype=np.int64)
+    indptr[1:] = np.cumsum([len(x) for x in r])
+    return indptr, np.concatenate(r), (np.arange(n_nodes) // (n_nodes // 4 + 1)).astype(np.int32)
+
+
+def check(torch_mod, graph, n_roots, batch_size, fanouts, p, what):
+    dg = DeviceGraph(torch_mod, graph, 4, edge_classes=True)
+    roots = np.random.default_rng(2).permutation(len(graph[0]) - 1).astype(np.int32)[:n_roots]
+    print(f"case {what}: {n_roots} roots in batches of {batch_size}, fanouts {fanouts}, p={p}", flush=True)
+    layers, nb = run_gpu(torch_mod, dg, roots, fanouts, p, False, 5, 1, 0, batch_size)
+    compare(layers, nb, graph, roots, fanouts, p, False, 5, 1, 0, batch_size, what)
+
+
+# ids of a hop (rows and chosen neighbours): just one part (11264) and just not, and just the sixteen parts (131072) and not
+@pytest.mark.parametrize("batch_size,fanout", [(1, 1), (64, 1), (1024, 10), (1025, 10), (1024, 64), (11915, 10), (11916, 10)])
+def test_frontier_parts(torch_mod, batch_size, fanout):
+    rng = np.random.default_rng(batch_size)
+    n = 20_000
+    graph = fixed_rows(n, lambda i: np.unique(rng.integers(0, n, size=i % (2 * fanout + 1))))
+    check(torch_mod, graph, min(n, 2 * batch_size - batch_size // 3), batch_size, [2, fanout], 0.5, "frontier parts")
+
+
+# a handful of nodes that every row chooses: lists of a part and of a range of sources that overflow, segments that are sorted
+# rather than ranked, in LDS (15000 edges) and in memory (108000)
+@pytest.mark.parametrize("batch_size,hubs", [(3000, 5), (12_000, 9)])
+def test_every_row_shares_its_neighbours(torch_mod, batch_size, hubs):
+    graph = fixed_rows(15_000, lambda i: 7 * np.arange(hubs) + 400)
+    check(torch_mod, graph, batch_size, batch_size, [3, hubs], 0.5, "shared neighbours")
+
+
+def test_one_part_gets_every_id(torch_mod):
+    """More distinct ids in one part than the table holds: the part is taken in slices."""
+    n = 420_000
+    ids = np.arange(n, dtype=np.uint32)
+    fold = ids ^ (ids >> 15)
+    part0 = ids[((fold ^ (fold >> 5) ^ (fold >> 10)) & 15) == 0].astype(np.int32)       # the kernel's choice of the part, sixteen parts
+    assert len(part0) > 20_000
+    rng = np.random.default_rng(1)
+    picks = np.sort(part0[(rng.integers(0, len(part0) - 20, size=(n, 1)) + np.arange(15))], axis=1)
+    graph = (np.arange(n + 1, dtype=np.int64) * 15, picks.reshape(-1), (np.arange(n) // (n // 4 + 1)).astype(np.int32))
+    check(torch_mod, graph, 8000, 8000, [2, 15], 0.5, "one part")
