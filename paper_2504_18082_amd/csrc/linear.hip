@@ -15,7 +15,9 @@ typedef unsigned int u32x4v __attribute__((ext_vector_type(4)));
 typedef short v4s16 __attribute__((ext_vector_type(4)));
 
 constexpr int TN_BM = 32;     // rows of the operands staged per step of the TN product (a multiple of 16; 96-row splits hold two)
-constexpr int TN_ROW = 144;   // staged row of the TN product: 128 columns + 16 of padding (288 bytes)
+constexpr int TN_DEPTH = 3;      // steps whose loads are in flight
+constexpr int TN_ROW = 160;   // staged row of the TN product: 128 columns + 32 of padding (320 bytes: the four rows that half a wave
+                              // reads with one transpose read lie 16 banks apart)
 
 constexpr int LDS_ROW = 40;   // 32 bf16 of payload + 8 of padding per staged row (80 bytes)
 
@@ -412,168 +414,157 @@ __global__ __launch_bounds__(256) void gemm_nt_small_kernel(NtArgs a, XentArgs x
 // ------------------------------------------------------------------------------------------------
 // The same product for the input layer of the large workloads: tens of thousands of rows, N = 256, any K (K <= 256 takes
 // the streaming kernel further down; this one serves wider inputs, e.g. 602 features.  GraphSAGE: self | aggregate;
-// one-operand layers: all of K from one array).  The tiled kernel
-// above reads every activation row four times (once per 64-column tile) and spends most of its time moving operands;
-// here one workgroup per compute unit takes 256 rows and ALL columns, so activations pass through a compute unit once:
-//   - K is taken in chunks of 128 columns, each operand array's columns in chunks of their own.  A chunk is 256 rows x
-//     256 bytes of activations and 256 x 256 bytes of weights: both are fetched with coalesced 16-byte loads (16 per
-//     thread each) and laid out in LDS with rows padded by 16 bytes, so that the MFMA fragments are conflict-free
-//     16-byte LDS reads; an array's last chunk that reaches past its columns is staged with zeros there;
-//   - the next chunk's loads are issued inside the current chunk's K loop, four per step, and travel under its MFMAs
-//     (issued in one go they hold the wave, the only one on its SIMD, for as long as the memory pipeline takes them);
-//   - a wave owns 64 rows x 256 columns (256 accumulator registers, one wave per SIMD): per 16-wide K step 10 fragment
-//     reads feed 16 MFMAs; the fragments of step s + 1 are requested before the MFMAs of step s are issued, because no
-//     other wave is there to hide the LDS latency;
+// one-operand layers: all of K from one array).  The tiled kernel above reads every activation row four times (once per 64-column
+// tile) and spends most of its time moving operands; here a workgroup takes 128 rows and ALL columns, so activations pass
+// through a compute unit once:
+//   - K is taken in chunks of 64 columns, each operand array's columns in chunks of their own (an array's last chunk may
+//     hold 32).  A chunk is fetched with coalesced 16-byte loads, four pieces of activations and eight of weights per thread,
+//     while the chunk before it is multiplied, and laid out in LDS with rows padded by 16 bytes, so that the MFMA fragments are
+//     conflict-free 16-byte LDS reads;
+//   - a wave owns 64 rows x 128 columns: per 16-wide K step six fragment reads feed eight MFMAs (LDS and matrix cores are about
+//     equally busy);
+//   - 55 KB of LDS and at most 256 registers: two workgroups per compute unit, two waves per SIMD.  One workgroup's MFMAs run
+//     while the other stages, waits at a barrier or stores.  That is what the kernel is built around: 256-row tiles of four waves
+//     alone on their compute unit (chunks of 128 columns, 256 accumulators per lane) took 73 us for 131 K rows x 608 -> 256
+//     where this takes 67, and a last round of few tiles costs half as much with tiles of half the height;
 //   - the accumulators start from the bias; ReLU and the bf16 conversion happen on the way through LDS again, from
-//     where whole 512-byte rows leave.
+//     where 256-byte row pieces leave.
 // ------------------------------------------------------------------------------------------------
-constexpr int WIDE_ROWS = 256;          // rows per workgroup
-constexpr int WIDE_KH = 128;            // K of one chunk
+constexpr int WIDE_ROWS = 128;          // rows per workgroup
+constexpr int WIDE_KC = 64;             // K of one chunk
 constexpr int WIDE_N = 256;
-constexpr int WIDE_LROW = WIDE_KH + 8;  // staged row: 128 bf16 + 8 of padding (272 bytes)
-constexpr int WIDE_OROW = WIDE_N + 8;   // staged output row
-constexpr size_t WIDE_LDS_BYTES = (size_t)2 * 256 * WIDE_LROW * sizeof(uint16_t) + WIDE_N * sizeof(float);
+constexpr int WIDE_LROW = WIDE_KC + 8;  // staged row: 64 bf16 + 8 of padding (144 bytes)
+constexpr int WIDE_OROW = 128 + 8;      // staged output row of one wave
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_nt_wide_kernel(NtArgs a)
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_nt_wide_kernel(NtArgs a)
 {
-    constexpr int KSTEPS = WIDE_KH / 16, NTILES = WIDE_N / 32;
-    extern __shared__ __attribute__((aligned(16))) uint16_t wide_lds[];
-    uint16_t *Ws = wide_lds;                                   // [256 n][WIDE_LROW]
-    uint16_t *As = wide_lds + 256 * WIDE_LROW;                 // [256 m][WIDE_LROW]
-    float *bias_s = reinterpret_cast<float *>(wide_lds + 2 * 256 * WIDE_LROW);
-    static_assert((size_t)4 * 64 * WIDE_OROW * sizeof(uint16_t) <= (size_t)2 * 256 * WIDE_LROW * sizeof(uint16_t), "output staging must fit");
+    constexpr int KSTEPS = WIDE_KC / 16, AP = WIDE_ROWS * 8 / 256, WP = WIDE_N * 8 / 256;     // pieces of 16 bytes per thread
+    __shared__ __attribute__((aligned(16))) uint16_t lds[(WIDE_ROWS + WIDE_N) * WIDE_LROW];
+    __shared__ __attribute__((aligned(16))) float bias_s[WIDE_N];
+    uint16_t *As = lds;                                        // [128 m][WIDE_LROW]
+    uint16_t *Ws = lds + WIDE_ROWS * WIDE_LROW;                // [256 n][WIDE_LROW]
+    static_assert(4 * 32 * WIDE_OROW <= (WIDE_ROWS + WIDE_N) * WIDE_LROW, "output staging must fit");
     const int M = min(a.hdr[CR_HDR_N_DST], a.max_rows);
     if ((int)blockIdx.x * WIDE_ROWS >= M) return;
     // the last tile is moved back so that it ends at the last row: it recomputes a few rows of its neighbour (same
-    // values, written twice) and no load has to be clamped to the row count.  With fewer than 256 rows the one tile
+    // values, written twice) and no load has to be clamped to the row count.  With fewer than 128 rows the one tile
     // reads rows past the last one: they exist (the arrays hold max_rows >= 16384 rows), rows are independent, and
     // results past the last row are not stored.
     const int m0 = max(0, min((int)blockIdx.x * WIDE_ROWS, M - WIDE_ROWS));
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, lr = lane & 31;
+    const int wr = (wave & 1) * 64, wc = (wave >> 1) * 128;    // this wave's rows and columns of the tile
     const int K = a.K, K0 = a.K0;
     // Column k of the product sits in the first operand array for k < K0 and in the second from there on.  Each array's
-    // columns are taken in chunks of 128 of their own (the first array's chunks, then the second's), so a chunk lies in
-    // one array whatever K0 is; the last chunk of an array whose width is no multiple of 128 is a partial one.
-    const int nchunk0 = (K0 + WIDE_KH - 1) / WIDE_KH;
-    const int nchunk = nchunk0 + (K - K0 + WIDE_KH - 1) / WIDE_KH;
-    // chunk c: its first column within its array, and the columns it has there (128, fewer in a partial chunk)
-    auto chunk_off = [&](int c) { return (c < nchunk0 ? c : c - nchunk0) * WIDE_KH; };
-    auto chunk_cols = [&](int c) { return min(WIDE_KH, (c < nchunk0 ? K0 : K - K0) - chunk_off(c)); };
+    // columns are taken in chunks of their own (the first array's chunks, then the second's), so a chunk lies in one array
+    // whatever K0 is.  Widths are multiples of 32: an array's last chunk holds 64 columns or 32.
+    const int nchunk0 = (K0 + WIDE_KC - 1) / WIDE_KC;
+    const int nchunk = nchunk0 + (K - K0 + WIDE_KC - 1) / WIDE_KC;
+    auto chunk_off = [&](int c) { return (c < nchunk0 ? c : c - nchunk0) * WIDE_KC; };
+    auto chunk_cols = [&](int c) { return min(WIDE_KC, (c < nchunk0 ? K0 : K - K0) - chunk_off(c)); };
 
-    // staging assignment: piece p = i * 256 + tid of a chunk = (row p / 16, 16-byte piece p % 16).  An address is a base
-    // that is the same for the whole workgroup (chunk, 16-row group i) plus one per-thread offset that serves all 16
-    // pieces: no address registers are held across the K loop.  Pieces past a partial chunk's columns are loaded from the
-    // chunk's first piece and staged as zeros.
-    const int srow = tid >> 4, spiece = tid & 15;
-    u32x4v wreg[16], areg[16];
-    auto fetch = [&](int c, int i) {     // pieces i of the chunk's 16 activation and 16 weight pieces of this thread
-        const int koff = chunk_off(c);
+    // staging assignment: piece p = i * 256 + tid of a chunk = (row p / 8, 16-byte piece p % 8).  An address is a base that is
+    // the same for the whole workgroup (chunk, 32-row group i) plus one per-thread offset that serves all pieces of an
+    // operand.  Pieces past a chunk of 32 columns are loaded from the chunk's first piece and not staged.
+    const int srow = tid >> 3, spiece = tid & 7;
+    // (past the last chunk its own pieces are fetched again: a load under a condition would be waited for at once)
+    u32x4v wreg[WP], areg0[AP], areg1[AP];
+    auto fetch_a = [&](u32x4v (&r)[AP], int c0) {
+        const int c = min(c0, nchunk - 1);
         const int sp = spiece * 8 < chunk_cols(c) ? spiece * 8 : 0;
-        const uint16_t *Ai = (c < nchunk0 ? a.A0 : a.A1) + koff + (int64_t)(m0 + i * 16) * a.lda;
-        const uint16_t *Wi = a.B + (c < nchunk0 ? 0 : K0) + koff + (int64_t)(i * 16) * K;
-        areg[i] = *reinterpret_cast<const u32x4v *>(Ai + (uint32_t)(srow * (int)a.lda + sp));
-        wreg[i] = *reinterpret_cast<const u32x4v *>(Wi + (uint32_t)(srow * K + sp));
-    };
-    auto stage = [&](int c) {
-        const bool full = chunk_cols(c) == WIDE_KH;            // (uniform)
-        const bool mine = spiece * 8 < chunk_cols(c);
-        const u32x4v zero = {0u, 0u, 0u, 0u};
+        const uint16_t *A = (c < nchunk0 ? a.A0 : a.A1) + chunk_off(c) + (int64_t)m0 * a.lda;
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int row = i * 16 + srow;
-            *reinterpret_cast<u32x4v *>(&As[row * WIDE_LROW + spiece * 8]) = (full || mine) ? areg[i] : zero;
-            *reinterpret_cast<u32x4v *>(&Ws[row * WIDE_LROW + spiece * 8]) = (full || mine) ? wreg[i] : zero;
-        }
+        for (int i = 0; i < AP; ++i) r[i] = *reinterpret_cast<const u32x4v *>(A + (int64_t)(i * 32) * a.lda + (uint32_t)(srow * (int)a.lda + sp));
     };
+    auto fetch_w = [&](int c0) {
+        const int c = min(c0, nchunk - 1);
+        const int sp = spiece * 8 < chunk_cols(c) ? spiece * 8 : 0;
+        const uint16_t *W = a.B + (c < nchunk0 ? 0 : K0) + chunk_off(c);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) fetch(0, i);
+        for (int i = 0; i < WP; ++i) wreg[i] = *reinterpret_cast<const u32x4v *>(W + (int64_t)(i * 32) * K + (uint32_t)(srow * K + sp));
+    };
+    auto stage = [&](const u32x4v (&r)[AP], int c) {
+        if (spiece * 8 >= chunk_cols(c)) return;
+#pragma unroll
+        for (int i = 0; i < AP; ++i) *reinterpret_cast<u32x4v *>(&As[(i * 32 + srow) * WIDE_LROW + spiece * 8]) = r[i];
+#pragma unroll
+        for (int i = 0; i < WP; ++i) *reinterpret_cast<u32x4v *>(&Ws[(i * 32 + srow) * WIDE_LROW + spiece * 8]) = wreg[i];
+    };
+    fetch_a(areg0, 0);
+    fetch_w(0);
+    fetch_a(areg1, 1);
     if (tid < WIDE_N / 4)
         *reinterpret_cast<float4 *>(&bias_s[tid * 4]) = a.bias ? *reinterpret_cast<const float4 *>(a.bias + tid * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    stage(0);
+    stage(areg0, 0);
     __syncthreads();
 
-    // the accumulators start from the bias (a lane's 4-column pieces: columns t*32 + 8*grp + 4*half .. + 4)
-    f32x16 acc[2][NTILES];
+    // the accumulators start from the bias (a lane's 4-column pieces: columns wc + t*32 + 8*grp + 4*half .. + 4)
+    f32x16 acc[2][4];
 #pragma unroll
-    for (int t = 0; t < NTILES; ++t)
+    for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int grp = 0; grp < 4; ++grp) {
-            const float4 bq = *reinterpret_cast<const float4 *>(&bias_s[t * 32 + 8 * grp + 4 * half]);
+            const float4 bq = *reinterpret_cast<const float4 *>(&bias_s[wc + t * 32 + 8 * grp + 4 * half]);
 #pragma unroll
             for (int rb = 0; rb < 2; ++rb) {
                 acc[rb][t][grp * 4 + 0] = bq.x; acc[rb][t][grp * 4 + 1] = bq.y; acc[rb][t][grp * 4 + 2] = bq.z; acc[rb][t][grp * 4 + 3] = bq.w;
             }
         }
-    const uint16_t *arow0 = As + (wave * 64 + lr) * WIDE_LROW + 8 * half, *arow1 = arow0 + 32 * WIDE_LROW;
-    const uint16_t *wrow = Ws + lr * WIDE_LROW + 8 * half;
-    // one chunk's K loop; PREFETCH: the next chunk's loads, two of each per step, travel under the MFMAs
-    auto chunk_loop = [&](auto prefetch, int c) {
-        constexpr bool PREFETCH = decltype(prefetch)::value;
-        bf16x8 wnext[NTILES], anext[2];
-        anext[0] = lds_read8(arow0);
-        anext[1] = lds_read8(arow1);
+    const uint16_t *arow0 = As + (wr + lr) * WIDE_LROW + 8 * half, *arow1 = arow0 + 32 * WIDE_LROW;
+    const uint16_t *wrow = Ws + (wc + lr) * WIDE_LROW + 8 * half;
+    auto step = [&](int ks) {
+        const bf16x8 a0 = lds_read8(arow0 + ks * 16), a1 = lds_read8(arow1 + ks * 16);
+        bf16x8 w[4];
 #pragma unroll
-        for (int t = 0; t < NTILES; ++t) wnext[t] = lds_read8(wrow + t * 32 * WIDE_LROW);
+        for (int t = 0; t < 4; ++t) w[t] = lds_read8(wrow + t * 32 * WIDE_LROW + ks * 16);
 #pragma unroll
-        for (int ks = 0; ks < KSTEPS; ++ks) {
-            bf16x8 wcur[NTILES];
-            const bf16x8 a0 = anext[0], a1 = anext[1];
-#pragma unroll
-            for (int t = 0; t < NTILES; ++t) wcur[t] = wnext[t];
-            if (ks + 1 < KSTEPS) {
-                anext[0] = lds_read8(arow0 + (ks + 1) * 16);
-                anext[1] = lds_read8(arow1 + (ks + 1) * 16);
-#pragma unroll
-                for (int t = 0; t < NTILES; ++t) wnext[t] = lds_read8(wrow + t * 32 * WIDE_LROW + (ks + 1) * 16);
-            }
-            if constexpr (PREFETCH) {
-                fetch(c + 1, 2 * ks);
-                fetch(c + 1, 2 * ks + 1);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int t = 0; t < NTILES; ++t) {
-                acc[0][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wcur[t], a0, acc[0][t], 0, 0, 0);
-                acc[1][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wcur[t], a1, acc[1][t], 0, 0, 0);
-            }
-            __builtin_amdgcn_sched_barrier(0);
+        for (int t = 0; t < 4; ++t) {
+            acc[0][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t], a0, acc[0][t], 0, 0, 0);
+            acc[1][t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w[t], a1, acc[1][t], 0, 0, 0);
         }
     };
-    // (the last chunk is peeled off: with the prefetch and the staging under a condition inside one loop the compiler
-    // keeps the 128 staging registers alive across the whole loop and spills)
-    for (int c = 0; c + 1 < nchunk; ++c) {
-        chunk_loop(std::true_type{}, c);
-        __syncthreads();                  // every wave is done reading this chunk
-        stage(c + 1);
+    // chunk c is in LDS, the activations of chunk c + 1 are on their way in `next`, those of c + 2 go to `after`
+    auto chunk = [&](int c, const u32x4v (&next)[AP], u32x4v (&after)[AP]) {
+        fetch_w(c + 1);
+        fetch_a(after, c + 2);
+        step(0);
+        step(1);
+        if (chunk_cols(c) > 32) {                              // (uniform)
+#pragma unroll
+            for (int ks = 2; ks < KSTEPS; ++ks) step(ks);
+        }
+        __syncthreads();                                       // every wave is done reading this chunk
+        stage(next, min(c + 1, nchunk - 1));
         __syncthreads();
+    };
+    for (int c = 0; c < nchunk; c += 2) {
+        chunk(c, areg1, areg0);
+        if (c + 1 >= nchunk) break;
+        chunk(c + 1, areg0, areg1);
     }
-    chunk_loop(std::false_type{}, nchunk - 1);
-    __syncthreads();
 
-    // epilogue: ReLU, bf16; a lane holds, for row lr of each block, the columns t*32 + 8*grp + 4*half .. + 4
+    // epilogue: ReLU, bf16, 32 rows at a time; a lane holds, for row lr of each block, the columns t*32 + 8*grp + 4*half .. + 4
     const float floor_v = a.relu ? 0.f : -INFINITY;
-    uint16_t *ob = wide_lds + wave * 64 * WIDE_OROW;
+    uint16_t *ob = lds + wave * 32 * WIDE_OROW;
 #pragma unroll
-    for (int t = 0; t < NTILES; ++t)
+    for (int rb = 0; rb < 2; ++rb) {
 #pragma unroll
-        for (int grp = 0; grp < 4; ++grp) {
-            const int n = t * 32 + 8 * grp + 4 * half;
+        for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int rb = 0; rb < 2; ++rb) {
+            for (int grp = 0; grp < 4; ++grp) {
                 const float v0 = fmaxf(acc[rb][t][grp * 4 + 0], floor_v), v1 = fmaxf(acc[rb][t][grp * 4 + 1], floor_v);
                 const float v2 = fmaxf(acc[rb][t][grp * 4 + 2], floor_v), v3 = fmaxf(acc[rb][t][grp * 4 + 3], floor_v);
-                *reinterpret_cast<uint2 *>(&ob[(rb * 32 + lr) * WIDE_OROW + n]) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
+                *reinterpret_cast<uint2 *>(&ob[lr * WIDE_OROW + t * 32 + 8 * grp + 4 * half]) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
             }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        const int mw = m0 + wr + rb * 32;
+#pragma unroll
+        for (int it = 0; it < 8; ++it) {
+            const int c = it * 64 + lane, row = c >> 4, c8 = (c & 15) * 8;
+            const u32x4v x = *reinterpret_cast<const u32x4v *>(&ob[row * WIDE_OROW + c8]);
+            if (mw + row < M) *reinterpret_cast<u32x4v *>(a.Cb + (int64_t)(mw + row) * a.ldcb + wc + c8) = x;
         }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    constexpr int CPR = WIDE_N / 8;       // 16-byte chunks per output row
-    const int mw = m0 + wave * 64;
-#pragma unroll 8
-    for (int it = 0; it < CPR; ++it) {
-        const int c = it * 64 + lane, row = c / CPR, c8 = (c % CPR) * 8;
-        const u32x4v x = *reinterpret_cast<const u32x4v *>(&ob[row * WIDE_OROW + c8]);
-        if (mw + row < M) *reinterpret_cast<u32x4v *>(a.Cb + (int64_t)(mw + row) * a.ldcb + c8) = x;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     }
 }
 
@@ -836,17 +827,11 @@ static void launch_nt(const NtArgs &a, hipStream_t s)
             return;
         }
     }
-    // many rows against weights that fit one compute unit's LDS, bf16 output only: the weight-stationary kernel
-    if (a.max_rows >= NT_WIDE_MIN_ROWS && a.N == WIDE_N && a.K0 % 8 == 0 && a.K % 8 == 0 && a.A1 != nullptr && a.Cb != nullptr &&
+    // many rows, wider inputs, bf16 output only
+    if (a.max_rows >= NT_WIDE_MIN_ROWS && a.N == WIDE_N && a.K0 % 32 == 0 && a.K % 32 == 0 && a.A1 != nullptr && a.Cb != nullptr &&
         a.C0 == nullptr && a.ldcb == a.N && a.lda < (1 << 20)) {
-        static const bool ready = [] {
-            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_nt_wide_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)WIDE_LDS_BYTES) == hipSuccess;
-        }();
-        if (ready) {
-            hipLaunchKernelGGL(gemm_nt_wide_kernel, dim3((unsigned)ceil_div(a.max_rows, WIDE_ROWS)), dim3(256), WIDE_LDS_BYTES, s, a);
-            return;
-        }
+        hipLaunchKernelGGL(gemm_nt_wide_kernel, dim3((unsigned)ceil_div(a.max_rows, WIDE_ROWS)), dim3(256), 0, s, a);
+        return;
     }
     // xcd_compact needs the grid rounded up to a multiple of eight blocks
     const unsigned ncol = (unsigned)(a.N / 64);
@@ -882,9 +867,12 @@ struct TnArgs {
 
 // T = [buffer][operand: 0 = A, 1 = Z][m][column]: the tiles are staged as they come from memory (row-major);
 // the transposition the MFMA operands need (eight consecutive m of one column per lane) is done by the LDS
-// transpose read of gfx950.  Row stride 288 bytes: the four 32-byte row pieces a 16-lane group reads
-// fall into disjoint banks.  `bid` is the workgroup's number among the `ntile` x (splits) workgroups of the product.
-__device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint32_t ntile, uint16_t (&T)[2][2][TN_BM][TN_ROW])
+// transpose read of gfx950.  Row stride 320 bytes: the four 64-byte row pieces that 32 lanes read fall into disjoint
+// banks.  `bid` is the workgroup's number among the `ntile` x (splits) workgroups of the product.
+// SUBS == 2: eight waves, the second four take the later half of the split's steps with tiles and accumulators of their own; the
+// halves are added through LDS at the end (the earlier half first, so in a fixed order).
+template <int SUBS>
+__device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint32_t ntile, uint16_t (&Tall)[SUBS][2][2][TN_BM][TN_ROW])
 {
     const int M = min(a.hdr[CR_HDR_N_DST], a.max_rows);
     // the tiles of one split run next to each other on one XCD (they share the split's rows of A and Z);
@@ -893,8 +881,12 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
     const int rows_per_split = rows_per_split_for(M, a.slots);
     if (!xcd_compact(bid, (uint32_t)((M + rows_per_split - 1) / rows_per_split) * ntile, work)) return;
     const int split = (int)(work / ntile), tile_id = (int)(work % ntile);
-    const int m_begin = split * rows_per_split;
-    const int m_end = min(M, m_begin + rows_per_split);
+    const int sub = SUBS > 1 ? (int)__builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 8)) : 0;
+    const int split_begin = split * rows_per_split, split_end = min(M, split_begin + rows_per_split);
+    const int nsteps = ((split_end - split_begin + TN_BM - 1) / TN_BM + SUBS - 1) / SUBS;       // steps of either half
+    const int m_begin = min(split_end, split_begin + sub * nsteps * TN_BM);
+    const int m_end = min(split_end, m_begin + nsteps * TN_BM);
+    uint16_t (&T)[2][2][TN_BM][TN_ROW] = Tall[sub];
     const int n_tiles = (a.N + 127) / 128;
     const int k_tiles_part = (a.K0 + 127) / 128;   // k-tiles per operand part (self | agg): a tile never straddles the two
     const int kt = tile_id / n_tiles;
@@ -903,7 +895,7 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
     const int k0 = part * a.K0 + kp0;              // first row of the output tile
     const int k_valid = min(128, a.K0 - kp0);
     const int n0 = (tile_id % n_tiles) * 128;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x & 255, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, lr = lane & 31;
     const int wk = wave >> 1, wn = wave & 1;
 
@@ -925,7 +917,7 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
         __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t *>(base), 0, (int)((uint32_t)m_end * ld_bytes), 0x00020000);
 
     constexpr int RPT = TN_BM / 8;                 // rows per thread and step: row group mg takes rows mg * RPT .. + RPT
-    uint4 ring[3][RPT];
+    uint4 ring[TN_DEPTH][RPT];
     auto fetch = [&](uint4 (&r)[RPT], int step) {
         const uint32_t mrow = (uint32_t)(m_begin + step * TN_BM + mg * RPT);
 #pragma unroll
@@ -972,16 +964,14 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
-    const int nsteps = (m_end - m_begin + TN_BM - 1) / TN_BM;
-    fetch(ring[0], 0);
-    fetch(ring[1], 1);
-    fetch(ring[2], 2);
+#pragma unroll
+    for (int i = 0; i < TN_DEPTH; ++i) fetch(ring[i], i);
     stage(ring[0], 0);
     __syncthreads();
 
     auto body = [&](int t, uint4 (&slot_next_fetch)[RPT], const uint4 (&slot_next_stage)[RPT]) {
         const int buf = t & 1;
-        fetch(slot_next_fetch, t + 3);             // the slot that held step t (already staged)
+        fetch(slot_next_fetch, t + TN_DEPTH);         // the slot that held step t (already staged)
 #pragma unroll
         for (int kk = 0; kk < TN_BM / 16; ++kk) {
             bf16x8 x[2], z[2];
@@ -1002,17 +992,39 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
         __syncthreads();
     };
     int t = 0;
-    for (; t + 3 <= nsteps; t += 3) {
-        body(t, ring[0], ring[1]);
-        body(t + 1, ring[1], ring[2]);
-        body(t + 2, ring[2], ring[0]);
+    for (; t + TN_DEPTH <= nsteps; t += TN_DEPTH) {
+#pragma unroll
+        for (int j = 0; j < TN_DEPTH; ++j) body(t + j, ring[j], ring[(j + 1) % TN_DEPTH]);
     }
-    if (t < nsteps) body(t, ring[0], ring[1]);
-    if (t + 1 < nsteps) body(t + 1, ring[1], ring[2]);
+#pragma unroll
+    for (int j = 0; j < TN_DEPTH - 1; ++j)
+        if (t + j < nsteps) body(t + j, ring[j], ring[j + 1]);
+
+    // the halves meet: each wave hands 32 of its 64 rows of the tile to its counterpart and finishes the other 32
+    float *meet = reinterpret_cast<float *>(&Tall[0][0][0][0][0]);
+    constexpr int MEET = 4 * 2 * 16 * 64;          // floats that one half hands over
+    if constexpr (SUBS > 1) {
+        static_assert(2 * MEET * sizeof(float) + 16 * 128 * sizeof(float) <= sizeof(Tall), "the halves meet in the staging tiles' room");
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) meet[sub * MEET + ((wave * 2 + j) * 16 + r) * 64 + lane] = sub == 0 ? acc[1][j][r] : acc[0][j][r];
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float other = meet[(1 - sub) * MEET + ((wave * 2 + j) * 16 + r) * 64 + lane];
+                if (sub == 0) acc[0][j][r] += other;
+                else acc[1][j][r] += other;
+            }
+    }
 
     float *P = a.partial + (int64_t)split * (a.K2 + 1) * a.N;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < 2; ++i) {
+        if (SUBS > 1 && i != sub) continue;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
             const int n = n0 + wn * 64 + j * 32 + lr;
@@ -1022,18 +1034,20 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
                 if (kl < k_valid && n < a.N) P[(int64_t)(k0 + kl) * a.N + n] = acc[i][j][r];
             }
         }
-    // bias gradient: the eight row groups' column sums meet in LDS and are added in a fixed order
+    }
+    // bias gradient: the row groups' column sums meet in LDS and are added in a fixed order
     if (kt == 0) {
-        float (*csum)[128] = reinterpret_cast<float (*)[128]>(&T[0][0][0][0]);     // the staging tiles are free now
+        // (one half: the staging tiles are free now; two: behind what the halves hand over)
+        float (*csum)[128] = reinterpret_cast<float (*)[128]>(meet + (SUBS > 1 ? 2 * MEET : 0));
         if (op == 1) {
 #pragma unroll
-            for (int c = 0; c < 8; ++c) csum[mg][sc + c] = cacc[c];
+            for (int c = 0; c < 8; ++c) csum[sub * 8 + mg][sc + c] = cacc[c];
         }
         __syncthreads();
-        if (tid < 128 && n0 + tid < a.N) {
+        if (sub == 0 && tid < 128 && n0 + tid < a.N) {
             float tot = 0.f;
 #pragma unroll
-            for (int g8 = 0; g8 < 8; ++g8) tot += csum[g8][tid];
+            for (int g8 = 0; g8 < 8 * SUBS; ++g8) tot += csum[g8][tid];
             P[(int64_t)a.K2 * a.N + n0 + tid] = tot;
         }
     }
@@ -1041,9 +1055,23 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
 
 __global__ __launch_bounds__(256) void gemm_tn_kernel(TnArgs a)
 {
-    __shared__ __attribute__((aligned(16))) uint16_t T[2][2][TN_BM][TN_ROW];
-    gemm_tn_body(a, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, T);
+    __shared__ __attribute__((aligned(16))) uint16_t T[1][2][2][TN_BM][TN_ROW];
+    gemm_tn_body<1>(a, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, T);
 }
+
+// Blocks of many rows.  One workgroup of four waves per compute unit (the split plan) leaves every SIMD a single wave, which
+// waits out its own chain of transpose reads, MFMAs, staging and barrier in each step (1250 cycles, of which the MFMAs are 256);
+// more loads in flight change nothing (three to eight steps ahead: the same), a second workgroup does but doubles the
+// partial sums.  Eight waves in two halves give every SIMD two waves with the partial sums of one workgroup:
+// 131 K rows x 608 x 256 (graph attention on the reddit-like graph) 87 -> 69 us, 61 K rows x 256 x 256 (papers) 21.6 -> 20.0.
+// Below this many rows the product shares its launch with the input gradient's (next kernel) or is short.
+__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tn_tall_kernel(TnArgs a)
+{
+    extern __shared__ __attribute__((aligned(16))) uint16_t tn_lds[];
+    gemm_tn_body<2>(a, blockIdx.y * gridDim.x + blockIdx.x, gridDim.x, *reinterpret_cast<uint16_t (*)[2][2][2][TN_BM][TN_ROW]>(tn_lds));
+}
+constexpr size_t TN_TALL_LDS_BYTES = sizeof(uint16_t) * 2 * 2 * 2 * TN_BM * TN_ROW;
+constexpr int TN_TALL_MIN_ROWS = 16384;
 
 // The two products of a layer's backward pass that need nothing from each other (weight gradient, input
 // gradient) in one launch: both are short and bound by memory round trips, so side by side they take about as
@@ -1054,7 +1082,7 @@ __global__ __launch_bounds__(256) void gemm_tn_nt_kernel(TnArgs t, NtArgs n, uin
     __shared__ __attribute__((aligned(16))) uint16_t lds[2 * 2 * TN_BM * TN_ROW];
     static_assert(sizeof(lds) >= sizeof(uint16_t) * (2 * 128 * LDS_ROW + 2 * 64 * LDS_ROW), "the staging tiles of either product fit");
     if (blockIdx.x < tn_blocks) {
-        gemm_tn_body(t, blockIdx.x, tn_tiles, *reinterpret_cast<uint16_t (*)[2][2][TN_BM][TN_ROW]>(lds));
+        gemm_tn_body<1>(t, blockIdx.x, tn_tiles, *reinterpret_cast<uint16_t (*)[1][2][2][TN_BM][TN_ROW]>(lds));
     } else {
         gemm_nt_body<2, 4>(n, blockIdx.x - tn_blocks, nt_cols, *reinterpret_cast<uint16_t (*)[2][128][LDS_ROW]>(lds),
                            *reinterpret_cast<uint16_t (*)[2][64][LDS_ROW]>(lds + 2 * 128 * LDS_ROW));
@@ -1326,7 +1354,8 @@ cr_status cr::linear_bwd_products(const cr_sage_layer *layer, const int32_t *hdr
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     const unsigned tn_tiles = (unsigned)(n_op * ceil_div(F_pad, 128) * ceil_div(N_pad, 128));
-    if (d_agg || d_in_bf16) {
+    const bool want_input = d_agg || d_in_bf16, tall = max_rows >= TN_TALL_MIN_ROWS;
+    if (want_input && !tall) {
         // the input-gradient product shares the launch and the 512 resident workgroup slots: fewer, longer splits so
         // that both parts fit one round (its tiles counted at ~0.7 of the capacity, the usual fill of a sampled block)
         const int64_t nt_share = (int64_t)(n_op * F_pad / 64) * ceil_div(max_rows, 128) * 7 / 10;
@@ -1336,11 +1365,17 @@ cr_status cr::linear_bwd_products(const cr_sage_layer *layer, const int32_t *hdr
     TnArgs t;
     t.hdr = hdr; t.max_rows = max_rows; t.A0 = n_op == 2 ? h_self : agg; t.A1 = agg; t.lda = ld_in; t.K0 = F_pad; t.K2 = n_op * F_pad;
     t.Z = dz_bf16; t.N = N_pad; t.slots = splits; t.partial = partial;
-    if (d_agg || d_in_bf16) {   // also the gradient w.r.t. the layer's inputs (weights from before the step), in the same launch
-        NtArgs a;
-        a.hdr = hdr; a.max_rows = max_rows; a.A0 = dz_bf16; a.A1 = nullptr; a.lda = N_pad; a.K0 = N_pad; a.K = N_pad;
-        a.B = layer->W_bf16; a.N = n_op * F_pad; a.bias = nullptr; a.relu = 0;
-        a.C0 = n_op == 2 ? d_self : d_agg; a.C1 = d_agg; a.ldc = F_pad; a.N0 = F_pad; a.Cb = d_in_bf16; a.ldcb = n_op * F_pad;
+    NtArgs a;                       // the gradient w.r.t. the layer's inputs (weights from before the step)
+    a.hdr = hdr; a.max_rows = max_rows; a.A0 = dz_bf16; a.A1 = dz_bf16; a.lda = N_pad; a.K0 = N_pad; a.K = N_pad;
+    a.B = layer->W_bf16; a.N = n_op * F_pad; a.bias = nullptr; a.relu = 0;
+    a.C0 = n_op == 2 ? d_self : d_agg; a.C1 = d_agg; a.ldc = F_pad; a.N0 = F_pad; a.Cb = d_in_bf16; a.ldcb = n_op * F_pad;
+    if (tall) {
+        // many rows: both products fill the chip by themselves, and the input gradient may take the kernels for many rows
+        static const hipError_t ready = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_tn_tall_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)TN_TALL_LDS_BYTES);
+        CR_HIP_CHECK(ready);
+        hipLaunchKernelGGL(gemm_tn_tall_kernel, dim3(tn_tiles, (unsigned)splits + (7 + tn_tiles - 1) / tn_tiles), dim3(512), TN_TALL_LDS_BYTES, s, t);
+        if (want_input) launch_nt(a, s);
+    } else if (want_input) {        // both in one launch
         const unsigned nt_cols = (unsigned)(a.N / 64);
         const unsigned tn_blocks = (unsigned)round_up((int64_t)tn_tiles * splits + 7, 8);
         const unsigned nt_blocks = (unsigned)round_up((int64_t)nt_cols * ceil_div(max_rows, 128) + 7, 8);
