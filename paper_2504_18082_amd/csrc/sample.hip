@@ -787,7 +787,9 @@ __device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int ro
     if (!EXACT && ranked) {
         // (float arithmetic: the threshold only steers how many candidates there are)
         const float mf = (float)m;
-        const float target = mf + 3.0f * __builtin_amdgcn_sqrtf(mf) + 3.0f;
+        // (m of P words lie below the m-th: three standard deviations of that count and a little more.  Fewer candidates cost more
+        // in rows that are redone than they save: 2 and 2.5 deviations measure 1.3 and 3 % slower on a products-like group)
+        const float target = mf + 3.0f * __builtin_amdgcn_sqrtf(mf * fmaxf(0.0f, 1.0f - mf * __builtin_amdgcn_rcpf((float)P))) + 3.0f;
         uint32_t T = 0xFFFFFFFFu;
         bool all = true;
         if (MODE == 2) {
@@ -1253,6 +1255,8 @@ struct ScanArgs {
     const int32_t *dst_ids;
     int64_t dst_stride;
     int32_t fanout;
+    int32_t *head_ids;            // mode 4, input-side block in global ids: takes the destination nodes too, or NULL
+    int64_t head_stride;
 };
 
 // out[0..n] = exclusive prefix sums of in[0..n) per batch (blockIdx.y).  A workgroup owns one tile of 256 x 16
@@ -1319,6 +1323,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(ScanArgs a)
             const int32_t node = a.dst_ids[(int64_t)g * a.dst_stride + j];
             const int64_t d = a.g_indptr[node + 1] - a.g_indptr[node];
             v = (int)(d < a.fanout ? d : a.fanout);
+            if (a.head_ids) a.head_ids[(int64_t)g * a.head_stride + j] = node;
         }
         tile[j + j / SCAN_ITEMS] = v;
     }
@@ -1356,6 +1361,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(ScanArgs a)
             // a block sampled below a frontier that was cut short is as invalid as that frontier
             hdr[CR_HDR_STATUS] = a.prev_hdr ? a.prev_hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_STATUS] : 0;
             hdr[4] = hdr[5] = hdr[6] = hdr[7] = 0;
+            if (a.head_ids) hdr[CR_HDR_N_SRC] = -1;
         } else if (a.mode == 1) {
             const int need = n_dst + total;
             if (need > a.cap_src) {        // only possible with capacities below the bound: cut the frontier, mark the block
@@ -1440,6 +1446,7 @@ struct OrderArgs {
     int32_t cap_dst;
     uint16_t *bucket;         // [n_batches][bucket_stride]: a row's bucket, kept from the counting pass for the scatter pass
     int64_t bucket_stride;
+    int32_t cap_rows;         // most rows a batch has
 };
 
 __device__ __forceinline__ int order_bucket(const OrderArgs &a, int node)
@@ -1503,6 +1510,53 @@ __global__ __launch_bounds__(256) void order_pass_kernel(OrderArgs a)
         __syncthreads();
         for (int b = threadIdx.x; b < a.n_buckets; b += 256) a.cells[cell0 + (int64_t)b * cols + col] = lds[b];
     }
+}
+
+// The same for few rows (a group of at most ORDER_SMALL of them, or batches of at most as many): one workgroup counts, adds up
+// and hands out positions, one launch instead of three (a group of one 64-root batch: 12 -> 4 us).
+constexpr int ORDER_SMALL = 8192;
+__global__ __launch_bounds__(1024) void order_small_kernel(OrderArgs a, int n_batches)
+{
+    __shared__ int count[ORDER_BUCKETS];
+    __shared__ int lds[17];
+    constexpr int PER = ORDER_SMALL / 1024, BPT = ORDER_BUCKETS / 1024;
+    const int g0 = a.grouped ? 0 : (int)blockIdx.x, ng = a.grouped ? n_batches : 1, tid = threadIdx.x;
+    for (int b = tid; b < ORDER_BUCKETS; b += 1024) count[b] = 0;
+    __syncthreads();
+    int bkt[PER];                            // row i of the workgroup: batch g0 + i / rows, row i % rows
+    const int rows = a.cap_rows;
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = k * 1024 + tid, g = g0 + i / rows, r = i % rows;
+        bkt[k] = -1;
+        if (i < ng * rows && r < group_n_dst(a.prev_hdr, g, a.n_roots_total, a.batch_size)) {
+            bkt[k] = order_bucket(a, a.dst_ids[(int64_t)g * a.dst_stride + r]);
+            atomicAdd(&count[bkt[k]], 1);
+        }
+    }
+    __syncthreads();
+    int x[BPT], sum = 0, total;
+#pragma unroll
+    for (int k = 0; k < BPT; ++k) {
+        x[k] = count[tid * BPT + k];
+        sum += x[k];
+    }
+    int run = block_exclusive_scan_1024(sum, lds, total);
+#pragma unroll
+    for (int k = 0; k < BPT; ++k) {
+        count[tid * BPT + k] = run;
+        run += x[k];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PER; ++k) {
+        const int i = k * 1024 + tid, g = g0 + i / rows, r = i % rows;
+        if (bkt[k] < 0) continue;
+        const int pos = atomicAdd(&count[bkt[k]], 1);
+        if (a.grouped) a.order[pos] = g * a.cap_dst + r;
+        else a.order[(int64_t)g * a.order_stride + pos] = r;
+    }
+    if (a.grouped && tid == 0) a.order[(int64_t)n_batches * a.cap_dst] = total;
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -2529,13 +2583,17 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         sc.out_copy = nullptr; sc.copy_stride = 0; sc.hdr = b.hdr;
         sc.cap_src = b.cap_src; sc.async_status = async_status();
         sc.g_indptr = graph->indptr; sc.dst_ids = dst_ids; sc.dst_stride = dst_stride; sc.fanout = f;
+        sc.head_ids = nullptr; sc.head_stride = 0;
         const dim3 scan_grid((unsigned)ceil_div(cap_dst, SCAN_TILE), n_batches);
         sa.out_indptr = nullptr; sa.out_indptr_stride = 0; sa.out_ids = nullptr; sa.out_stride = 0;
         if (direct_out || lds_hop) {
-            if (cap_dst <= SCAN_TILE) sc.mode = 4;
-            else
+            if (cap_dst <= SCAN_TILE) {
+                sc.mode = 4;
+                if (direct_out) { sc.head_ids = b.src_ids; sc.head_stride = b.cap_src; }
+            } else {
                 hipLaunchKernelGGL(row_counts_kernel, dim3((unsigned)ceil_div(cap_dst, 256), n_batches), blk, 0, s, graph->indptr, dst_ids, dst_stride,
                                    prev_hdr, n_roots_total, batch_size, f, p.cnt, (int64_t)p.max_dst);
+            }
             hipLaunchKernelGGL(scan_kernel, scan_grid, dim3(SCAN_THREADS), 0, s, sc);
             sa.out_indptr = b.indptr; sa.out_indptr_stride = b.cap_dst + 1;
             sa.out_ids = direct_out ? b.gather_ids : p.sel; sa.out_stride = direct_out ? b.cap_nnz : p.max_nnz;
@@ -2557,6 +2615,11 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
             oa.cells = p.order_hist; oa.offsets = p.order_cursor; oa.order = order; oa.order_stride = b.cap_dst;
             oa.grouped = grouped; oa.cap_dst = b.cap_dst;
             oa.bucket = p.order_bucket; oa.bucket_stride = p.max_dst;
+            oa.cap_rows = cap_dst;
+            if ((int64_t)cap_dst * (grouped ? n_batches : 1) <= ORDER_SMALL) {
+                hipLaunchKernelGGL(order_small_kernel, dim3(grouped ? 1 : n_batches), dim3(1024), 0, s, oa, n_batches);
+                continue;
+            }
             const int n_cells = oa.n_buckets * oa.n_tiles * (grouped ? n_batches : 1);
             const dim3 og((unsigned)oa.n_tiles, n_batches);
             hipLaunchKernelGGL(order_pass_kernel<false>, og, blk, 0, s, oa);
@@ -2564,7 +2627,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
             so.prev_hdr = prev_hdr; so.n_roots_total = n_roots_total; so.batch_size = batch_size;
             so.mode = 3; so.n_fixed = n_cells; so.in = p.order_hist; so.in_stride = n_cells + 1; so.out = p.order_cursor;
             so.out_stride = n_cells + 1; so.out_copy = nullptr; so.copy_stride = 0; so.hdr = b.hdr;
-            so.tile_before = nullptr; so.cap_src = 0; so.async_status = nullptr;
+            so.tile_before = nullptr; so.cap_src = 0; so.async_status = nullptr; so.head_ids = nullptr;
             const int scan_tiles = (int)ceil_div(n_cells, SCAN_TILE);
             if (grouped && scan_tiles > 8 && scan_tiles <= 16384) {
                 hipLaunchKernelGGL(scan_tile_sums_kernel, dim3((unsigned)scan_tiles), dim3(SCAN_THREADS), 0, s, p.order_hist, n_cells, p.order_tiles);
@@ -2592,6 +2655,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         if (global_ids) {
             da.tcount = nullptr; da.tfill = nullptr; da.t_stride = 0; da.t_indptr = nullptr; da.t_indptr_stride = 0;
             da.t_indices = nullptr; da.t_tmp = nullptr; da.t_pos = nullptr; da.tt_stride = 0;
+            if (sc.head_ids) continue;                        // done with the row pointers
             if (direct_out) hipLaunchKernelGGL(frontier_head_kernel, dim3((unsigned)ceil_div(cap_dst, 256), n_batches), blk, 0, s, da);
             else hipLaunchKernelGGL(compact_ids_kernel, grid, blk, 0, s, da);
             continue;

@@ -80,3 +80,29 @@ def test_one_part_gets_every_id(torch_mod):
     picks = np.sort(part0[(rng.integers(0, len(part0) - 20, size=(n, 1)) + np.arange(15))], axis=1)
     graph = (np.arange(n + 1, dtype=np.int64) * 15, picks.reshape(-1), (np.arange(n) // (n // 4 + 1)).astype(np.int32))
     check(torch_mod, graph, 8000, 8000, [2, 15], 0.5, "one part")
+
+
+# destination rows of a whole group in community order: one workgroup (at most 8192 rows by capacity), just not, many buckets
+@pytest.mark.parametrize("batch_size,n_batches,n_comm", [(64, 1, 5), (409, 4, 4096), (410, 4, 9000), (1024, 8, 70)])
+def test_group_order(torch_mod, batch_size, n_batches, n_comm):
+    from paper_2504_18082_amd import binding as B
+    torch = torch_mod
+    graph = mixed_graph(24_000)
+    comm = np.sort(np.random.default_rng(n_comm).integers(0, n_comm, size=24_000)).astype(np.int32)
+    dg = DeviceGraph(torch, (graph[0], graph[1], comm), n_comm, edge_classes=True)
+    print(f"case group order: {n_batches} batches of {batch_size}, {n_comm} communities", flush=True)
+    cfg = B.make_sample_cfg([3, 4], 0.5, 3, 1, 0, B.CR_SAMPLE_INPUT_GLOBAL_IDS | B.CR_SAMPLE_ROW_ORDER)
+    layers = B.alloc_block_sets(cfg, 24_000, batch_size, n_batches, group_order_input=True)
+    layers[0].group_order.fill_(-1)
+    ws = torch.empty(B.cr_sample_blocks_workspace_bytes(cfg, 24_000, batch_size, n_batches), dtype=torch.uint8, device="cuda")
+    roots = torch.from_numpy(np.random.default_rng(1).permutation(24_000).astype(np.int32)[:batch_size * n_batches - 3]).cuda()
+    B.cr_sample_blocks(dg.c, cfg, roots, roots.numel(), batch_size, n_batches, ws, layers)
+    torch.cuda.synchronize()
+    b = layers[0]
+    n_dst, src, order = b.hdr[:, 0].cpu().numpy(), b.src_ids.cpu().numpy(), b.group_order.cpu().numpy()
+    n = int(n_dst.sum())
+    assert order[n_batches * b.cap_dst] == n and np.all(b.hdr[:, 1].cpu().numpy() == -1)
+    want = np.concatenate([g * b.cap_dst + np.arange(n_dst[g]) for g in range(n_batches)])
+    assert np.array_equal(np.sort(order[:n]), want)
+    c = comm[src.reshape(n_batches, -1)[order[:n] // b.cap_dst, order[:n] % b.cap_dst]].astype(np.int64)
+    assert np.all(np.diff(c if n_comm <= 4096 else c * 4096 // n_comm) >= 0)
