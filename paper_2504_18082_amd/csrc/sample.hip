@@ -257,25 +257,10 @@ __device__ __forceinline__ void select_big_row(const SelectArgs &a, int g, int r
 // general path, which needs no threshold).
 constexpr int CAND_CAP = 128;
 
-// rk[i] += (k < w[i]) for four words at once.  Written out by hand so that the four comparisons land in four different
+// rk[i] += (w[i] < k) for four words at once.  Written out by hand so that the four comparisons land in four different
 // scalar register pairs and the four add-with-carry instructions follow them: the compiler routes every comparison
 // through VCC and has to wait two cycles between each comparison and its add (three instructions lie between a
 // comparison and the add that reads its result here, more than the two wait states the hardware asks for).
-__device__ __forceinline__ void rank4(uint32_t k, const uint32_t (&w)[4], int (&rk)[4])
-{
-    uint64_t s0, s1, s2, s3;
-    asm("v_cmp_lt_u32_e64 %4, %8, %9\n\t"
-        "v_cmp_lt_u32_e64 %5, %8, %10\n\t"
-        "v_cmp_lt_u32_e64 %6, %8, %11\n\t"
-        "v_cmp_lt_u32_e64 %7, %8, %12\n\t"
-        "v_addc_co_u32_e64 %0, %4, 0, %0, %4\n\t"
-        "v_addc_co_u32_e64 %1, %5, 0, %1, %5\n\t"
-        "v_addc_co_u32_e64 %2, %6, 0, %2, %6\n\t"
-        "v_addc_co_u32_e64 %3, %7, 0, %3, %7"
-        : "+v"(rk[0]), "+v"(rk[1]), "+v"(rk[2]), "+v"(rk[3]), "=&s"(s0), "=&s"(s1), "=&s"(s2), "=&s"(s3)
-        : "v"(k), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
-}
-// the same with the comparison turned round: rk[i] += (w[i] < k)
 __device__ __forceinline__ void rank4_below(uint32_t k, const uint32_t (&w)[4], int (&rk)[4])
 {
     uint64_t s0, s1, s2, s3;
@@ -653,17 +638,20 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 //   uniform        pool = the row, m = min(fanout, degree);
 //   p = 1          with n_in >= fanout intra-community slots the pool is those and m = fanout; with fewer, all of them are
 //                  kept and the pool is the inter-community slots with m = fanout - n_in (0 in strict mode).
-// Slots whose word lies below a threshold of about (m + 3 sqrt(m) + 3) / P become candidates, are compacted in slot order
-// into the row's stretch of an LDS list, and every lane ranks its four slots against that list (one broadcast read serves
-// four comparisons per lane).  The ranking compares words only; a row whose kept count then differs from the count it must
-// have (a threshold that let fewer than m slots through, or equal words at the boundary) is redone without threshold and
-// with (word, slot) pairs compared in full, so the result is exact in every case.
+// The kept slots are those below a bound T with exactly m words of the pool below it.  T is found by search: it is moved
+// inside a bracket to where evenly spread words would put it, and the words below it are counted per row with four ballots
+// and population counts under the row's mask of lanes (about 40 instructions a step, no LDS; 3 to 4 steps a row, 5 to 6 for
+// the slowest row of a pass).  The kernel is bound by vector instruction issue; ranking every slot against a list of its
+// row's candidates in LDS, which this replaces, took about 400 instructions a pass against 230.  Selection of a
+// products-like group of 32 batches (uniform, three hops): 792 -> 630 us; of a papers-like one 910 -> 804 us; weighted, a
+// reddit-like group of 8: 222 -> 193 us.  A row without such a bound in SEARCH_STEPS steps (equal words at the boundary) is
+// redone with (word, slot) pairs compared in full, so the result is exact in every case.
 //
 // Weighted sampling (0.5 < p < 1) takes the same passes with single-precision keys: approx_clock(r) * m_class, compared
 // through their bit patterns (all positive).  They decide only WHICH slots are kept (the output is in slot order), so the
-// result is exact whenever the largest kept key and the smallest key left out are further apart than the keys' error
-// bounds; that is checked per row, and a row that fails (or whose threshold let too few slots through) is redone with
-// the exact integer keys.  The bound |approx_clock(r) * 2^24 - E(r)| <= CLOCK_ERR_ABS + CLOCK_ERR_REL * E(r) (E in its
+// result is exact whenever no key lies within its error bound of T; that is checked per row, and a row that fails is redone
+// with the exact integer keys (thirteen microseconds for a wave that has one: such rows used to be a reddit-like group's
+// tail).  The bound |approx_clock(r) * 2^24 - E(r)| <= CLOCK_ERR_ABS + CLOCK_ERR_REL * E(r) (E in its
 // Q24 units) holds with a factor of two to spare for every one of the 2^32 words: cr_selftest_clock_approximation
 // measures it on the device.
 constexpr float CLOCK_ERR_ABS = 8.0f;             // Q24 units
@@ -696,56 +684,44 @@ constexpr int QUAD_ROWS = 32;            // destination rows per wave, ...
 constexpr int QUAD_MIN_ROWS = 2;         // ... and as few as this
 constexpr int QUAD_FILL_WAVES = 8192;    // until there are this many waves (eight per SIMD)
 constexpr int QUAD_MAX_DEG = 4 * WAVE;   // longest row a pass holds
+constexpr int SEARCH_STEPS = 24;         // bounds tried before a row is ranked in full
 
 struct alignas(16) QuadRow {
-    int32_t v, deg, startq, nq_row;      // node, degree, first quad in the wave's quad sequence, number of quads | which of
-                                         // the wave's destination rows it is << 8
+    int32_t v, deg;                      // node, degree
     int64_t base;                        // first adjacency entry
-    int32_t *out;                        // where the row's chosen ids go
+    int64_t out;                         // where the row's chosen ids go, counted from the group's array
+    int64_t pad;
 };
 
-// One pass; returns the rows that have to be redone exactly (bit r = the r-th row of the wave's quad sequence: the rows
-// are laid out in the order the packing placed them, not in the order of the block).  rowmask: rows to process.
+// One pass over the rows packed into it: lane `lane` (below `used`) holds quad lane - first of the wave's r-th row.  Returns
+// the rows that have to be redone exactly.
 template <int MODE, bool EXACT>
-__device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int row0, int p, uint32_t rowmask, const QuadRow *rows,
-                                              const int *startq, uint32_t *klist, uint32_t *clist, uint32_t *rowinfo,
-                                              unsigned long long *k64, uint32_t *rowstat, int lane)
+__device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int row0, int r, int first, int used, const QuadRow *rows,
+                                              int32_t *out, uint32_t *klist, unsigned long long *k64, int lane)
 {
     const int f = a.fanout;
     const uint32_t batch = a.first_batch + (uint32_t)g;
-    const int gq = p * WAVE + lane;
-    // the row of this lane's quad: the last one that starts at or before it (startq is non-decreasing, startq[0] = 0)
-    static_assert(QUAD_ROWS == 32, "the bisection below takes five steps");
-    int r = startq[16] <= gq ? 16 : 0;
-    r += startq[r + 8] <= gq ? 8 : 0;
-    r += startq[r + 4] <= gq ? 4 : 0;
-    r += startq[r + 2] <= gq ? 2 : 0;
-    r += startq[r + 1] <= gq ? 1 : 0;
     const QuadRow R = rows[r];
-    const int qi = gq - R.startq;
-    const int nq = R.nq_row & 0xFF;
-    const bool active = qi < nq && ((rowmask >> r) & 1u);
-    if (__ballot(active) == 0) return 0u;
-    const int first = R.startq - p * WAVE, last = first + nq - 1;         // the row's lanes in this pass
+    const bool active = lane < used;
+    const int qi = lane - first, nq = (R.deg + 3) >> 2;
     const int jb = 4 * qi;
     const int left = active ? R.deg - jb : 0;
     const uint32_t vmask = left >= 4 ? 0xFu : ((1u << left) - 1u);        // the quad's slots that exist
     const u32x4 w = philox4x32_10((uint32_t)qi, (uint32_t)R.v, batch, a.ctr3, a.seed_lo, a.seed_hi);
     const uint32_t wr[4] = {w.x, w.y, w.z, w.w};
 
-    // number of set flags of this row in the lanes before this one, and in the whole row (flags of lanes outside any
-    // row are zero)
-    // (in_pass: the same count over all the lanes before this one, whatever their row)
-    auto seg = [&](uint32_t m4, int &excl, int &total, int &in_pass) {
-        int e = 0;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) e = lanes_below(__ballot((m4 >> i) & 1u), e);
-        const int before_row = (int)pull32((uint32_t)e, first);
-        const int upto_last = (int)pull32((uint32_t)(e + __popc(m4)), last);
-        excl = e - before_row;
-        total = upto_last - before_row;
-        in_pass = e;
+    // the row's lanes of this pass; counts over a row are population counts of ballots under this mask: no LDS round trips
+    const uint64_t row_lanes = active ? (nq >= WAVE ? ~0ull : ((1ull << nq) - 1ull) << first) : 0ull;
+    auto count4 = [&](bool f0, bool f1, bool f2, bool f3) -> int {          // set flags in the whole row
+        const uint64_t b0 = __ballot(f0), b1 = __ballot(f1), b2 = __ballot(f2), b3 = __ballot(f3);
+        return __popcll(b0 & row_lanes) + __popcll(b1 & row_lanes) + __popcll(b2 & row_lanes) + __popcll(b3 & row_lanes);
     };
+    auto before4 = [&](bool f0, bool f1, bool f2, bool f3) -> int {         // ... and in the row's lanes before this one
+        const uint64_t b0 = __ballot(f0), b1 = __ballot(f1), b2 = __ballot(f2), b3 = __ballot(f3);
+        return lanes_below(b3 & row_lanes, lanes_below(b2 & row_lanes, lanes_below(b1 & row_lanes, lanes_below(b0 & row_lanes, 0))));
+    };
+    auto count_bits = [&](uint32_t m4) { return count4(m4 & 1u, m4 & 2u, m4 & 4u, m4 & 8u); };
+    auto before_bits = [&](uint32_t m4) { return before4(m4 & 1u, m4 & 2u, m4 & 4u, m4 & 8u); };
 
     uint32_t pool = vmask, take = 0u;
     int m = min(f, R.deg), P = R.deg, expect = m;
@@ -757,8 +733,7 @@ __device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int ro
             const uint64_t win = (uint64_t)a.edge_intra[wi] | ((uint64_t)a.edge_intra[min(wi + 1, w_max)] << 32);
             nib = (uint32_t)(win >> (e & 31)) & 0xFu;
         }
-        int unused, unused2;
-        seg(nib & vmask, unused, n_in, unused2);
+        n_in = count_bits(nib & vmask);
     }
     if (MODE == 1) {
         const uint32_t in4 = nib & vmask;
@@ -770,6 +745,11 @@ __device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int ro
             expect = n_in + m;
         }
     }
+    const bool ranked = active && m > 0 && m < P;
+    if (!ranked) {
+        if (m >= P) take |= pool;           // the whole pool is kept
+        pool = 0u;
+    }
     // the ordering words of the lane's four slots: the random words themselves, or (weighted) the bit patterns of the
     // single-precision keys
     uint32_t kw[4] = {wr[0], wr[1], wr[2], wr[3]};
@@ -777,182 +757,140 @@ __device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int ro
 #pragma unroll
         for (int i = 0; i < 4; ++i) kw[i] = __float_as_uint(approx_clock(wr[i]) * (float)(((nib >> i) & 1u) ? a.q_out : a.q_in));
     }
-    const bool ranked = active && m > 0 && m < P;
-    if (!ranked) {
-        if (m >= P) take |= pool;           // the whole pool is kept
-        pool = 0u;
-    }
-    uint32_t cm = pool;                      // candidates among this lane's slots
-    float kappa = INFINITY;                  // weighted: every slot that is no candidate has a key of at least this
-    if (!EXACT && ranked) {
-        // (float arithmetic: the threshold only steers how many candidates there are)
-        const float mf = (float)m;
-        // (m of P words lie below the m-th: three standard deviations of that count and a little more.  Fewer candidates cost more
-        // in rows that are redone than they save: 2 and 2.5 deviations measure 1.3 and 3 % slower on a products-like group)
-        const float target = mf + 3.0f * __builtin_amdgcn_sqrtf(mf * fmaxf(0.0f, 1.0f - mf * __builtin_amdgcn_rcpf((float)P))) + 3.0f;
-        uint32_t T = 0xFFFFFFFFu;
-        bool all = true;
+    uint32_t emit;
+    int epos;
+    bool ok = true;
+    if constexpr (!EXACT) {
+        // slots kept without a ranking lie below every bound, slots outside the pool above every one
+        const uint32_t none = ~(pool | take);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) kw[i] = (kw[i] & (uint32_t)((int32_t)(pool << (31 - i)) >> 31)) | (uint32_t)((int32_t)(none << (31 - i)) >> 31);
+        // A bound T with `expect` words of the row below it: T is moved inside a bracket (lo: cl words below, hi: ch) to where
+        // evenly spread words would put it.  x runs over [0, 1] (weighted: the bound's place in a single exponential law of the
+        // row's mean rate); float arithmetic only steers T, the counts are what decides.  A row that is done has lo = hi and
+        // keeps its T.
+        const float want = (float)expect + 0.5f;
+        float lo = 0.0f, cl = MODE == 1 ? (float)(expect - m) : 0.0f, hi = 1.0f, ch = cl + (float)P;
+        float to_key = 4294967296.0f;
         if (MODE == 2) {
-            // expected number of keys below kappa: n_in (1 - 2^(-kappa / q_out)) + n_out (1 - 2^(-kappa / q_in)); three
-            // Newton steps from the tangent at zero (never past the root)
-            if (target < (float)P) {
-                const float ln2 = 0.69314718f, fi = (float)n_in, fo = (float)(P - n_in);
-                const float s_in = __builtin_amdgcn_rcpf((float)a.q_out), s_out = __builtin_amdgcn_rcpf((float)a.q_in);
-                float kp = target / (ln2 * (fi * s_in + fo * s_out));
-#pragma unroll
-                for (int it = 0; it < 3; ++it) {
-                    const float ei = __builtin_amdgcn_exp2f(-kp * s_in), eo = __builtin_amdgcn_exp2f(-kp * s_out);
-                    const float gv = fi * (1.0f - ei) + fo * (1.0f - eo) - target;
-                    const float gd = ln2 * (fi * s_in * ei + fo * s_out * eo);
-                    if (gd > 0.0f) kp -= gv / gd;
-                }
-                if (kp > 0.0f && kp < 3.0e38f) { kappa = kp; T = __float_as_uint(kp); all = false; }
-            }
-        } else {
-            const float tf = target * 4294967296.0f * __builtin_amdgcn_rcpf((float)P);
-            if (tf < 4294967040.0f) { T = (uint32_t)tf; all = false; }
+            // the law's rate: the slots' mean rate for the first of them, that of the mean waiting time for the last (with the
+            // mean rate alone, rows of few slots more than the fanout take 8 to 20 steps at p = 0.97, with this 3 to 5)
+            const float fi = (float)n_in, fo = (float)(P - n_in), w_in = (float)a.q_out, w_out = (float)a.q_in;
+            const float fr = want * __builtin_amdgcn_rcpf((float)P + 1.0f), p_f = (float)P;
+            const float rate = (fi * __builtin_amdgcn_rcpf(w_in) + fo * __builtin_amdgcn_rcpf(w_out)) * __builtin_amdgcn_rcpf(p_f);
+            const float late = p_f * __builtin_amdgcn_rcpf(fi * w_in + fo * w_out);
+            to_key = __builtin_amdgcn_rcpf(rate + fr * (late - rate));
+            lo = 1.0f; hi = 0.0f;            // (weighted: x is what is left of the law, 1 at T = 0)
         }
-        if (!all) {
-            uint32_t below = 0u;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) below |= (kw[i] < T ? 1u : 0u) << i;
-            cm &= below;
+        uint32_t T = 0u;
+        uint64_t open = __ballot(ranked);
+        for (int step = 0; step < SEARCH_STEPS && open != 0; ++step) {
+            const float x = lo + (hi - lo) * ((want - cl) * __builtin_amdgcn_rcpf(ch - cl + 1.0f));
+            T = MODE == 2 ? __float_as_uint(fmaxf(0.0f, -__builtin_amdgcn_logf(x) * to_key)) : (uint32_t)(x * to_key);
+            const int c = count4(kw[0] < T, kw[1] < T, kw[2] < T, kw[3] < T);
+            const float cf = (float)c;
+            const bool low = c <= expect, high = c >= expect;
+            lo = low ? x : lo;
+            cl = low ? cf : cl;
+            hi = high ? x : hi;
+            ch = high ? cf : ch;
+            open &= ~__ballot(low && high);
         }
-    }
-    int cpos, n_c, cglob;
-    seg(cm, cpos, n_c, cglob);
-    int rk[4] = {0, 0, 0, 0};
-    uint32_t below_m = 0u;                   // candidates among this lane's slots with fewer than m candidates in front
-    const int nc_mine = ranked ? n_c : 0;
-    if constexpr (MODE == 2 && EXACT) {
-        // the exact integer keys, 64 bits each: every slot of the row is a candidate, (key, slot) pairs compared in full
-        unsigned long long ek[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) ek[i] = (uint64_t)exp_clock_q24<true>(wr[i]) * (uint64_t)(((nib >> i) & 1u) ? a.q_out : a.q_in);
-        unsigned long long *kl = k64 + 4 * first;
-        if (ranked) {
-            int k = cpos;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if ((cm >> i) & 1u) kl[k++] = ek[i];
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        for (int t = 0; __ballot(t < nc_mine) != 0; ++t) {
-            if (t < nc_mine) {
-                const unsigned long long kt = kl[t];
+        ok = ((open >> lane) & 1u) == 0;
+        T = ranked ? T : 1u;
+        if (MODE == 2) {
+            // No key may lie within its error bound of T: then every kept slot's exact key is below every other's.  The bound's
+            // absolute part goes with the slot's own class: with the larger class weight for all slots three times as many rows
+            // were redone, 14 us of 222 on a reddit-like group.  T is anywhere in the gap around it, so a row that fails tries
+            // again a few bounds higher and lower.  (Slots outside the pool hold a NaN: never near.)
+            auto apart = [&](float t) -> bool {
+                const float rel = t * (CLOCK_ERR_REL + 0x1p-20f);
+                const float near_in = rel + (CLOCK_ERR_ABS + 0.25f) * 0x1p-24f * (float)a.q_out;
+                const float near_out = rel + (CLOCK_ERR_ABS + 0.25f) * 0x1p-24f * (float)a.q_in;
+                bool near[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i)
-                    rk[i] += (kt < ek[i] || (kt == ek[i] && t < cpos + (int)__popc(cm & ((1u << i) - 1u)))) ? 1 : 0;
+                    near[i] = __builtin_fabsf(__uint_as_float(kw[i]) - t) <= (((nib >> i) & 1u) ? near_in : near_out);
+                return count4(near[0], near[1], near[2], near[3]) == 0;
+            };
+            const float tf = __uint_as_float(T);
+            bool safe = !ranked || apart(tf);
+            if (__ballot(ok && !safe) != 0) {
+                const float shift = 2.5f * (tf * (CLOCK_ERR_REL + 0x1p-20f) + (CLOCK_ERR_ABS + 0.25f) * 0x1p-24f * (float)max(a.q_in, a.q_out));
+#pragma unroll 1
+                for (int s = 0; s < 2; ++s) {
+                    const float t = fmaxf(0.0f, s ? tf - shift : tf + shift);
+                    const uint32_t moved = __float_as_uint(t);
+                    const bool as_many = count4(kw[0] < moved, kw[1] < moved, kw[2] < moved, kw[3] < moved) == expect;
+                    if (apart(t) && as_many && !safe) { safe = true; T = moved; }
+                }
+            }
+            ok = ok && safe;
+        }
+        const bool k0 = kw[0] < T, k1 = kw[1] < T, k2 = kw[2] < T, k3 = kw[3] < T;
+        emit = (k0 ? 1u : 0u) | (k1 ? 2u : 0u) | (k2 ? 4u : 0u) | (k3 ? 8u : 0u);
+        epos = before4(k0, k1, k2, k3);
+    } else {
+        const int cpos = before_bits(pool), nc_mine = ranked ? P : 0;
+        int rk[4] = {0, 0, 0, 0};
+        uint32_t below_m = 0u;               // slots of the pool with fewer than m of its slots in front
+        if constexpr (MODE == 2) {
+            // the exact integer keys, 64 bits each; (key, slot) pairs compared in full
+            unsigned long long ek[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) ek[i] = (uint64_t)exp_clock_q24<true>(wr[i]) * (uint64_t)(((nib >> i) & 1u) ? a.q_out : a.q_in);
+            unsigned long long *kl = k64 + 4 * first;
+            if (ranked) {
+                int k = cpos;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if ((pool >> i) & 1u) kl[k++] = ek[i];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int t = 0; __ballot(t < nc_mine) != 0; ++t) {
+                if (t < nc_mine) {
+                    const unsigned long long kt = kl[t];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        rk[i] += (kt < ek[i] || (kt == ek[i] && t < cpos + (int)__popc(pool & ((1u << i) - 1u)))) ? 1 : 0;
+                }
+            }
+        } else {
+            // the row's list: the pool's words in slot order
+            uint32_t *kl = klist + 4 * first;
+            if (ranked) {
+                int k = cpos;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if ((pool >> i) & 1u) kl[k++] = kw[i];
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            for (int t = 0; __ballot(t < nc_mine) != 0; ++t) {
+                if (t < nc_mine) {
+                    const uint32_t kt = kl[t];
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+                        rk[i] += (kt < kw[i] || (kt == kw[i] && t < cpos + (int)__popc(pool & ((1u << i) - 1u)))) ? 1 : 0;
+                }
             }
         }
 #pragma unroll
         for (int i = 0; i < 4; ++i) below_m |= rk[i] < m ? 1u << i : 0u;
-    } else {
-        // the row's list: candidates' words in slot order, padded with the largest word to a multiple of four
-        uint32_t *kl = klist + 4 * first;
-        if (active) *reinterpret_cast<uint4 *>(klist + 4 * lane) = make_uint4(~0u, ~0u, ~0u, ~0u);
-        // With at most 64 candidates in the whole pass a lane ranks ONE candidate (the lane-th of the pass, in slot order)
-        // against its row's list, two instructions per list entry, instead of its own four slots against it, eight per
-        // entry: in rows much longer than their list most slots are no candidates.  clist[c]: where candidate c sits in the
-        // lists (bits 0..7) and its row (bits 8..11); rowinfo[r]: start of the row's list, its length << 8, m << 20.
-        const int n_pass_cand = (int)rl32((uint32_t)(cglob + (int)__popc(cm)), WAVE - 1);
-        const bool by_candidate = !EXACT && n_pass_cand <= WAVE;
-        if (ranked) {
-            int k = cpos, c = cglob;
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                if ((cm >> i) & 1u) {
-                    kl[k] = kw[i];
-                    if (by_candidate) clist[c++] = (uint32_t)(4 * first + k) | ((uint32_t)r << 8);
-                    ++k;
-                }
-            if (by_candidate && qi == 0) rowinfo[r] = (uint32_t)(4 * first) | ((uint32_t)n_c << 8) | ((uint32_t)m << 20);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (by_candidate) {
-            const bool have = lane < n_pass_cand;
-            const uint32_t ce = clist[lane];                       // (stale beyond the pass's candidates: masked below)
-            const uint32_t ri = rowinfo[(ce >> 8) & (QUAD_ROWS - 1)];
-            const uint32_t mine = klist[ce & 0xFFu];
-            const uint32_t *rl = klist + (ri & 0xFCu);
-            const int nc = have ? (int)((ri >> 8) & 0xFFFu) : 0;
-            int ra[4] = {0, 0, 0, 0};
-            for (int t0 = 0; __ballot(t0 < nc) != 0; t0 += 4) {
-                if (t0 < nc) {
-                    const uint4 kt = *reinterpret_cast<const uint4 *>(rl + t0);
-                    const uint32_t ks[4] = {kt.x, kt.y, kt.z, kt.w};
-                    rank4_below(mine, ks, ra);
-                }
-            }
-            const uint64_t low = __ballot(have && ra[0] + ra[1] + ra[2] + ra[3] < (int)(ri >> 20));
-            // this lane's candidates are numbers cglob, cglob + 1, .. of the pass: hand their bits back to its slots
-            uint32_t b = (uint32_t)(low >> (cglob & (WAVE - 1)));
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t is_c = (cm >> i) & 1u;
-                below_m |= (b & is_c) << i;
-                b >>= is_c;
-            }
-        } else {
-            for (int t0 = 0; __ballot(t0 < nc_mine) != 0; t0 += 4) {
-                if (t0 < nc_mine) {
-                    const uint4 kt = *reinterpret_cast<const uint4 *>(kl + t0);
-                    const uint32_t ks[4] = {kt.x, kt.y, kt.z, kt.w};
-#pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        if (!EXACT) {
-                            rank4(ks[q], kw, rk);
-                        } else {
-#pragma unroll
-                            for (int i = 0; i < 4; ++i)
-                                rk[i] += (ks[q] < kw[i] || (ks[q] == kw[i] && t0 + q < cpos + (int)__popc(cm & ((1u << i) - 1u)))) ? 1 : 0;
-                        }
-                    }
-                }
-            }
-#pragma unroll
-            for (int i = 0; i < 4; ++i) below_m |= rk[i] < m ? 1u << i : 0u;
-        }
-    }
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the lists are reused by the next pass
-    const uint32_t emit = take | (cm & below_m);
-    int epos, total, unused3;
-    seg(emit, epos, total, unused3);
-    bool ok = total == expect;            // (always true in the exact pass)
-    if constexpr (MODE == 2 && !EXACT) {
-        // largest kept key and smallest key left out, per row and class (LDS atomics on the bit patterns):
-        // rowstat[4 r + ..] = max kept intra, max kept inter, min left-out intra, min left-out inter
-        rowstat[lane] = rowstat[lane + WAVE] = (lane & 2) ? 0x7F800000u : 0u;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (ranked) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                if ((cm >> i) & 1u) {
-                    const int cls = ((nib >> i) & 1u) ? 0 : 1;
-                    if ((below_m >> i) & 1u) atomicMax(&rowstat[4 * r + cls], kw[i]);
-                    else atomicMin(&rowstat[4 * r + 2 + cls], kw[i]);
-                }
-            }
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        if (ranked) {
-            const uint4 st = *reinterpret_cast<const uint4 *>(&rowstat[4 * r]);
-            const float m_in = (float)a.q_out, m_out = (float)a.q_in;      // an intra-community slot's clock is scaled by 1 - p
-            const float hi_in = __uint_as_float(st.x), hi_out = __uint_as_float(st.y);
-            const float lo_in = __uint_as_float(st.z), lo_out = __uint_as_float(st.w);
-            // (a slot that is no candidate has an approximate key of at least kappa, whatever its class)
-            ok = ok && keys_apart(hi_in, m_in, lo_in, m_in) && keys_apart(hi_in, m_in, lo_out, m_out) &&
-                 keys_apart(hi_out, m_out, lo_in, m_in) && keys_apart(hi_out, m_out, lo_out, m_out) &&
-                 keys_apart(hi_in, m_in, kappa, m_out) && keys_apart(hi_out, m_out, kappa, m_out);
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the lists are reused by the next pass
+        emit = take | (pool & below_m);
+        epos = before_bits(emit);
     }
     if (active && ok) {
-        int k = epos;
+        const int32_t *from = a.g_indices + R.base + jb;
+        int32_t id[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if ((emit >> i) & 1u) R.out[k++] = a.g_indices[R.base + jb + i];
-        if (qi == 0) set_row_count(a, g, row0 + (R.nq_row >> 8), total);
+            if ((emit >> i) & 1u) id[i] = from[i];
+        int32_t *to = out + R.out + epos;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if ((emit >> i) & 1u) to[__popc(emit & ((1u << i) - 1u))] = id[i];
+        if (qi == 0) set_row_count(a, g, row0 + r, expect);
     }
     uint64_t bad = __ballot(active && qi == 0 && !ok);
     uint32_t redo = 0u;
@@ -1102,21 +1040,16 @@ __device__ __forceinline__ bool select_big_row_weighted_f32(const SelectArgs &a,
 }
 
 // (occupancy targets: the weighted instantiation takes 85 registers when left alone, which leaves five waves per SIMD and
-// measures 5 % slower on a sampled group than 80 registers -- six waves, as many workgroups as its LDS allows -- with two
-// words spilled; the other two fit 64 registers, eight waves: 3 % on a group at p = 1)
+// measures 5 % slower on a sampled group than 80 registers, six waves; the other two fit 64 registers, eight waves: 3 % on a group at p = 1)
 template <int MODE>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 2 ? 6 : 8, 8))) void select_quad_kernel(SelectArgs a)
 {
     __shared__ QuadRow rows_s[4][QUAD_ROWS];
-    __shared__ int startq_s[4][QUAD_ROWS];
     __shared__ __align__(16) uint32_t klist_s[4][4 * WAVE];
-    __shared__ uint32_t cslot_s[4][CAND_CAP];              // (long rows: candidates' slots; passes: the pass's candidates)
-    __shared__ uint32_t rowinfo_s[4][QUAD_ROWS];
+    __shared__ uint32_t cslot_s[4][CAND_CAP];              // long rows: candidates' slots
     __shared__ unsigned long long k64_s[MODE == 2 ? 4 : 1][MODE == 2 ? 4 * WAVE : 1];     // weighted: exact 64-bit keys
-    __shared__ __align__(16) uint32_t rowstat_s[MODE == 2 ? 4 : 1][4 * QUAD_ROWS];
     const int wv = (int)threadIdx.x / WAVE;
     unsigned long long *k64 = k64_s[MODE == 2 ? wv : 0];
-    uint32_t *rowstat = rowstat_s[MODE == 2 ? wv : 0];
     const int g = blockIdx.y;
     const int n_dst = group_n_dst(a.prev_hdr, g, a.n_roots_total, a.batch_size);
     const int row0 = (int)(blockIdx.x * 4 + wv) * a.rows_per_wave;
@@ -1127,55 +1060,48 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 2 ?
     int32_t mv = 0;
     int64_t mbase = 0;
     int mdeg = 0;
-    int32_t *mout = nullptr;
+    int64_t mout = 0;
+    int32_t *out = a.out_indptr ? a.out_ids + (int64_t)g * a.out_stride : a.sel + (int64_t)g * a.sel_stride;
     if (lane < a.rows_per_wave && row0 + lane < n_dst) {
         mv = a.dst_ids[(int64_t)g * a.dst_stride + row0 + lane];
         mbase = a.g_indptr[mv];
         const int64_t d = a.g_indptr[mv + 1] - mbase;
         mdeg = (int)(d > 0x7FFFFFFF ? 0x7FFFFFFF : d);
-        mout = sel_row_ptr(a, g, row0 + lane);
+        mout = a.out_indptr ? (int64_t)a.out_indptr[(int64_t)g * a.out_indptr_stride + row0 + lane] : (int64_t)(row0 + lane) * a.fanout;
         if (mdeg == 0) set_row_count(a, g, row0 + lane, 0);
     }
     const int mq = (mdeg > 0 && mdeg <= QUAD_MAX_DEG) ? (mdeg + 3) >> 2 : 0;
-    // Packing of the rows' quads into passes of 64 (a row never straddles two passes): a pass takes, again and again, the
-    // first row not yet placed that still fits (first fit over the rows; filling the passes with the rows in their own
-    // order leaves them three quarters full on the degree mixes of sampled frontiers, this gets them to ~85 %).  The rows
-    // are stored in the order they were placed, so that their first quads ascend and a lane finds its row by bisection;
-    // rows without quads (empty, or longer than a pass) come last with a start no lane reaches.
-    uint32_t waiting = (uint32_t)__ballot(mq > 0);       // (lanes from QUAD_ROWS on hold no row: mq = 0)
-    int my_start = 0x3FFFFFFF, my_place = 0, placed = 0, n_pass = 0;
-    while (waiting) {
-        int room = WAVE;
-        for (;;) {
-            const uint32_t fits = (uint32_t)__ballot(mq <= room) & waiting;
-            if (!fits) break;
-            const int i = __builtin_ctz(fits);
-            if (lane == i) { my_start = n_pass * WAVE + (WAVE - room); my_place = placed; }
-            room -= (int)rl32((uint32_t)mq, i);
-            waiting &= ~(1u << i);
-            ++placed;
-        }
-        ++n_pass;
-    }
-    {
-        const uint32_t rest = (uint32_t)__ballot(lane < QUAD_ROWS && mq == 0);
-        if (lane < QUAD_ROWS && mq == 0) my_place = placed + (int)__popc(rest & ((1u << lane) - 1u));
-    }
     if (lane < QUAD_ROWS) {
         QuadRow R;
-        R.v = mv; R.deg = mdeg; R.startq = my_start; R.nq_row = mq | (lane << 8); R.base = mbase; R.out = mout;
-        rows_s[wv][my_place] = R;
-        startq_s[wv][my_place] = my_start;
+        R.v = mv; R.deg = mdeg; R.base = mbase; R.out = mout; R.pad = 0;
+        rows_s[wv][lane] = R;
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-
-    uint32_t exact_rows = a.exact_select ? ~0u : 0u;
-    if (!a.exact_select)
-        for (int p = 0; p < n_pass; ++p)
-            exact_rows |= quad_pass<MODE, false>(a, g, row0, p, ~0u, rows_s[wv], startq_s[wv], klist_s[wv], cslot_s[wv], rowinfo_s[wv], k64, rowstat, lane);
-    if (exact_rows)
-        for (int p = 0; p < n_pass; ++p)
-            quad_pass<MODE, true>(a, g, row0, p, exact_rows, rows_s[wv], startq_s[wv], klist_s[wv], cslot_s[wv], rowinfo_s[wv], k64, rowstat, lane);
+    // Packing of the rows' quads into passes of 64 (a row never straddles two passes): a pass takes, again and again, the
+    // first row not yet placed that still fits (first fit over the rows; filling the passes with the rows in their own
+    // order leaves them three quarters full on the degree mixes of sampled frontiers, this gets them to ~85 %).  Every lane
+    // from the row's first one on notes the row as it is placed, so that the pass needs no search for it.
+    auto run = [&](uint32_t waiting, auto exact) -> uint32_t {
+        constexpr bool EXACT = decltype(exact)::value;
+        uint32_t redo = 0u;
+        while (waiting) {
+            int room = WAVE, r = 0, first = 0;
+            for (;;) {
+                const uint32_t fits = (uint32_t)__ballot(mq <= room) & waiting;
+                if (!fits) break;
+                const int i = __builtin_ctz(fits), at = WAVE - room;
+                r = lane >= at ? i : r;
+                first = lane >= at ? at : first;
+                room -= (int)rl32((uint32_t)mq, i);
+                waiting &= ~(1u << i);
+            }
+            redo |= quad_pass<MODE, EXACT>(a, g, row0, r, first, WAVE - room, rows_s[wv], out, klist_s[wv], k64, lane);
+        }
+        return redo;
+    };
+    const uint32_t all_rows = (uint32_t)__ballot(mq > 0);       // (lanes from QUAD_ROWS on hold no row: mq = 0)
+    const uint32_t exact_rows = a.exact_select ? all_rows : run(all_rows, std::false_type{});
+    if (exact_rows) run(exact_rows, std::true_type{});
 
     // longer rows, one at a time
 #pragma unroll 1

@@ -106,3 +106,22 @@ def test_group_order(torch_mod, batch_size, n_batches, n_comm):
     assert np.array_equal(np.sort(order[:n]), want)
     c = comm[src.reshape(n_batches, -1)[order[:n] // b.cap_dst, order[:n] % b.cap_dst]].astype(np.int64)
     assert np.all(np.diff(c if n_comm <= 4096 else c * 4096 // n_comm) >= 0)
+
+
+# the bound that parts kept from left-out neighbours: one left out, one kept, rows that fill a pass, one class short of the fanout
+@pytest.mark.parametrize("p", [0.5, 0.51, 0.9, 0.97, 1.0])
+@pytest.mark.parametrize("fanout", [1, 15, 64])
+def test_rows_just_above_the_fanout(torch_mod, fanout, p):
+    rng = np.random.default_rng(fanout)
+    n = 4096
+    degrees = [fanout + 1, fanout + 2, 256, 255, 254, max(1, fanout), 5, 4, 3, 257, fanout + 1, 64]
+
+    def rows(i):
+        deg = degrees[i % len(degrees)]
+        near = rng.integers(0, deg + 1) if i % 3 else deg - (i % 2)      # how many lie in the node's own community
+        home = i // (n // 4 + 1) * (n // 4 + 1)
+        own = np.arange(home, min(n, home + n // 4 + 1))
+        other = np.setdiff1d(np.arange(n), own)
+        return np.concatenate([rng.choice(own, near, replace=False), rng.choice(other, deg - near, replace=False)])
+
+    check(torch_mod, fixed_rows(n, rows), n - 3, 1000, [fanout], p, f"rows of about {fanout} neighbours, p={p}")
