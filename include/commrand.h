@@ -480,7 +480,7 @@ cr_status cr_sage_linear_bwd_input(const cr_sage_layer *layer, const int32_t *hd
                                    void *stream);
 
 /* Backward pass of one whole GraphSAGE-mean layer above the input layer (Eq. 1, differentiated) in two launches
- * instead of four.  Same results, bit for bit, as
+ * instead of four (three for capacities of 16384 rows and more, where the two products run by themselves).  Same results, bit for bit, as
  *   cr_sage_linear_bwd(layer, header of batch g, blocks->cap_dst, h_self, agg, ld_in, dz_bf16, lr, weight_decay,
  *                      NULL, NULL, d_in_bf16, dW_out, db_out, ws, ws_bytes)
  * followed by
