@@ -19,6 +19,9 @@ constexpr int TN_DEPTH = 3;      // steps whose loads are in flight
 constexpr int TN_ROW = 160;   // staged row of the TN product: 128 columns + 32 of padding (320 bytes: the four rows that half a wave
                               // reads with one transpose read lie 16 banks apart)
 
+// the larger of the two, NaN if x is one (fmaxf would give the bound instead: 0 under a ReLU, -inf without one)
+__device__ __forceinline__ float at_least(float x, float bound) { return __builtin_elementwise_maximum(x, bound); }
+
 constexpr int LDS_ROW = 40;   // 32 bf16 of payload + 8 of padding per staged row (80 bytes)
 
 __device__ __forceinline__ bf16x8 lds_read8(const uint16_t *p)
@@ -552,8 +555,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
         for (int t = 0; t < 4; ++t)
 #pragma unroll
             for (int grp = 0; grp < 4; ++grp) {
-                const float v0 = fmaxf(acc[rb][t][grp * 4 + 0], floor_v), v1 = fmaxf(acc[rb][t][grp * 4 + 1], floor_v);
-                const float v2 = fmaxf(acc[rb][t][grp * 4 + 2], floor_v), v3 = fmaxf(acc[rb][t][grp * 4 + 3], floor_v);
+                const float v0 = at_least(acc[rb][t][grp * 4 + 0], floor_v), v1 = at_least(acc[rb][t][grp * 4 + 1], floor_v);
+                const float v2 = at_least(acc[rb][t][grp * 4 + 2], floor_v), v3 = at_least(acc[rb][t][grp * 4 + 3], floor_v);
                 *reinterpret_cast<uint2 *>(&ob[lr * WIDE_OROW + t * 32 + 8 * grp + 4 * half]) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
             }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -662,8 +665,8 @@ __device__ __forceinline__ void nt_stream_body(const NtArgs &a, const int M, uin
     auto convert_piece = [&](const f32x16 (&acc)[2][2], int piece) {
         const int cb = piece >> 3, grp = (piece >> 1) & 3, rb = piece & 1;
         const int n = 32 * cb + 8 * grp + 4 * half;
-        const float v0 = fmaxf(acc[rb][cb][grp * 4 + 0], floor_v), v1 = fmaxf(acc[rb][cb][grp * 4 + 1], floor_v);
-        const float v2 = fmaxf(acc[rb][cb][grp * 4 + 2], floor_v), v3 = fmaxf(acc[rb][cb][grp * 4 + 3], floor_v);
+        const float v0 = at_least(acc[rb][cb][grp * 4 + 0], floor_v), v1 = at_least(acc[rb][cb][grp * 4 + 1], floor_v);
+        const float v2 = at_least(acc[rb][cb][grp * 4 + 2], floor_v), v3 = at_least(acc[rb][cb][grp * 4 + 3], floor_v);
         *reinterpret_cast<uint2 *>(&ob[(rb * 32 + lr) * STREAM_OROW + n]) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
     };
     // the patch leaves as 128-byte row pieces

@@ -63,3 +63,60 @@ def test_many_rows(torch_mod, M, F_in, F_out, n_op):
             assert_close(got[:, cols], want[:, part * F_in:(part + 1) * F_in], 2.0 ** -8, "d_in", scale=1e-4)
         assert np.all(d_in.cpu().numpy()[M:].view(np.uint16) == 0x7FC0)
 
+
+
+# rows that are not finite through the kernels for many rows, N = 256: forward and input gradient, streaming (K = 256) and wide
+# (K = 320).  What the sums make of them comes out -- NaN stays NaN, with ReLU too, as it does below 16384 rows and in the oracle
+@pytest.mark.parametrize("F_in,F_out,cap", [(128, 256, 16384), (128, 320, 16384), (160, 256, 16384), (128, 256, 4096)])
+def test_rows_that_are_not_finite(torch_mod, F_in, F_out, cap):
+    torch = torch_mod
+    from paper_2504_18082_amd import binding as B
+    M = cap - 7
+    print(f"case not finite F_in={F_in} F_out={F_out} capacity={cap}", flush=True)
+    rng = np.random.default_rng(F_out)
+
+    def spoiled(cols):
+        x = rng.standard_normal((M, cols)).astype(np.float32)
+        for r in (0, 5, M - 1):
+            x[r, r % cols] = np.nan
+        x[17, 3], x[18, 3], x[19, 3], x[19, 4] = np.inf, -np.inf, np.inf, -np.inf
+        return x
+
+    W = np.abs(rng.standard_normal((2 * F_in, F_out)) / 16).astype(np.float32)       # (of one sign: row 19 meets inf and -inf)
+
+    def new_layer():                    # (a step on these gradients leaves NaN in the weights)
+        layer = B.SageLayer(W, np.zeros(F_out, np.float32))
+        layer.refresh()
+        return layer
+
+    layer = new_layer()
+    hdr = hdr_for(torch, M)
+    pad = lambda a: np.pad(a, ((0, cap - M), (0, 0)))
+    dz = spoiled(F_out)
+    d_dz = to_bf16_dev(torch, pad(dz), layer.N_pad)
+    clean = to_bf16_dev(torch, np.zeros((cap, F_in), np.float32), layer.F_pad)
+    ws = torch.empty(B.cr_sage_linear_bwd_workspace_bytes(F_in, F_out, cap), dtype=torch.uint8, device="cuda")
+    dW, db = torch.zeros((2 * F_in, F_out), device="cuda"), torch.zeros(F_out, device="cuda")
+    d_in = [torch.zeros((cap, 2 * layer.F_pad), dtype=torch.int16, device="cuda") for _ in range(2)]
+    B.cr_sage_linear_bwd(layer, C.c_void_p(hdr.data_ptr()), cap, clean, clean, layer.F_pad, d_dz, 0.0, 0.0, None, None, ws, dW, db, d_in_bf16=d_in[0])
+    layer = new_layer()
+    B.cr_sage_linear_bwd_input(layer, C.c_void_p(hdr.data_ptr()), cap, d_dz, None, None, d_in_bf16=d_in[1])
+    bf = lambda a: torch.from_numpy(oracle.round_bf16(a)).double()
+    Wb = bf(W)
+
+    def same(got, want, what):
+        assert np.array_equal(np.isnan(got), np.isnan(want)), f"{what}: NaN in other places"
+        assert np.array_equal(got[np.isinf(want)], want[np.isinf(want)]), f"{what}: infinities"
+        fin = np.isfinite(want)
+        assert_close(got[fin], want[fin], 2.0 ** -8, what, scale=1e-2)       # one rounding to bf16 of a float sum of ~13 in magnitude
+
+    want = (bf(dz) @ Wb.t()).numpy()
+    for t in d_in:
+        same(bf16_tensor_to_float(t)[:M], want, "d_in")
+    x = spoiled(2 * F_in)
+    hs, ag = to_bf16_dev(torch, pad(x[:, :F_in]), layer.F_pad), to_bf16_dev(torch, pad(x[:, F_in:]), layer.F_pad)
+    want = (bf(x) @ Wb).numpy()
+    for relu in (False, True):
+        out = torch.zeros((cap, layer.N_pad), dtype=torch.int16, device="cuda")
+        B.cr_sage_linear_fwd(layer, C.c_void_p(hdr.data_ptr()), cap, hs, ag, layer.F_pad, relu, None, out)
+        same(bf16_tensor_to_float(out)[:M, :F_out], np.where(want < 0, 0.0, want) if relu else want, f"out relu={relu}")
