@@ -1069,8 +1069,9 @@ __global__ __launch_bounds__(256) void gemm_tn_kernel(TnArgs a)
 // waits out its own chain of transpose reads, MFMAs, staging and barrier in each step (1250 cycles, of which the MFMAs are 256);
 // more loads in flight change nothing (three to eight steps ahead: the same), a second workgroup does but doubles the
 // partial sums.  Eight waves in two halves give every SIMD two waves with the partial sums of one workgroup:
-// 131 K rows x 608 x 256 (graph attention on the reddit-like graph) 87 -> 69 us, 61 K rows x 256 x 256 (papers) 21.6 -> 20.0.
-// Below this many rows the product shares its launch with the input gradient's (next kernel) or is short.
+// 131 K rows x 608 x 256 (graph attention on the reddit-like graph) 87 -> 69 us, 61 K rows x 256 x 256 (papers) 21.6 -> 20.0;
+// with the reduction of the partial sums 81 -> 67 us (131 K rows x 608 x 256), 27.6 -> 26.6 (66 K x 256 x 256), 21.5 -> 20.7 (33 K);
+// at 16 K rows 19.4 -> 19.8 (256 x 256), 23.0 -> 22.5 (608 x 256), 33.6 -> 30.4 (1216 x 256): about where it begins to pay.  Where the input gradient is wanted too, the next kernel serves.
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void gemm_tn_tall_kernel(TnArgs a)
 {
     extern __shared__ __attribute__((aligned(16))) uint16_t tn_lds[];
@@ -1360,8 +1361,8 @@ cr_status cr::linear_bwd_products(const cr_sage_layer *layer, const int32_t *hdr
     hipStream_t s = static_cast<hipStream_t>(stream);
 
     const unsigned tn_tiles = (unsigned)(n_op * ceil_div(F_pad, 128) * ceil_div(N_pad, 128));
-    const bool want_input = d_agg || d_in_bf16, tall = max_rows >= TN_TALL_MIN_ROWS;
-    if (want_input && !tall) {
+    const bool want_input = d_agg || d_in_bf16;
+    if (want_input) {
         // the input-gradient product shares the launch and the 512 resident workgroup slots: fewer, longer splits so
         // that both parts fit one round (its tiles counted at ~0.7 of the capacity, the usual fill of a sampled block)
         const int64_t nt_share = (int64_t)(n_op * F_pad / 64) * ceil_div(max_rows, 128) * 7 / 10;
@@ -1371,23 +1372,26 @@ cr_status cr::linear_bwd_products(const cr_sage_layer *layer, const int32_t *hdr
     TnArgs t;
     t.hdr = hdr; t.max_rows = max_rows; t.A0 = n_op == 2 ? h_self : agg; t.A1 = agg; t.lda = ld_in; t.K0 = F_pad; t.K2 = n_op * F_pad;
     t.Z = dz_bf16; t.N = N_pad; t.slots = splits; t.partial = partial;
-    NtArgs a;                       // the gradient w.r.t. the layer's inputs (weights from before the step)
-    a.hdr = hdr; a.max_rows = max_rows; a.A0 = dz_bf16; a.A1 = dz_bf16; a.lda = N_pad; a.K0 = N_pad; a.K = N_pad;
-    a.B = layer->W_bf16; a.N = n_op * F_pad; a.bias = nullptr; a.relu = 0;
-    a.C0 = n_op == 2 ? d_self : d_agg; a.C1 = d_agg; a.ldc = F_pad; a.N0 = F_pad; a.Cb = d_in_bf16; a.ldcb = n_op * F_pad;
-    if (tall) {
-        // many rows: both products fill the chip by themselves, and the input gradient may take the kernels for many rows
-        static const hipError_t ready = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_tn_tall_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)TN_TALL_LDS_BYTES);
-        CR_HIP_CHECK(ready);
-        hipLaunchKernelGGL(gemm_tn_tall_kernel, dim3(tn_tiles, (unsigned)splits + (7 + tn_tiles - 1) / tn_tiles), dim3(512), TN_TALL_LDS_BYTES, s, t);
-        if (want_input) launch_nt(a, s);
-    } else if (want_input) {        // both in one launch
+    const dim3 tn_grid(tn_tiles, (unsigned)splits + (7 + tn_tiles - 1) / tn_tiles);
+    if (want_input) {   // also the gradient w.r.t. the layer's inputs (weights from before the step), in the same launch
+        // (At any number of rows.  The whole call with the products in launches of their own, the tall kernel and what launch_nt
+        // picks, at 16384 / 32768 / 65536 / 131072 rows: two operands of 256 -> 256, float gradients, 34 / 48 / 76 / 156 us against
+        // 26 / 40 / 69 / 155 here; one operand of 256 -> 256, bf16 gradients, which the streaming product serves, 30 / 36 / 47 / 66
+        // against 22 / 25 / 39 / 65; one of 256 -> 512, 35 / 43 / 64 / 113 against 27 / 36 / 61 / 115.)
+        NtArgs a;
+        a.hdr = hdr; a.max_rows = max_rows; a.A0 = dz_bf16; a.A1 = nullptr; a.lda = N_pad; a.K0 = N_pad; a.K = N_pad;
+        a.B = layer->W_bf16; a.N = n_op * F_pad; a.bias = nullptr; a.relu = 0;
+        a.C0 = n_op == 2 ? d_self : d_agg; a.C1 = d_agg; a.ldc = F_pad; a.N0 = F_pad; a.Cb = d_in_bf16; a.ldcb = n_op * F_pad;
         const unsigned nt_cols = (unsigned)(a.N / 64);
         const unsigned tn_blocks = (unsigned)round_up((int64_t)tn_tiles * splits + 7, 8);
         const unsigned nt_blocks = (unsigned)round_up((int64_t)nt_cols * ceil_div(max_rows, 128) + 7, 8);
         hipLaunchKernelGGL(gemm_tn_nt_kernel, dim3(tn_blocks + nt_blocks), dim3(256), 0, s, t, a, tn_blocks, tn_tiles, nt_cols);
+    } else if (max_rows >= TN_TALL_MIN_ROWS) {
+        static const hipError_t ready = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_tn_tall_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)TN_TALL_LDS_BYTES);
+        CR_HIP_CHECK(ready);
+        hipLaunchKernelGGL(gemm_tn_tall_kernel, tn_grid, dim3(512), TN_TALL_LDS_BYTES, s, t);
     } else {
-        hipLaunchKernelGGL(gemm_tn_kernel, dim3(tn_tiles, (unsigned)splits + (7 + tn_tiles - 1) / tn_tiles), dim3(256), 0, s, t);
+        hipLaunchKernelGGL(gemm_tn_kernel, tn_grid, dim3(256), 0, s, t);
     }
     SgdArgs g;
     g.hdr = hdr; g.max_rows = max_rows; g.n_splits = splits; g.partial = partial;

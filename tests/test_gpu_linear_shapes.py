@@ -120,3 +120,35 @@ def test_rows_that_are_not_finite(torch_mod, F_in, F_out, cap):
         out = torch.zeros((cap, layer.N_pad), dtype=torch.int16, device="cuda")
         B.cr_sage_linear_fwd(layer, C.c_void_p(hdr.data_ptr()), cap, hs, ag, layer.F_pad, relu, None, out)
         same(bf16_tensor_to_float(out)[:M, :F_out], np.where(want < 0, 0.0, want) if relu else want, f"out relu={relu}")
+
+
+def launches(torch, call):
+    """Number of kernels a call launches (nodes of its captured graph)."""
+    from paper_2504_18082_amd import binding as B
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = C.c_size_t(0)
+    assert B.lib().hipGraphGetNodes(C.c_void_p(graph.raw_cuda_graph()), None, C.byref(n)) == 0
+    return n.value
+
+
+# the weight gradient and the input gradient go side by side in one launch at every number of rows (two launches are slower up to
+# 131072 rows, by half at 16384), the reduction of the weight gradient's partial sums is the other
+@pytest.mark.parametrize("cap,F_out,n_op", [(4096, 256, 2), (16384, 256, 2), (16384, 256, 1), (66_000, 320, 2)])
+def test_backward_products_share_a_launch(torch_mod, cap, F_out, n_op):
+    torch = torch_mod
+    from paper_2504_18082_amd import binding as B
+    print(f"case shared launch, capacity {cap}", flush=True)
+    layer = B.SageLayer(np.zeros((n_op * 128, F_out), np.float32), np.zeros(F_out, np.float32), n_operands=n_op)
+    layer.refresh()
+    rows = lambda cols: torch.zeros((cap, cols), dtype=torch.int16, device="cuda")
+    hdr, x, dz, d_in = hdr_for(torch, cap - 5), rows(128), rows(layer.N_pad), rows(n_op * 128)
+    ws = torch.empty(B.cr_sage_linear_bwd_workspace_bytes(128, F_out, cap), dtype=torch.uint8, device="cuda")
+    dW, db = torch.zeros((n_op * 128, F_out), device="cuda"), torch.zeros(F_out, device="cuda")
+    for out in (d_in, None):
+        call = lambda: B.cr_sage_linear_bwd(layer, C.c_void_p(hdr.data_ptr()), cap, x if n_op == 2 else None, x, 128, dz, 0.0, 0.0, None, None, ws,
+                                            dW, db, d_in_bf16=out)
+        call()                                   # (the kernels are loaded by now)
+        torch.cuda.synchronize()
+        assert launches(torch, call) == 2
