@@ -210,8 +210,9 @@ typedef struct {
 } cr_block_set;
 
 #define CR_SAMPLE_STRICT_INTRA 1u /* at p = 1 never take an inter-community neighbour (rows may be short) */
-#define CR_SAMPLE_HASH_DEDUP 2u   /* de-duplicate the frontier with the open-addressing table even when the graph is small
-                                     enough for the direct-address table (less workspace; same results) */
+#define CR_SAMPLE_HASH_DEDUP 2u   /* de-duplicate every hop's frontier with the open-addressing table: also where the graph is
+                                     small enough for the direct-address table (less workspace) and where the hop is small
+                                     enough to need no table in memory; same results */
 
 #define CR_SAMPLE_INPUT_GLOBAL_IDS 4u /* leave the input-side block (layer 0) in global ids: its frontier is not
                                      de-duplicated or relabelled.  Produced for layer 0: hdr (N_DST, NNZ, STATUS;
@@ -260,9 +261,11 @@ cr_status cr_block_capacities(const cr_sample_cfg *cfg, int64_t n_nodes, int32_t
 cr_status cr_sample_blocks_workspace_bytes(const cr_sample_cfg *cfg, int64_t n_nodes, int32_t batch_size,
                                            int32_t n_batches, size_t *bytes /*host*/);
 
-/* Which frontier de-duplication table cr_sample_blocks will use for this request (same results either way): one int32
- * per node and batch, addressed by node id (CR_DEDUP_DIRECT: graphs up to four times the largest table), or an
- * open-addressing table of twice the largest frontier (CR_DEDUP_HASH: larger graphs, or CR_SAMPLE_HASH_DEDUP). */
+/* Which frontier de-duplication table cr_sample_blocks keeps in the workspace for this request (same results either way):
+ * one int32 per node and batch, addressed by node id (CR_DEDUP_DIRECT: graphs up to four times the largest table), or an
+ * open-addressing table of twice the largest frontier (CR_DEDUP_HASH: larger graphs, or CR_SAMPLE_HASH_DEDUP).  With
+ * CR_SAMPLE_HASH_DEDUP or in strict sampling at p = 1 every hop that is de-duplicated uses it; otherwise the larger hops do, and
+ * hops of up to 294912 ids (destination nodes and edges of a batch, by capacity) may be de-duplicated on chip instead. */
 #define CR_DEDUP_DIRECT 0
 #define CR_DEDUP_HASH 1
 /* Self-test of the weighted neighbour selection (Section 4.2 with 0.5 < p < 1; exponential-clock keys): the selection

@@ -2486,7 +2486,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         const bool global_ids = l == 0 && (cfg->flags & CR_SAMPLE_INPUT_GLOBAL_IDS), tr = !global_ids && b.t_indptr != nullptr;
         const bool direct_out = global_ids && !sa.strict_p1;
         // Frontier in LDS: hops of at most 32 parts of ids (294912) whose row pointers are known before the selection, that is
-        // all but the strict setting.  Measured against the tables in memory (all kernels of the hop except its selection):
+        // all but the strict setting (CR_SAMPLE_HASH_DEDUP asks for the table in so many words).  Measured against the tables in memory (all kernels of the hop except its selection):
         // 32 x 67 K ids (products-like, second hop) 335 -> 90 us, 32 x 6 K ids (its root hop, one workgroup per batch and
         // one launch instead of nine) 95 -> 33 us, 8 x 280 K ids (reddit-like input hop, 32 parts) 310 -> 177 us.  The cost
         // grows with ids times parts, the tables' with ids: beyond this the ratio that is left is used up (the 1.1 M ids of
@@ -2499,7 +2499,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         if (t_parts < ceil_div(b.cap_src, T_SOURCES)) t_parts = ceil_div(b.cap_src, T_SOURCES);
         if (t_parts < hop_chunks) t_parts = hop_chunks;
         const bool lds_transpose = tr && t_parts <= T_PARTS_MAX && cap_dst < (1 << 17) && hop_lds_ready();
-        const bool lds_hop = !global_ids && !sa.strict_p1 && hop_items <= (int64_t)PARTS_MAX * LIST_MEAN && p.max_nnz_t >= p.cap_nnz[l] &&
+        const bool lds_hop = !global_ids && !sa.strict_p1 && !(cfg->flags & CR_SAMPLE_HASH_DEDUP) && hop_items <= (int64_t)PARTS_MAX * LIST_MEAN && p.max_nnz_t >= p.cap_nnz[l] &&
                              (!tr || lds_transpose) && hop_lds_ready();
         const bool one_part = lds_hop && hop_items <= LIST_CAP;
         ScanArgs sc;

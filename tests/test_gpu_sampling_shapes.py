@@ -61,6 +61,47 @@ def test_frontier_parts(torch_mod, batch_size, fanout):
     check(torch_mod, graph, min(n, 2 * batch_size - batch_size // 3), batch_size, [2, fanout], 0.5, "frontier parts")
 
 
+def wide_graph(n, n_rows, degree):
+    """n nodes, the first n_rows of them with `degree` neighbours anywhere: a hop at those reaches almost as many ids as it has edges."""
+    rng = np.random.default_rng(degree)
+    r = np.sort(rng.integers(0, n - degree, size=(n_rows, degree)), axis=1) + np.arange(degree)          # ascending, distinct
+    indptr = np.minimum(np.arange(n + 1, dtype=np.int64), n_rows) * degree
+    return indptr, r.reshape(-1).astype(np.int32), (np.arange(n) // (n // 4 + 1)).astype(np.int32)
+
+
+def sample_wide(torch, batch_size, fanout, flags=0, p=0.5, cut=0):
+    """One batch at the head of wide_graph, two hops; the first hop's frontier array `cut` entries short of what it needs."""
+    from paper_2504_18082_amd import binding as B
+    n = 1_200_000
+    graph = wide_graph(n, batch_size + 1000, fanout + 1)
+    roots = np.random.default_rng(2).permutation(batch_size + 1000).astype(np.int32)[:batch_size]
+    want = oracle.sample_blocks(graph, roots, [1, fanout], p, bool(flags & B.CR_SAMPLE_STRICT_INTRA), 5, 1, 0, np.full(n, -1, dtype=np.int32))
+    cfg = B.make_sample_cfg([1, fanout], p, 5, 1, 0, flags | (B.CR_SAMPLE_SMALL_FRONTIER if cut else 0))
+    layers = B.alloc_block_sets(cfg, n, batch_size, 1)
+    if cut:
+        cap_src = want[1].n_src - cut
+        layers = [B.BlockSet(1, 1, cap_src, 2 * cap_src, cap_src, False), B.BlockSet(1, fanout, batch_size, cap_src, batch_size * fanout, True)]
+    ws = torch.full((B.cr_sample_blocks_workspace_bytes(cfg, n, batch_size, 1),), 0xAB, dtype=torch.uint8, device="cuda")
+    dg = DeviceGraph(torch, graph, 4, edge_classes=True)
+    B.cr_sample_blocks(dg.c, cfg, torch.from_numpy(roots).cuda(), batch_size, batch_size, 1, ws, layers)
+    torch.cuda.synchronize()
+    return graph, roots, want, layers, ws
+
+
+@pytest.mark.parametrize("batch_size", [700, 3000])
+def test_hash_dedup_flag_takes_the_table(torch_mod, batch_size):
+    """CR_SAMPLE_HASH_DEDUP names the open-addressing table, which has at least twice as many words as the frontier has ids: half
+    of them stay as they were cleared (all ones, which nothing else leaves in the workspace).  One hop only: the input-side block
+    is left in global ids."""
+    from paper_2504_18082_amd import binding as B
+    print(f"case hash flag: {batch_size} rows", flush=True)
+    for flags, table in ((B.CR_SAMPLE_INPUT_GLOBAL_IDS, False), (B.CR_SAMPLE_INPUT_GLOBAL_IDS | B.CR_SAMPLE_HASH_DEDUP, True)):
+        graph, roots, want, layers, ws = sample_wide(torch_mod, batch_size, 8, flags)
+        compare(layers, 1, graph, roots, [1, 8], 0.5, False, 5, 1, 0, batch_size, "hash flag", input_global=True)
+        cleared = int((ws[:ws.numel() // 8 * 8].view(torch_mod.int64) == -1).sum())
+        assert cleared >= want[1].n_src if table else cleared == 0
+
+
 # a handful of nodes that every row chooses: lists of a part and of a range of sources that overflow, segments that are sorted
 # rather than ranked, in LDS (15000 edges) and in memory (108000)
 @pytest.mark.parametrize("batch_size,hubs", [(3000, 5), (12_000, 9)])
