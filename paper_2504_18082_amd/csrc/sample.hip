@@ -1771,7 +1771,8 @@ constexpr int T_SOURCES = 11264;                // sources of one transposed ran
 constexpr int T_LIST = 14336;                   // edges of one transposed range
 constexpr int T_MEAN = 9216;
 constexpr int T_PARTS_MAX = 40;
-constexpr int T_RANK_MAX = 1024;                // longest segment whose entries count their rank; longer ones are sorted
+constexpr int T_RANK_WORK = 1 << 18;            // most comparisons that the rows of a range are ranked with (2^19 and 2^20 measure the
+                                                // same; with 2^21 hops on skewed graphs take up to 2.8 times as long in all)
 constexpr size_t DEDUP_LDS_BYTES = (size_t)(2 * LIST_CAP + PART_TABLE) * 4;
 constexpr size_t NUMBER_LDS_BYTES = (size_t)NUMBER_WORDS * 12;
 constexpr size_t T_LDS_BYTES = (size_t)(T_SOURCES + 1 + 2 * T_LIST + 32) * 4;
@@ -1797,7 +1798,7 @@ __device__ __forceinline__ uint32_t id_part(uint32_t id, uint32_t parts)
 }
 
 struct HopShared {
-    int count, overflow, below, n_long;
+    int count, overflow, below, work;
     int scan[17];
 };
 
@@ -2024,36 +2025,127 @@ __device__ __forceinline__ int hop_number(const DedupArgs &a, int g, int n_dst, 
     return n_src;
 }
 
-// sorts x[0..n) ascending (n workgroup-uniform): a merge network whose every exchange moves the smaller value to the lower
-// index, so the places from n on act as values behind all others
-__device__ __forceinline__ void merge_network(int32_t *x, int n)
+// Rows of a range of sources [lo, lo + n) that the lists of hop_transpose do not hold, or whose segments are so long that ranking
+// their rows one against all takes longer than this.  Either is a matter of the graph: a few nodes that a large share of a hop's
+// rows chooses are numbered early and lie in one range.  The edges are taken in order, those of the range collected in order, up
+// to T_WINDOW of them; two stable passes of seven bits sort them by source, which leaves every source's rows ascending, and they
+// go behind the rows of the windows before: start[s] is where the next row of source s goes.  Nothing here depends on how the
+// edges spread over the sources.  (In place of ranks in memory for ranges that the lists do not hold, and merge networks for
+// segments of more than 1024 rows.  One batch of 16384 rows, fanout 15, on a graph with a power law: 1946 -> 188 us, 690 with the
+// counters in memory; 32 x 1024 rows, fanouts 15 10 5, half of the edges with 16 nodes: 4986 -> 86, 800; 2 x 2048 rows of 64
+// there: 2926 -> 86, 200.)
+constexpr int T_ROUND = 4 * HOP_THREADS;        // edges looked at between two barriers
+constexpr int T_WINDOW = 2 * T_ROUND;           // a window is put in order once another round might not fit
+static_assert(2 * T_WINDOW + T_SOURCES <= 2 * T_LIST, "the window and its copy and a word per source fit the room of the lists");
+__device__ __forceinline__ void transpose_windows(const int32_t *indices, const int32_t *edge_rows, int nnz, int lo, int n, int *start, int32_t *room,
+                                                  int *wave_sum /*[16]*/, HopShared &sh, int32_t *out)
 {
-    auto exchange = [&](int i, int j) {
-        if (j >= n) return;
-        const int32_t p = x[i], q = x[j];
-        if (q < p) { x[i] = q; x[j] = p; }
-    };
-    for (int size = 2; size < 2 * n; size *= 2) {
+    constexpr int WAVES = HOP_THREADS / WAVE, PER_WAVE = T_WINDOW / WAVES, DIGITS = 128;
+    int32_t *list = room, *other = room + T_WINDOW;
+    int *head = reinterpret_cast<int *>(room + 2 * T_WINDOW);      // [T_SOURCES]: first place of a source's rows in the sorted window
+    int *digit = head;                                             // [DIGITS][WAVES], before that
+    const int tid = threadIdx.x, lane = lane_id(), wave = tid / WAVE;
+    int held = 0;                                                  // (uniform, as everything that steers the loops)
+    auto sort_pass = [&](const int32_t *from, int32_t *to, int shift) {
+        for (int i = tid; i < DIGITS * WAVES; i += HOP_THREADS) digit[i] = 0;
         __syncthreads();
-        for (int i = threadIdx.x; i < n; i += HOP_THREADS)
-            if ((i & (size - 1)) < size / 2) exchange(i, i ^ (size - 1));
-        for (int d = size / 4; d > 0; d /= 2) {
-            __syncthreads();
-            for (int i = threadIdx.x; i < n; i += HOP_THREADS)
-                if ((i & d) == 0) exchange(i, i + d);
+        const int first = wave * PER_WAVE + lane, last = min(held, (wave + 1) * PER_WAVE);
+        for (int i = first; i < last; i += WAVE) atomicAdd(&digit[((from[i] >> shift) & (DIGITS - 1)) * WAVES + wave], 1);
+        __syncthreads();
+        static_assert(DIGITS * WAVES == 2 * HOP_THREADS, "two counters per thread");
+        const int c0 = digit[2 * tid], c1 = digit[2 * tid + 1];
+        int total;
+        const int run = block_exclusive_scan_1024(c0 + c1, sh.scan, total);
+        digit[2 * tid] = run;
+        digit[2 * tid + 1] = run + c0;
+        __syncthreads();
+        for (int i = first; i - lane < last; i += WAVE) {          // (whole waves)
+            const bool have = i < last;
+            const int32_t x = have ? from[i] : 0;
+            const int d = (x >> shift) & (DIGITS - 1);
+            uint64_t peers = __ballot(have);                       // lanes with the same digit
+#pragma unroll
+            for (int b = 0; b < 7; ++b) {
+                const uint64_t m = __ballot(have && ((d >> b) & 1));
+                peers &= ((d >> b) & 1) ? m : ~m;
+            }
+            const int below = lanes_below(peers, 0);
+            int at = 0;
+            if (have) at = digit[d * WAVES + wave] + below;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (have && below == 0) digit[d * WAVES + wave] = at + __popcll(peers);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            if (have) to[at] = x;
         }
+        __syncthreads();
+    };
+    for (int i0 = 0; i0 < nnz; i0 += T_ROUND) {
+        // a wave takes consecutive edges, so that the list keeps their order
+        const int e0 = i0 + wave * (T_ROUND / WAVES) + lane;
+        int32_t x[4], row[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int e = min(e0 + k * WAVE, nnz - 1);
+            x[k] = indices[e] - lo;
+            row[k] = edge_rows[e];
+        }
+        bool take[4];
+        int mine = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            take[k] = e0 + k * WAVE < nnz && (uint32_t)x[k] < (uint32_t)n;
+            mine += __popcll(__ballot(take[k]));
+        }
+        if (lane == 0) wave_sum[wave] = mine;
+        __syncthreads();
+        int at = held, more = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+            const int c = wave_sum[w];
+            at += w < wave ? c : 0;
+            more += c;
+        }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const uint64_t m = __ballot(take[k]);
+            if (take[k]) list[lanes_below(m, at)] = (row[k] << 14) | x[k];      // (rows < 2^17)
+            at += __popcll(m);
+        }
+        held += more;
+        __syncthreads();
+        if (held <= T_WINDOW - T_ROUND && i0 + T_ROUND < nnz) continue;
+        sort_pass(list, other, 0);
+        sort_pass(other, list, 7);
+        for (int i = tid; i < held; i += HOP_THREADS) {
+            const int s = list[i] & 16383;
+            if (i == 0 || (list[i - 1] & 16383) != s) head[s] = i;
+        }
+        __syncthreads();
+        for (int i = tid; i < held; i += HOP_THREADS) {
+            const int32_t y = list[i];
+            const int s = y & 16383;
+            out[start[s] + i - head[s]] = y >> 14;
+        }
+        __syncthreads();
+        for (int i = tid; i < held; i += HOP_THREADS) {
+            const int s = list[i] & 16383;
+            if (i == held - 1 || (list[i + 1] & 16383) != s) start[s] += i - head[s] + 1;
+        }
+        __syncthreads();
+        held = 0;
     }
-    __syncthreads();
 }
 
-// Transposed block of one range of sources: row pointers and, per source, the destination rows that use it, ascending.
+// Transposed block of one range of sources: row pointers and, per source, the destination rows that use it, ascending.  ANY_SIZE:
+// the range may have more edges than the lists hold.
+template <bool ANY_SIZE>
 __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_dst, int n_src, int nnz, int part, int parts, uint32_t *lds, HopShared &sh)
 {
     int *start = reinterpret_cast<int *>(lds);                                  // [T_SOURCES + 1]
     int32_t *list = reinterpret_cast<int32_t *>(lds) + T_SOURCES + 1;           // [T_LIST] row << 14 | source, as they come
     int32_t *sorted = list + T_LIST;                                            // [T_LIST] ... source by source
-    int *longs = reinterpret_cast<int *>(sorted + T_LIST);                      // [32] sources with long segments
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid / WAVE;
+    int *wave_sum = reinterpret_cast<int *>(sorted + T_LIST);                   // [32] of the windows
+    const int tid = threadIdx.x, lane = lane_id();
     const int32_t *indices = a.indices + (int64_t)g * a.indices_stride;
     int32_t *t_indptr = a.t_indptr + (int64_t)g * a.t_indptr_stride, *t_indices = a.t_indices + (int64_t)g * a.indices_stride;
     const int range = (n_src + parts - 1) / parts;
@@ -2061,7 +2153,7 @@ __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_d
     if (part == parts - 1 && tid == 0) t_indptr[n_src] = nnz;
     if (n <= 0) return;                                                        // (uniform)
     for (int i = tid; i <= n; i += HOP_THREADS) start[i] = 0;
-    if (tid == 0) { sh.count = 0; sh.below = 0; sh.n_long = 0; }
+    if (tid == 0) { sh.count = 0; sh.below = 0; sh.work = 0; }
     __syncthreads();
     // the range's edges: source and place of every edge into the lists (the lists' two arrays, for now), then the row in its
     // place's stead, both packed into one word
@@ -2080,13 +2172,16 @@ __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_d
     auto scan_starts = [&]() {
         constexpr int PER = T_SOURCES / HOP_THREADS;
         int sum = 0, total;
+        uint32_t squares = 0;
         const int s0 = tid * PER;
         int x[PER];
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
             x[k] = s0 + k < n ? start[s0 + k] : 0;
             sum += x[k];
+            squares += (uint32_t)x[k] * (uint32_t)x[k];
         }
+        if (count <= T_LIST && squares > 1024u) atomicAdd(&sh.work, (int)squares);      // (the others: segments of 32 at most)
         int run = block_exclusive_scan_1024(sum, sh.scan, total);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
@@ -2099,7 +2194,7 @@ __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_d
         if (tid == 0) start[n] = total;
         __syncthreads();
     };
-    if (count <= T_LIST) {
+    if (!ANY_SIZE || count <= T_LIST) {
 #pragma unroll 4
         for (int i = tid; i < count; i += HOP_THREADS) list[i] = (edge_rows[list[i]] << 14) | sorted[i];      // (rows < 2^17)
         __syncthreads();
@@ -2108,69 +2203,44 @@ __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_d
         for (int i = tid; i < count; i += HOP_THREADS) atomicAdd(&start[list[i] & 16383], 1);
         __syncthreads();
         scan_starts();
-        for (int i = tid; i < count; i += HOP_THREADS) {
-            const int32_t x = list[i];
-            sorted[atomicAdd(&start[x & 16383], 1)] = x;                       // start[s] becomes the segment's end
-        }
-        __syncthreads();
-        for (int i = tid; i < count; i += HOP_THREADS) {
-            const int32_t x = sorted[i];
-            const int s = x & 16383, s0 = s > 0 ? start[s - 1] : 0, s1 = start[s];
-            if (s1 - s0 > T_RANK_MAX) {
-                if (i == s0) longs[atomicAdd(&sh.n_long, 1)] = s;              // (at most T_LIST / T_RANK_MAX of them)
-                continue;
+        if (sh.work <= T_RANK_WORK) {
+            for (int i = tid; i < count; i += HOP_THREADS) {
+                const int32_t x = list[i];
+                sorted[atomicAdd(&start[x & 16383], 1)] = x;                   // start[s] becomes the segment's end
             }
-            // (most segments hold one or two rows; the longer ones are read four at a time, or a wave waits out one LDS round
-            // trip per row of its longest segment)
-            int rank = 0;
-            for (int q = s0; q < s1; q += 4) {
+            __syncthreads();
+            for (int i = tid; i < count; i += HOP_THREADS) {
+                const int32_t x = sorted[i];
+                const int s = x & 16383, s0 = s > 0 ? start[s - 1] : 0, s1 = start[s];
+                // (most segments hold one or two rows; the longer ones are read four at a time, or a wave waits out one LDS round
+                // trip per row of its longest segment)
+                int rank = 0;
+                for (int q = s0; q < s1; q += 4) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const int32_t y = sorted[min(q + u, s1 - 1)];
-                    rank += (q + u < s1 && (y < x || (y == x && q + u < i))) ? 1 : 0;
+                    for (int u = 0; u < 4; ++u) {
+                        const int32_t y = sorted[min(q + u, s1 - 1)];
+                        rank += (q + u < s1 && (y < x || (y == x && q + u < i))) ? 1 : 0;
+                    }
                 }
+                t_indices[base + s0 + rank] = x >> 14;
             }
-            t_indices[base + s0 + rank] = x >> 14;
+            return;
+        }
+    } else {
+        // more edges than the lists hold
+        constexpr int U = 8;
+        for (int i0 = tid; i0 < nnz; i0 += U * HOP_THREADS) {
+            int32_t x[U];
+#pragma unroll
+            for (int k = 0; k < U; ++k) x[k] = indices[min(i0 + k * HOP_THREADS, nnz - 1)];
+#pragma unroll
+            for (int k = 0; k < U; ++k)
+                if (i0 + k * HOP_THREADS < nnz && (uint32_t)(x[k] - lo) < (uint32_t)n) atomicAdd(&start[x[k] - lo], 1);
         }
         __syncthreads();
-        for (int l = 0; l < sh.n_long; ++l) {
-            const int s = longs[l], s0 = s > 0 ? start[s - 1] : 0, len = start[s] - s0;
-            merge_network(sorted + s0, len);
-            for (int q = tid; q < len; q += HOP_THREADS) t_indices[base + s0 + q] = sorted[s0 + q] >> 14;
-        }
-        return;
+        scan_starts();
     }
-    // more edges than the lists hold: lengths and rows in two more passes, the rows in memory
-#pragma unroll 4
-    for (int e = tid; e < nnz; e += HOP_THREADS) {
-        const int s = indices[e] - lo;
-        if ((uint32_t)s < (uint32_t)n) atomicAdd(&start[s], 1);
-    }
-    __syncthreads();
-    scan_starts();
-    int32_t *tmp = a.t_tmp + (int64_t)g * a.tt_stride + base;
-#pragma unroll 4
-    for (int e = tid; e < nnz; e += HOP_THREADS) {
-        const int s = indices[e] - lo, row = edge_rows[e];
-        if ((uint32_t)s < (uint32_t)n) tmp[atomicAdd(&start[s], 1)] = row;     // start[s] becomes the segment's end
-    }
-    __syncthreads();
-    for (int s = wave; s < n; s += HOP_THREADS / WAVE) {
-        const int s0 = s > 0 ? start[s - 1] : 0, len = start[s] - s0;
-        if (len > T_RANK_MAX) continue;
-        for (int q = lane; q < len; q += WAVE) {
-            const int row = tmp[s0 + q];
-            int rank = 0;
-            for (int r = 0; r < len; ++r) rank += (tmp[s0 + r] < row || (tmp[s0 + r] == row && r < q)) ? 1 : 0;
-            t_indices[base + s0 + rank] = row;
-        }
-    }
-    for (int s = 0; s < n; ++s) {                                              // (uniform)
-        const int s0 = s > 0 ? start[s - 1] : 0, len = start[s] - s0;
-        if (len <= T_RANK_MAX) continue;
-        merge_network(tmp + s0, len);
-        for (int q = tid; q < len; q += HOP_THREADS) t_indices[base + s0 + q] = tmp[s0 + q];
-    }
+    transpose_windows(indices, edge_rows, nnz, lo, n, start, list, wave_sum, sh, t_indices + base);
 }
 
 #define CR_HOP()                                                                      \
@@ -2195,7 +2265,7 @@ __global__ __launch_bounds__(HOP_THREADS) void hop_number_kernel(DedupArgs a)
 __global__ __launch_bounds__(HOP_THREADS) void hop_transpose_kernel(DedupArgs a)
 {
     CR_HOP();
-    hop_transpose(a, g, n_dst, a.hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_N_SRC], nnz, (int)blockIdx.x, (int)gridDim.x, hop_lds, sh);
+    hop_transpose<true>(a, g, n_dst, a.hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_N_SRC], nnz, (int)blockIdx.x, (int)gridDim.x, hop_lds, sh);
 }
 
 // the three of them for a hop that is one part
@@ -2206,7 +2276,7 @@ __global__ __launch_bounds__(HOP_THREADS) void hop_kernel(DedupArgs a)
     __syncthreads();
     const int n_src = hop_number(a, g, n_dst, nnz, 0, 1, hop_lds, sh);
     __syncthreads();
-    if (a.t_indptr) hop_transpose(a, g, n_dst, n_src, nnz, 0, 1, hop_lds, sh);
+    if (a.t_indptr) hop_transpose<false>(a, g, n_dst, n_src, nnz, 0, 1, hop_lds, sh);
 }
 
 // one thread per 32 adjacency entries: find the row of the first one, then walk

@@ -102,12 +102,22 @@ def test_hash_dedup_flag_takes_the_table(torch_mod, batch_size):
         assert cleared >= want[1].n_src if table else cleared == 0
 
 
-# a handful of nodes that every row chooses: lists of a part and of a range of sources that overflow, segments that are sorted
-# rather than ranked, in LDS (15000 edges) and in memory (108000)
+# a handful of nodes that every row chooses: lists of a part and of a range of sources that overflow, ranges whose rows are sorted
+# rather than ranked, in one window (15000 edges) and in many (108000)
 @pytest.mark.parametrize("batch_size,hubs", [(3000, 5), (12_000, 9)])
 def test_every_row_shares_its_neighbours(torch_mod, batch_size, hubs):
     graph = fixed_rows(15_000, lambda i: 7 * np.arange(hubs) + 400)
     check(torch_mod, graph, batch_size, batch_size, [3, hubs], 0.5, "shared neighbours")
+
+
+# rows whose neighbours follow a power law, and hops of one part, several and many: ranges ranked next to ranges taken by windows (with
+# a list that overflows, and with one that does not), windows with many sources, a last window of a few edges
+@pytest.mark.parametrize("batch_size,fanout", [(700, 15), (1500, 15), (4097, 12), (9000, 15), (18_000, 15)])
+def test_skewed_neighbours(torch_mod, batch_size, fanout):
+    rng = np.random.default_rng(batch_size)
+    n = 40_000
+    graph = fixed_rows(n, lambda i: np.unique((rng.random(fanout + 5) ** 4 * n).astype(np.int32)))
+    check(torch_mod, graph, 2 * batch_size - 3, batch_size, [2, fanout], 0.5, "skewed")
 
 
 def test_one_part_gets_every_id(torch_mod):
