@@ -265,7 +265,8 @@ cr_status cr_sample_blocks_workspace_bytes(const cr_sample_cfg *cfg, int64_t n_n
  * one int32 per node and batch, addressed by node id (CR_DEDUP_DIRECT: graphs up to four times the largest table), or an
  * open-addressing table of twice the largest frontier (CR_DEDUP_HASH: larger graphs, or CR_SAMPLE_HASH_DEDUP).  With
  * CR_SAMPLE_HASH_DEDUP or in strict sampling at p = 1 every hop that is de-duplicated uses it; otherwise the larger hops do, and
- * hops of up to 294912 ids (destination nodes and edges of a batch, by capacity) may be de-duplicated on chip instead. */
+ * hops of up to 73728 ids per batch of the group, at most 294912 (destination nodes and edges of a batch, by capacity), may be
+ * de-duplicated on chip instead. */
 #define CR_DEDUP_DIRECT 0
 #define CR_DEDUP_HASH 1
 /* Self-test of the weighted neighbour selection (Section 4.2 with 0.5 < p < 1; exponential-clock keys): the selection

@@ -2556,12 +2556,17 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         const bool global_ids = l == 0 && (cfg->flags & CR_SAMPLE_INPUT_GLOBAL_IDS), tr = !global_ids && b.t_indptr != nullptr;
         const bool direct_out = global_ids && !sa.strict_p1;
         // Frontier in LDS: hops of at most 32 parts of ids (294912) whose row pointers are known before the selection, that is
-        // all but the strict setting (CR_SAMPLE_HASH_DEDUP asks for the table in so many words).  Measured against the tables in memory (all kernels of the hop except its selection):
+        // all but the strict setting (CR_SAMPLE_HASH_DEDUP asks for the table in so many words).  Measured against the tables in
+        // memory (all kernels of the hop except its selection):
         // 32 x 67 K ids (products-like, second hop) 335 -> 90 us, 32 x 6 K ids (its root hop, one workgroup per batch and
         // one launch instead of nine) 95 -> 33 us, 8 x 280 K ids (reddit-like input hop, 32 parts) 310 -> 177 us.  The cost
         // grows with ids times parts, the tables' with ids: beyond this the ratio that is left is used up (the 1.1 M ids of
         // a relabelled products-like input hop would be read 128 times), and the tables serve.  The transpose reads every
         // edge once per range of sources and is cut off at forty ranges for the same reason.
+        // Eight parts per batch of the group and no more: all parts of a batch read all of its ids, which takes as long for
+        // one batch as for eight, while the tables' kernels get shorter.  The whole call, tables over this, one batch of
+        // 55 / 74 / 110 / 147 / 295 K ids: 1.04 to 1.12, 0.96 to 1.01, 0.94 to 1.04, 0.88 to 0.95, 0.75 to 0.87; two of 110 / 147 /
+        // 220 / 295 K: 1.02 to 1.10, 0.97 to 1.01, 0.94 to 1.06, 0.88 to 1.01; four of 295 K: 1.04 to 1.18.
         const int64_t hop_items = (int64_t)cap_dst + p.cap_nnz[l];
         // (workgroups per batch that a hop is cut into at least: small groups are cut finer, or most compute units sit idle)
         const int hop_chunks = n_batches >= 32 ? PARTS_MIN : (n_batches <= 8 ? 32 : 256 / n_batches);
@@ -2569,8 +2574,9 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         if (t_parts < ceil_div(b.cap_src, T_SOURCES)) t_parts = ceil_div(b.cap_src, T_SOURCES);
         if (t_parts < hop_chunks) t_parts = hop_chunks;
         const bool lds_transpose = tr && t_parts <= T_PARTS_MAX && cap_dst < (1 << 17) && hop_lds_ready();
-        const bool lds_hop = !global_ids && !sa.strict_p1 && !(cfg->flags & CR_SAMPLE_HASH_DEDUP) && hop_items <= (int64_t)PARTS_MAX * LIST_MEAN && p.max_nnz_t >= p.cap_nnz[l] &&
-                             (!tr || lds_transpose) && hop_lds_ready();
+        const int64_t parts_max = PARTS_MIN * (int64_t)n_batches < PARTS_MAX ? PARTS_MIN * n_batches : PARTS_MAX;
+        const bool lds_hop = !global_ids && !sa.strict_p1 && !(cfg->flags & CR_SAMPLE_HASH_DEDUP) && hop_items <= parts_max * LIST_MEAN &&
+                             p.max_nnz_t >= p.cap_nnz[l] && (!tr || lds_transpose) && hop_lds_ready();
         const bool one_part = lds_hop && hop_items <= LIST_CAP;
         ScanArgs sc;
         sc.tile_before = nullptr;

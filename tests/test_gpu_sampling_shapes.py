@@ -52,7 +52,7 @@ def check(torch_mod, graph, n_roots, batch_size, fanouts, p, what):
     compare(layers, nb, graph, roots, fanouts, p, False, 5, 1, 0, batch_size, what)
 
 
-# ids of a hop (rows and chosen neighbours): just one part (11264) and just not, and just the sixteen parts (131072) and not
+# ids of a hop (rows and chosen neighbours): just one part (11264) and just not, and two sizes of sixteen parts
 @pytest.mark.parametrize("batch_size,fanout", [(1, 1), (64, 1), (1024, 10), (1025, 10), (1024, 64), (11915, 10), (11916, 10)])
 def test_frontier_parts(torch_mod, batch_size, fanout):
     rng = np.random.default_rng(batch_size)
@@ -69,23 +69,38 @@ def wide_graph(n, n_rows, degree):
     return indptr, r.reshape(-1).astype(np.int32), (np.arange(n) // (n // 4 + 1)).astype(np.int32)
 
 
-def sample_wide(torch, batch_size, fanout, flags=0, p=0.5, cut=0):
-    """One batch at the head of wide_graph, two hops; the first hop's frontier array `cut` entries short of what it needs."""
+def sample_wide(torch, batch_size, fanout, flags=0, p=0.5, cut=0, n_batches=1):
+    """Batches at the head of wide_graph, two hops; the first hop's frontier array `cut` entries short of what the first batch needs."""
     from paper_2504_18082_amd import binding as B
-    n = 1_200_000
-    graph = wide_graph(n, batch_size + 1000, fanout + 1)
-    roots = np.random.default_rng(2).permutation(batch_size + 1000).astype(np.int32)[:batch_size]
-    want = oracle.sample_blocks(graph, roots, [1, fanout], p, bool(flags & B.CR_SAMPLE_STRICT_INTRA), 5, 1, 0, np.full(n, -1, dtype=np.int32))
+    n, n_roots = 1_200_000, batch_size * n_batches
+    graph = wide_graph(n, n_roots + 1000, fanout + 1)
+    roots = np.random.default_rng(2).permutation(n_roots + 1000).astype(np.int32)[:n_roots]
+    want = oracle.sample_blocks(graph, roots[:batch_size], [1, fanout], p, bool(flags & B.CR_SAMPLE_STRICT_INTRA), 5, 1, 0, np.full(n, -1, dtype=np.int32))
     cfg = B.make_sample_cfg([1, fanout], p, 5, 1, 0, flags | (B.CR_SAMPLE_SMALL_FRONTIER if cut else 0))
-    layers = B.alloc_block_sets(cfg, n, batch_size, 1)
+    layers = B.alloc_block_sets(cfg, n, batch_size, n_batches)
     if cut:
         cap_src = want[1].n_src - cut
         layers = [B.BlockSet(1, 1, cap_src, 2 * cap_src, cap_src, False), B.BlockSet(1, fanout, batch_size, cap_src, batch_size * fanout, True)]
-    ws = torch.full((B.cr_sample_blocks_workspace_bytes(cfg, n, batch_size, 1),), 0xAB, dtype=torch.uint8, device="cuda")
+    ws = torch.full((B.cr_sample_blocks_workspace_bytes(cfg, n, batch_size, n_batches),), 0xAB, dtype=torch.uint8, device="cuda")
     dg = DeviceGraph(torch, graph, 4, edge_classes=True)
-    B.cr_sample_blocks(dg.c, cfg, torch.from_numpy(roots).cuda(), batch_size, batch_size, 1, ws, layers)
+    B.cr_sample_blocks(dg.c, cfg, torch.from_numpy(roots).cuda(), n_roots, batch_size, n_batches, ws, layers)
     torch.cuda.synchronize()
     return graph, roots, want, layers, ws
+
+
+# ids of a hop where the parts double (73728, 147456) and where the tables in memory take over (73728 for one batch, 147456 for a group
+# of two, 294912 for any): just at and just above, each with its transposed block; nearly every edge is a first appearance.  The
+# direct-address table leaves its cleared words behind
+@pytest.mark.parametrize("batch_size,n_batches,table", [(8192, 1, False), (8193, 1, True), (8193, 2, False), (16384, 2, False), (16385, 2, True),
+                                                        (16385, 4, False), (32768, 4, False), (32769, 4, True)])
+def test_frontier_parts_double(torch_mod, batch_size, n_batches, table):
+    from paper_2504_18082_amd import binding as B
+    print(f"case frontier of {n_batches} x {9 * batch_size} ids", flush=True)
+    graph, roots, want, layers, ws = sample_wide(torch_mod, batch_size, 8, B.CR_SAMPLE_INPUT_GLOBAL_IDS, n_batches=n_batches)
+    compare(layers, n_batches, graph, roots, [1, 8], 0.5, False, 5, 1, 0, batch_size, "parts double", input_global=True)
+    assert want[1].n_src > 0.8 * 9 * batch_size
+    words = (ws[:ws.numel() // 4 * 4].view(torch_mod.int32) == 0x7FFFFFFF).sum()
+    assert int(words) >= n_batches * 1_200_000 if table else int(words) == 0
 
 
 @pytest.mark.parametrize("batch_size", [700, 3000])
@@ -106,8 +121,8 @@ def test_hash_dedup_flag_takes_the_table(torch_mod, batch_size):
 # rather than ranked, in one window (15000 edges) and in many (108000)
 @pytest.mark.parametrize("batch_size,hubs", [(3000, 5), (12_000, 9)])
 def test_every_row_shares_its_neighbours(torch_mod, batch_size, hubs):
-    graph = fixed_rows(15_000, lambda i: 7 * np.arange(hubs) + 400)
-    check(torch_mod, graph, batch_size, batch_size, [3, hubs], 0.5, "shared neighbours")
+    graph = fixed_rows(30_000, lambda i: 7 * np.arange(hubs) + 400)
+    check(torch_mod, graph, 2 * batch_size, batch_size, [3, hubs], 0.5, "shared neighbours")
 
 
 # rows whose neighbours follow a power law, and hops of one part, several and many: ranges ranked next to ranges taken by windows (with
@@ -130,7 +145,7 @@ def test_one_part_gets_every_id(torch_mod):
     rng = np.random.default_rng(1)
     picks = np.sort(part0[(rng.integers(0, len(part0) - 20, size=(n, 1)) + np.arange(15))], axis=1)
     graph = (np.arange(n + 1, dtype=np.int64) * 15, picks.reshape(-1), (np.arange(n) // (n // 4 + 1)).astype(np.int32))
-    check(torch_mod, graph, 8000, 8000, [2, 15], 0.5, "one part")
+    check(torch_mod, graph, 16_000, 8000, [2, 15], 0.5, "one part")
 
 
 # destination rows of a whole group in community order: one workgroup (at most 8192 rows by capacity), just not, many buckets
