@@ -103,6 +103,47 @@ def test_frontier_parts_double(torch_mod, batch_size, n_batches, table):
     assert int(words) >= n_batches * 1_200_000 if table else int(words) == 0
 
 
+# transposed blocks of more than forty ranges (368640 edges) or of 131072 rows and more: counters, scan and ranks in memory, behind
+# either table
+@pytest.mark.parametrize("hash_dedup", [False, True])
+@pytest.mark.parametrize("batch_size,fanout", [(40_961, 9), (131_072, 1), (131_073, 2)])
+def test_transpose_in_memory(torch_mod, batch_size, fanout, hash_dedup):
+    from paper_2504_18082_amd import binding as B
+    print(f"case transpose in memory: {batch_size} rows of {fanout}, hash {hash_dedup}", flush=True)
+    graph, roots, _, layers, _ = sample_wide(torch_mod, batch_size, fanout, B.CR_SAMPLE_HASH_DEDUP if hash_dedup else 0)
+    compare(layers, 1, graph, roots, [1, fanout], 0.5, False, 5, 1, 0, batch_size, "transpose in memory")
+
+
+# a frontier cut short where several workgroups number the hop (27 K ids), and where the tables do (the same with the open-addressing
+# table, strict sampling): marked, the length that was needed reported, every local id inside the arrays
+@pytest.mark.parametrize("strict,hash_dedup", [(False, False), (False, True), (True, False)])
+def test_cut_frontier(torch_mod, strict, hash_dedup):
+    from paper_2504_18082_amd import binding as B
+    torch = torch_mod
+    flags = (B.CR_SAMPLE_STRICT_INTRA if strict else 0) | (B.CR_SAMPLE_HASH_DEDUP if hash_dedup else 0)
+    status = torch.zeros(B.CR_CTX_STATUS_WORDS, dtype=torch.int64, device="cuda")
+    ctx = B.Context(status=status)
+    ctx.make_current()
+    try:
+        print(f"case cut frontier strict={strict} hash={hash_dedup}", flush=True)
+        _, _, want, layers, _ = sample_wide(torch, 3000, 8, flags, 1.0 if strict else 0.5, cut=101)
+        blk, b, low = want[1], layers[1], layers[0]
+        assert ctx.poll_error() == (B.CR_ERR_ASYNC_OVERFLOW, blk.n_src)
+        n_src = blk.n_src - 101
+        hdr = b.hdr[0, :4].cpu().tolist()
+        assert hdr[:3] == [blk.n_dst, n_src, blk.nnz] and hdr[3] != 0 and int(low.hdr[0, 3]) != 0
+        assert np.array_equal(b.src_ids[0, :n_src].cpu().numpy(), blk.src_ids[:n_src])
+        idx = b.indices[0, :blk.nnz].cpu().numpy()
+        assert np.array_equal(idx, np.where(blk.indices < n_src, blk.indices, 0))
+        t_indptr, t_idx = b.t_indptr[0, :n_src + 1].cpu().numpy(), b.t_indices[0, :blk.nnz].cpu().numpy()
+        assert t_indptr[0] == 0 and t_indptr[-1] == blk.nnz and np.all(np.diff(t_indptr) == np.bincount(idx, minlength=n_src))
+        assert t_idx.min() >= 0 and t_idx.max() < blk.n_dst
+        assert int(low.hdr[0, 0]) == n_src and int(low.hdr[0, 2]) <= n_src
+    finally:
+        B.Context.make_none_current()
+        ctx.destroy()
+
+
 @pytest.mark.parametrize("batch_size", [700, 3000])
 def test_hash_dedup_flag_takes_the_table(torch_mod, batch_size):
     """CR_SAMPLE_HASH_DEDUP names the open-addressing table, which has at least twice as many words as the frontier has ids: half
