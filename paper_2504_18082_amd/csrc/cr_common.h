@@ -5,6 +5,7 @@
 #include <stdio.h>
 
 #include "../../include/commrand.h"
+#include "per_device.h"
 
 // host-side handle behind the C ABI's cr_ctx
 struct cr_ctx {
@@ -45,6 +46,17 @@ int64_t *async_status();    // device status words of the calling thread's curre
             return CR_ERR_HIP;                                                          \
         }                                                                               \
     } while (0)
+
+// Lets a kernel have more LDS than a launch gets without asking; a kernel's limit is one of the current device.
+inline bool lds_opt_in(PerDevice &asked, const void *kernel, size_t bytes)
+{
+    int device;
+    const bool granted = hipGetDevice(&device) == hipSuccess && asked.once(device, [&] {
+        return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) == hipSuccess;
+    });
+    if (!granted) (void)hipGetLastError();      // (the caller takes another kernel: not an error of the call)
+    return granted;
+}
 
 inline bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline int64_t round_up(int64_t x, int64_t m) { return (x + m - 1) / m * m; }

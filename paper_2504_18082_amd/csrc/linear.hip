@@ -819,11 +819,8 @@ static void launch_nt(const NtArgs &a, hipStream_t s)
     // many rows, bf16 output only, K small enough for the weights to stay in registers: the streaming kernel
     if (a.max_rows >= NT_WIDE_MIN_ROWS && a.N == WIDE_N && a.K <= STREAM_KMAX && a.K % 8 == 0 && a.K0 % 8 == 0 && a.A1 != nullptr &&
         a.Cb != nullptr && a.C0 == nullptr && a.ldcb == a.N && (int64_t)a.max_rows * a.lda < (1ll << 29)) {
-        static const bool ready = [] {
-            return hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_nt_stream_kernel), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)STREAM_LDS_BYTES) == hipSuccess;
-        }();
-        if (ready) {
+        static PerDevice asked;
+        if (lds_opt_in(asked, reinterpret_cast<const void *>(&gemm_nt_stream_kernel), STREAM_LDS_BYTES)) {
             const int64_t tiles = ceil_div(a.max_rows, STREAM_ROWS);
             hipLaunchKernelGGL(gemm_nt_stream_kernel, dim3((unsigned)(tiles < 256 ? tiles : 256)), dim3(256), STREAM_LDS_BYTES, s, a);
             return;
@@ -1079,6 +1076,12 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 constexpr size_t TN_TALL_LDS_BYTES = sizeof(uint16_t) * 2 * 2 * 2 * TN_BM * TN_ROW;
 constexpr int TN_TALL_MIN_ROWS = 16384;
+
+static bool tn_tall_ready()
+{
+    static PerDevice asked;
+    return lds_opt_in(asked, reinterpret_cast<const void *>(&gemm_tn_tall_kernel), TN_TALL_LDS_BYTES);
+}
 
 // The two products of a layer's backward pass that need nothing from each other (weight gradient, input
 // gradient) in one launch: both are short and bound by memory round trips, so side by side they take about as
@@ -1386,9 +1389,7 @@ cr_status cr::linear_bwd_products(const cr_sage_layer *layer, const int32_t *hdr
         const unsigned tn_blocks = (unsigned)round_up((int64_t)tn_tiles * splits + 7, 8);
         const unsigned nt_blocks = (unsigned)round_up((int64_t)nt_cols * ceil_div(max_rows, 128) + 7, 8);
         hipLaunchKernelGGL(gemm_tn_nt_kernel, dim3(tn_blocks + nt_blocks), dim3(256), 0, s, t, a, tn_blocks, tn_tiles, nt_cols);
-    } else if (max_rows >= TN_TALL_MIN_ROWS) {
-        static const hipError_t ready = hipFuncSetAttribute(reinterpret_cast<const void *>(&gemm_tn_tall_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)TN_TALL_LDS_BYTES);
-        CR_HIP_CHECK(ready);
+    } else if (max_rows >= TN_TALL_MIN_ROWS && tn_tall_ready()) {
         hipLaunchKernelGGL(gemm_tn_tall_kernel, tn_grid, dim3(512), TN_TALL_LDS_BYTES, s, t);
     } else {
         hipLaunchKernelGGL(gemm_tn_kernel, tn_grid, dim3(256), 0, s, t);

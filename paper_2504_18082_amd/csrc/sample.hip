@@ -2320,16 +2320,13 @@ struct SamplePlan {
     size_t bytes;
 };
 
-// the hop kernels' LDS, more than a launch gets without asking
 static bool hop_lds_ready()
 {
-    static const bool ready = [] {
-        const int most = (int)(T_LDS_BYTES > DEDUP_LDS_BYTES ? T_LDS_BYTES : DEDUP_LDS_BYTES);
-        return hipFuncSetAttribute(reinterpret_cast<const void *>(&hop_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, most) == hipSuccess &&
-               hipFuncSetAttribute(reinterpret_cast<const void *>(&hop_first_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)DEDUP_LDS_BYTES) == hipSuccess &&
-               hipFuncSetAttribute(reinterpret_cast<const void *>(&hop_transpose_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)T_LDS_BYTES) == hipSuccess;
-    }();
-    return ready;
+    static PerDevice hop, first, transpose;
+    constexpr size_t most = T_LDS_BYTES > DEDUP_LDS_BYTES ? T_LDS_BYTES : DEDUP_LDS_BYTES;
+    return lds_opt_in(hop, reinterpret_cast<const void *>(&hop_kernel), most) &&
+           lds_opt_in(first, reinterpret_cast<const void *>(&hop_first_kernel), DEDUP_LDS_BYTES) &&
+           lds_opt_in(transpose, reinterpret_cast<const void *>(&hop_transpose_kernel), T_LDS_BYTES);
 }
 
 static cr_status make_plan(const cr_sample_cfg *cfg, int64_t n_nodes, int32_t batch_size, int32_t n_batches,
