@@ -804,7 +804,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
     else nt_stream_run<16>(a, stream_lds);
 }
 
-constexpr int NT_WIDE_MIN_ROWS = 16384;   // below this the 256-row workgroups leave most compute units idle
+// The streaming and the wide kernel: below this their 64- and 128-row tiles leave compute units idle that the tiled kernel's
+// 128 x 64 tiles fill.  K = 256 (streaming): 6.7 against 8.7 us at 8192 rows, 7.8 against 9.5 at 12288; K = 512 (wide) 9.0
+// against 13.3 and 11.3 against 13.6, 14.4 at 16384; K = 1216 16.4 against 26.1 and 23.3 against 28.1, 29.5 at 16384.
+constexpr int NT_WIDE_MIN_ROWS = 16384;
 
 constexpr int NT_SMALL_ROWS = 2048;    // blocks of at most this many rows (by capacity) take the kernel above
 

@@ -650,10 +650,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 // Weighted sampling (0.5 < p < 1) takes the same passes with single-precision keys: approx_clock(r) * m_class, compared
 // through their bit patterns (all positive).  They decide only WHICH slots are kept (the output is in slot order), so the
 // result is exact whenever no key lies within its error bound of T; that is checked per row, and a row that fails is redone
-// with the exact integer keys.  (By reading some 8000 instructions for its wave, ten passes' worth, and so a launch's tail:
-// with T left wherever the search ended a reddit-like group's selection took 223 us, with T moved off the keys 193.)  The bound |approx_clock(r) * 2^24 - E(r)| <= CLOCK_ERR_ABS + CLOCK_ERR_REL * E(r) (E in its
-// Q24 units) holds with a factor of two to spare for every one of the 2^32 words: cr_selftest_clock_approximation
-// measures it on the device.
+// with the exact integer keys.  A redone row costs its wave some 8000 instructions (counted in the code, not measured), as much
+// as ten passes, and so a launch its tail: with T left wherever the search ended a reddit-like group's selection took 223 us,
+// with T moved off the keys 193.
+// The error bound: |approx_clock(r) * 2^24 - E(r)| <= CLOCK_ERR_ABS + CLOCK_ERR_REL * E(r), E in its Q24 units, for every one of
+// the 2^32 words, with a factor of two to spare; cr_selftest_clock_approximation measures it on the device.
 constexpr float CLOCK_ERR_ABS = 8.0f;             // Q24 units
 constexpr float CLOCK_ERR_REL = 0x1p-17f;       // (measured: 3 units / 2^-19)
 
