@@ -640,11 +640,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 //                  kept and the pool is the inter-community slots with m = fanout - n_in (0 in strict mode).
 // The kept slots are those below a bound T with exactly m words of the pool below it.  T is found by search: it is moved
 // inside a bracket to where evenly spread words would put it, and the words below it are counted per row with four ballots
-// and population counts under the row's mask of lanes (about 40 instructions a step, no LDS; 3 to 4 steps a row, 5 to 6 for
-// the slowest row of a pass).  The kernel is bound by vector instruction issue; ranking every slot against a list of its
-// row's candidates in LDS, which this replaces, took about 400 instructions a pass against 230.  Selection of a
-// products-like group of 32 batches (uniform, three hops): 792 -> 630 us; of a papers-like one 910 -> 804 us; weighted, a
-// reddit-like group of 8: 222 -> 193 us.  A row without such a bound in SEARCH_STEPS steps (equal words at the boundary) is
+// and population counts under the row's mask of lanes (about 40 instructions a step, no LDS; simulated on random words: 3 to 4
+// steps a row, 5 to 6 for the slowest row of a pass).  The kernel is bound by vector instruction issue; ranking every slot
+// against a list of its row's candidates in LDS, which this replaces, took 426 M vector instructions in the input-side hop of a
+// products-like group of 32 batches against 312 M.  Selection of that group (uniform, three hops): 792 -> 630 us; of a
+// papers-like one 910 -> 804 us; weighted, a reddit-like group of 8: 222 -> 193 us.  A row without such a bound in SEARCH_STEPS steps (equal words at the boundary) is
 // redone with (word, slot) pairs compared in full, so the result is exact in every case.
 //
 // Weighted sampling (0.5 < p < 1) takes the same passes with single-precision keys: approx_clock(r) * m_class, compared
