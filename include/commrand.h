@@ -234,9 +234,10 @@ typedef struct {
                                   was needed; every access stays inside the arrays.  The workspace is sized as without the
                                   flag. */
 
-#define CR_SAMPLE_EXACT_RANKING 64u /* verification aid: neighbour selection without its pre-filter thresholds, every row ranked on
-                                  full (key, slot) pairs -- the path that otherwise only serves the rare rows whose threshold
-                                  let too few slots through or whose boundary keys are equal.  Same results, slower. */
+#define CR_SAMPLE_EXACT_RANKING 64u /* verification aid: neighbour selection without its searched bounds and pre-filter thresholds, every
+                                  row ranked on full (key, slot) pairs -- the path that otherwise only serves the rare rows for
+                                  which no bound is found, whose threshold let too few slots through or whose boundary keys are
+                                  equal.  Same results, slower. */
 
 #define CR_SAMPLE_ROW_ORDER 16u /* fill the row_order array of every layer whose block set carries one (the workspace is
                                   then larger: set the flag for cr_sample_blocks_workspace_bytes too) */
@@ -270,7 +271,7 @@ cr_status cr_sample_blocks_workspace_bytes(const cr_sample_cfg *cfg, int64_t n_n
 #define CR_DEDUP_DIRECT 0
 #define CR_DEDUP_HASH 1
 /* Self-test of the weighted neighbour selection (Section 4.2 with 0.5 < p < 1; exponential-clock keys): the selection
- * ranks single-precision keys first and accepts a row only if its result provably equals the one of the exact integer
+ * compares single-precision keys first and accepts a row only if its result provably equals the one of the exact integer
  * keys, which rests on a bound on the error of the single-precision clock.  This call measures that error over all 2^32
  * random words on the device.  result: device float[4] (16-byte aligned), written asynchronously on `stream`:
  * [0] largest |error| in units of 2^-24 over the words of the upper half (clocks below 1), [1] largest relative error
@@ -484,7 +485,7 @@ cr_status cr_sage_linear_bwd_input(const cr_sage_layer *layer, const int32_t *hd
                                    void *stream);
 
 /* Backward pass of one whole GraphSAGE-mean layer above the input layer (Eq. 1, differentiated) in two launches
- * instead of four (three for capacities of 16384 rows and more, where the two products run by themselves).  Same results, bit for bit, as
+ * instead of four.  Same results, bit for bit, as
  *   cr_sage_linear_bwd(layer, header of batch g, blocks->cap_dst, h_self, agg, ld_in, dz_bf16, lr, weight_decay,
  *                      NULL, NULL, d_in_bf16, dW_out, db_out, ws, ws_bytes)
  * followed by

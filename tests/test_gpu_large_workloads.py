@@ -7,7 +7,8 @@ group-wide community order):
   products-like : 2.45 M nodes, ~124 M adjacency entries, 400-byte float rows (not 128-byte aligned), 5000 communities
   papers-like   : the FULL shape, 111 M nodes, ~3.2 G adjacency entries (offsets beyond 2^31), 256-byte bf16 rows,
                   100,000 communities, 172 classes; the graph is too large for the direct-address de-duplication
-                  table, so the open-addressing table is the one that runs
+                  table, so a hop that needs a table in memory -- the input-side one, where its frontier is
+                  de-duplicated -- takes the open-addressing one (the hops above it are de-duplicated on chip)
 
 The workloads are generated on the GPU (set-up) and the graph arrays are copied to the host for the oracle.  Root
 partitioning is compared in full; two batches of the group are compared with the oracle in full (every array of every

@@ -90,7 +90,8 @@ def test_tiny_group_of_batches(torch_mod, tiny_workload, p, strict):
 
 @pytest.mark.parametrize("p,hash_dedup", [(0.5, False), (0.9, False), (1.0, False), (0.5, True), (1.0, True)])
 def test_arxiv_three_layers(torch_mod, arxiv_workload, p, hash_dedup):
-    # both frontier de-duplication tables: direct-address (default at this size) and open addressing
+    # both frontier de-duplication tables: direct-address (the input-side hop at this size; the hops above it go without a table) and
+    # open addressing (every hop)
     w = arxiv_workload
     dg = DeviceGraph(torch_mod, w.graph, w.cfg.n_comm)
     perm = oracle.build_batches(oracle.RAND, 1, 3, 1, w.train_ids, w.comm, w.cfg.n_comm)
