@@ -139,6 +139,20 @@ __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi)
 __device__ __forceinline__ uint16_t f32_to_bf16(float f) { return (uint16_t)(pack_bf16x2(f, 0.f) & 0xFFFFu); }
 __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_float((uint32_t)h << 16); }
 
+// Stores a result that the launch does not read again, marked to leave the caches early.  The L2s are written back when a
+// launch ends (they are not coherent among the XCDs); what the stores have sent out by then is not waited for.
+template <typename T>
+__device__ __forceinline__ void store_out(T *p, const T &x)
+{
+    static_assert(sizeof(T) == 2 || sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "one store");
+    typedef uint32_t u32x2_t __attribute__((ext_vector_type(2)));
+    typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+    if constexpr (sizeof(T) == 2) __builtin_nontemporal_store(__builtin_bit_cast(uint16_t, x), reinterpret_cast<uint16_t *>(p));
+    else if constexpr (sizeof(T) == 4) __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, x), reinterpret_cast<uint32_t *>(p));
+    else if constexpr (sizeof(T) == 8) __builtin_nontemporal_store(__builtin_bit_cast(u32x2_t, x), reinterpret_cast<u32x2_t *>(p));
+    else __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, x), reinterpret_cast<u32x4_t *>(p));
+}
+
 // Block ids are dealt round-robin to the 8 XCDs, each with its own L2.  Give every XCD one
 // contiguous range of logical tiles so that neighbouring tiles share a cache.
 __device__ __forceinline__ uint32_t xcd_remap(uint32_t bid, uint32_t nblocks)

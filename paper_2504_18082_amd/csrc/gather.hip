@@ -43,7 +43,8 @@ template <> struct Vec16<uint16_t> {
     }
 };
 
-template <int N>
+// STREAM: with store_out
+template <bool STREAM, int N>
 __device__ __forceinline__ void store_bf16_row(uint16_t *dst, const float (&v)[N], int col, int F)
 {
     // dst points at column `col` of a zero-padded bf16 row; columns >= F are written as zero
@@ -54,9 +55,13 @@ __device__ __forceinline__ void store_bf16_row(uint16_t *dst, const float (&v)[N
         packed[i / 2] = (col + i + 1 < F) ? both : ((col + i < F) ? (both & 0xFFFFu) : 0u);
     }
     if constexpr (N == 4) {
-        *reinterpret_cast<uint2 *>(dst) = make_uint2(packed[0], packed[1]);
+        const uint2 w = make_uint2(packed[0], packed[1]);
+        if constexpr (STREAM) store_out(reinterpret_cast<uint2 *>(dst), w);
+        else *reinterpret_cast<uint2 *>(dst) = w;
     } else {
-        *reinterpret_cast<uint4 *>(dst) = make_uint4(packed[0], packed[1], packed[2], packed[3]);
+        const uint4 w = make_uint4(packed[0], packed[1], packed[2], packed[3]);
+        if constexpr (STREAM) store_out(reinterpret_cast<uint4 *>(dst), w);
+        else *reinterpret_cast<uint4 *>(dst) = w;
     }
 }
 
@@ -100,7 +105,9 @@ __global__ __launch_bounds__(256) void gather_mean_fwd_kernel(
     GroupInfo grp = GroupInfo{0, 0, 0, 0, 0, 0})
 {
     constexpr int VEC = Vec16<T>::N;
-    constexpr int U = NCHUNK == 1 ? 8 : (NCHUNK <= 3 ? 4 : 2);   // independent row loads in flight per lane
+    // independent row loads in flight per lane: five go into the fanouts in use (5, 10, 15, 25) without a rest, and fewer rows in
+    // flight leave more of what neighbouring rows share in the L2s (see launch_fwd_group)
+    constexpr int U = NCHUNK == 1 ? 5 : (NCHUNK <= 3 ? 4 : 2);
     constexpr int GPB = 256 / LPR;                                // groups (rows in progress) per workgroup
     const int n_dst = GROUPED ? min(order[(int64_t)grp.n_batches * grp.cap_dst], grp.n_batches * grp.cap_dst) : hdr[CR_HDR_N_DST];
     const int n_src = GROUPED ? grp.cap_src : hdr[CR_HDR_N_SRC];
@@ -254,7 +261,7 @@ __global__ __launch_bounds__(256) void gather_mean_fwd_kernel(
                         if (col + i < F) o[i] = acc[c][i];
                 }
             }
-            if (agg_bf16 && col < wcols) store_bf16_row<VEC>(agg_bf16 + (int64_t)out0 * ld_bf16 + col, acc[c], col, F);
+            if (agg_bf16 && col < wcols) store_bf16_row<GROUPED>(agg_bf16 + (int64_t)out0 * ld_bf16 + col, acc[c], col, F);
         }
 
         if (self_bf16) {
@@ -267,7 +274,7 @@ __global__ __launch_bounds__(256) void gather_mean_fwd_kernel(
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) v[i] = 0.f;
                     if (col < F) Vec16<T>::load(p + col, v);
-                    store_bf16_row<VEC>(self_bf16 + (int64_t)out0 * ld_bf16 + col, v, col, F);
+                    store_bf16_row<GROUPED>(self_bf16 + (int64_t)out0 * ld_bf16 + col, v, col, F);
                 }
             }
         }
@@ -295,6 +302,13 @@ static void launch_fwd(int cap_dst, const int32_t *hdr, const int32_t *indptr, c
                            GcnFwd{nullptr, nullptr, nullptr, nullptr}, order);
 }
 
+// What bounds the grouped gather is what the L2s miss: a random row costs the same from the memory-side cache (7.0 TB/s for rows
+// alone) as nearly from HBM (6.1), against 23 TB/s from the L2s, so what keeps shared rows in the L2s decides.  The results
+// are stored with store_out: 1 GB of them per group of 32 would push table rows out (papers-like table of 2.8 GB, 32 batches,
+// 1180 -> 1127 us; reddit-like, 16 batches, 928 -> 912; marking the table's rows that way instead: 1571 and 1790).  Then
+// five loads in flight instead of eight: 1121 and 883 (products-like, 32 batches: 1865 -> 1795 -> 1608; 3, 4, 6 in flight: 1651,
+// 1761, 1820), 1024 workgroups: 768 take 3-11 % longer, 2048 6-20 %.  The own row requested in front of the edges instead of
+// behind them: 3 % longer.
 constexpr int GROUP_PANEL_BYTES = 512;             // column panel of the grouped gather
 constexpr int GROUP_PANEL_MIN_ROW_BYTES = 1024;    // rows wider than this are gathered in panels
 
@@ -503,7 +517,7 @@ __device__ __forceinline__ void gather_mean_bwd_body(
                     }
                 }
             }
-            if (d_src_bf16 && col < ld_bf16) store_bf16_row<VEC>(d_src_bf16 + (int64_t)s * ld_bf16 + col, acc[c], col, F);
+            if (d_src_bf16 && col < ld_bf16) store_bf16_row<false>(d_src_bf16 + (int64_t)s * ld_bf16 + col, acc[c], col, F);
         }
 
         b0 = b1; e0 = e1; v0 = v1; w0 = w1;
