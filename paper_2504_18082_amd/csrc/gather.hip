@@ -517,7 +517,8 @@ __device__ __forceinline__ void gather_mean_bwd_body(
                     }
                 }
             }
-            if (d_src_bf16 && col < ld_bf16) store_bf16_row<false>(d_src_bf16 + (int64_t)s * ld_bf16 + col, acc[c], col, F);
+            // (STREAM: 45.3 -> 44.8 us for a products-like layer, 47.7 -> 47.1 for GCN's on the arxiv-like graph)
+            if (d_src_bf16 && col < ld_bf16) store_bf16_row<true>(d_src_bf16 + (int64_t)s * ld_bf16 + col, acc[c], col, F);
         }
 
         b0 = b1; e0 = e1; v0 = v1; w0 = w1;

@@ -668,7 +668,7 @@ __device__ __forceinline__ void nt_stream_body(const NtArgs &a, const int M, uin
         const float v2 = at_least(acc[rb][cb][grp * 4 + 2], floor_v), v3 = at_least(acc[rb][cb][grp * 4 + 3], floor_v);
         *reinterpret_cast<uint2 *>(&ob[(rb * 32 + lr) * STREAM_OROW + n]) = make_uint2(pack_bf16x2(v0, v1), pack_bf16x2(v2, v3));
     };
-    // the patch leaves as 128-byte row pieces
+    // the patch leaves as 128-byte row pieces (store_out: 61 K rows forward, their weight gradient and step 44.4 -> 42.9 us)
     auto flush = [&](int t) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         const int m0 = tile_m0(t);
@@ -676,7 +676,7 @@ __device__ __forceinline__ void nt_stream_body(const NtArgs &a, const int M, uin
         for (int it = 0; it < 8; ++it) {
             const int c = it * 64 + lane, row = c >> 3, c8 = (c & 7) * 8;
             const u32x4v x = *reinterpret_cast<const u32x4v *>(&ob[row * STREAM_OROW + c8]);
-            if (FULL || m0 + row < M) *reinterpret_cast<u32x4v *>(a.Cb + (int64_t)(m0 + row) * a.ldcb + 64 * wave + c8) = x;
+            if (FULL || m0 + row < M) store_out(reinterpret_cast<u32x4v *>(a.Cb + (int64_t)(m0 + row) * a.ldcb + 64 * wave + c8), x);
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the patch is rewritten for the next tile
     };
@@ -1027,6 +1027,7 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
             }
     }
 
+    // (store_out: the reduction reads a split's sums on every XCD.  The same pass 44.4 -> 42.8 us)
     float *P = a.partial + (int64_t)split * (a.K2 + 1) * a.N;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
@@ -1037,7 +1038,7 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
                 const int kl = wk * 64 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                if (kl < k_valid && n < a.N) P[(int64_t)(k0 + kl) * a.N + n] = acc[i][j][r];
+                if (kl < k_valid && n < a.N) store_out(P + (int64_t)(k0 + kl) * a.N + n, acc[i][j][r]);
             }
         }
     }
