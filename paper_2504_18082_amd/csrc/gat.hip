@@ -52,24 +52,46 @@ __device__ __forceinline__ void store_bf16x8(uint16_t *p, const float (&v)[8])
     *reinterpret_cast<uint4 *>(p) = make_uint4(w[0], w[1], w[2], w[3]);
 }
 
-// sum over the LH lanes of a head (LH a power of two; every lane of the head ends up with the total)
-__device__ __forceinline__ float head_sum(float x, int LH)
+// The partner's x in step STEP (0..3) of a reduction over the lanes of a head: a lane of the other half of its group of 2, 4, 8 or
+// 16 lanes, whose halves hold the same value in all of their lanes by then.  These are operand modifiers (quad permutes; the two
+// mirrors reach a lane of the right half), where a shuffle is an LDS access and its latency; the reductions are chains of them.
+// With this and rows kept as they were loaded until they are used, 131 K source rows of 256 columns, 4 heads, 275 K edges:
+// source side of the backward pass 68 -> 62.5 us, destination side 36 -> 31.3, aggregation 32.5 -> 31.3 (it and the destination
+// side read 141 MB of rows that the L2s miss: 24 us at what the memory-side cache delivers).
+template <int STEP>
+__device__ __forceinline__ float lane_across(float x)
 {
-    for (int off = 1; off < LH; off <<= 1) x += __shfl_xor(x, off);
-    return x;
+    constexpr int CTRL = STEP == 0 ? 0xB1 : (STEP == 1 ? 0x4E : (STEP == 2 ? 0x141 : 0x140));    // quad [1 0 3 2], quad [2 3 0 1], half mirror, mirror
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, true));
 }
 
-// the same for N independent values at once: the N reductions advance together, one exchange latency per step
+// op over the LH lanes of a head for N independent values (LH a power of two; every lane of the head ends up with the result)
+template <int N, typename Op>
+__device__ __forceinline__ void head_reduce(float (&x)[N], int LH, Op op)
+{
+    auto step = [&](auto from) {
+#pragma unroll
+        for (int k = 0; k < N; ++k) x[k] = op(x[k], from(x[k]));
+    };
+    if (LH > 1) step([](float v) { return lane_across<0>(v); });
+    if (LH > 2) step([](float v) { return lane_across<1>(v); });
+    if (LH > 4) step([](float v) { return lane_across<2>(v); });
+    if (LH > 8) step([](float v) { return lane_across<3>(v); });
+    if (LH > 16) step([](float v) { return __shfl_xor(v, 16); });
+    if (LH > 32) step([](float v) { return __shfl_xor(v, 32); });
+}
+
 template <int N>
 __device__ __forceinline__ void head_sum_n(float (&x)[N], int LH)
 {
-    for (int off = 1; off < LH; off <<= 1) {
-        float y[N];
-#pragma unroll
-        for (int k = 0; k < N; ++k) y[k] = __shfl_xor(x[k], off);
-#pragma unroll
-        for (int k = 0; k < N; ++k) x[k] += y[k];
-    }
+    head_reduce<N>(x, LH, [](float a, float b) { return a + b; });
+}
+
+__device__ __forceinline__ float head_sum(float x, int LH)
+{
+    float v[1] = {x};
+    head_sum_n<1>(v, LH);
+    return v[0];
 }
 
 __device__ __forceinline__ float dot8(const float (&a)[8], const float (&b)[8])
@@ -163,7 +185,7 @@ __global__ __launch_bounds__(256) void gat_scores_kernel(const int32_t *__restri
         al[i] = li.live ? attn[li.colc + i] : 0.f;
         ar[i] = li.live ? attn[s.ld + li.colc + i] : 0.f;
     }
-    constexpr int R = 4;                                     // rows in flight per group
+    constexpr int R = 8;
     for (int u0 = (int)blockIdx.x * GPB * R + li.grp; u0 < n_src; u0 += (int)gridDim.x * GPB * R) {
         float v[R][8];
 #pragma unroll
@@ -197,8 +219,42 @@ __global__ __launch_bounds__(256) void gat_scores_kernel(const int32_t *__restri
 // ---------------------------------------------------------------------------------------------------------------
 __device__ __forceinline__ float head_max(float x, int LH)
 {
-    for (int off = 1; off < LH; off <<= 1) x = fmaxf(x, __shfl_xor(x, off));
-    return x;
+    float v[1] = {x};
+    head_reduce<1>(v, LH, [](float a, float b) { return fmaxf(a, b); });
+    return v[0];
+}
+
+// el[u,h] of a row's edges for one head, every LH-th edge per lane, four look-ups in flight; done(j, el) is called for the edges
+// b + sub, b + sub + LH, .. below e in order
+template <typename Done>
+__device__ __forceinline__ void edge_scores(const int32_t *__restrict__ indices, const float *__restrict__ el, const GatShape &s, int h, int sub,
+                                            int b, int e, Done &&done)
+{
+    constexpr int E = 4;
+    for (int j0 = b + sub; j0 < e; j0 += E * s.LH) {
+        int u[E];
+        float x[E];
+#pragma unroll
+        for (int q = 0; q < E; ++q) u[q] = indices[min(j0 + q * s.LH, e - 1)];
+#pragma unroll
+        for (int q = 0; q < E; ++q) x[q] = el[(int64_t)u[q] * s.heads + h];
+#pragma unroll
+        for (int q = 0; q < E; ++q)
+            if (j0 + q * s.LH < e) done(j0 + q * s.LH, x[q]);
+    }
+}
+
+// this lane's 16 bytes of the projected rows of edges j .. j + U of a row with the edges b .. e (the last edge's row again past
+// the end, row 0 for a row without edges); zc = the lane's columns of row 0
+template <int U>
+__device__ __forceinline__ void fetch_edge_rows(const int32_t *__restrict__ indices, int j, int b, int e, const uint16_t *__restrict__ zc,
+                                                int ld, uint4 (&r)[U])
+{
+    int u[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) u[k] = indices[max(min(j + k, e - 1), 0)];
+#pragma unroll
+    for (int k = 0; k < U; ++k) r[k] = *reinterpret_cast<const uint4 *>(zc + (int64_t)(e > b ? u[k] : 0) * ld);
 }
 
 template <int LPR>
@@ -222,13 +278,16 @@ __global__ __launch_bounds__(256) void gat_aggregate_fwd_kernel(const int32_t *_
     for (int v = (int)blockIdx.x * GPB + li.grp; v < n_dst; v += (int)gridDim.x * GPB) {
         const int b = indptr[v], e = min(indptr[v + 1], b + s.max_deg);
         const float erv = er[(int64_t)v * s.heads + li.h];
+        // the first U rows travel while the scores are worked out
+        uint4 r[U];
+        fetch_edge_rows<U>(indices, b, b, e, z + li.colc, s.ld, r);
         float mx = -INFINITY;
-        for (int j = b + sub; j < e; j += s.LH) {
-            float x = el[(int64_t)indices[j] * s.heads + li.h] + erv;
+        edge_scores(indices, el, s, li.h, sub, b, e, [&](int j, float x0) {
+            float x = x0 + erv;
             x = x > 0.f ? x : s.slope * x;
             gw[(j - b) * s.heads] = x;
             mx = fmaxf(mx, x);
-        }
+        });
         mx = head_max(mx, s.LH);
         float sum = 0.f;
         for (int j = b + sub; j < e; j += s.LH) {
@@ -241,20 +300,16 @@ __global__ __launch_bounds__(256) void gat_aggregate_fwd_kernel(const int32_t *_
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the head's lanes now read each other's weights
         float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
         for (int j = b; j < e; j += U) {
-            int u[U];
-            float w[U], r[U][8];
-#pragma unroll
-            for (int k = 0; k < U; ++k) u[k] = indices[min(j + k, e - 1)];
+            if (j > b) fetch_edge_rows<U>(indices, j, b, e, z + li.colc, s.ld, r);
 #pragma unroll
             for (int k = 0; k < U; ++k) {
-                load_bf16x8(z + (int64_t)u[k] * s.ld + li.colc, li.mask, r[k]);
                 const float wk = gw[(min(j + k, e - 1) - b) * s.heads];
-                w[k] = j + k < e ? wk : 0.f;
+                const float w = j + k < e ? wk : 0.f;
+                float x[8];
+                unpack_bf16x8(r[k], li.mask, x);
+#pragma unroll
+                for (int i = 0; i < 8; ++i) acc[i] += w * x[i];
             }
-#pragma unroll
-            for (int k = 0; k < U; ++k)
-#pragma unroll
-                for (int i = 0; i < 8; ++i) acc[i] += w[k] * r[k][i];
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the slice is reused by the group's next row
         float o[8];
@@ -333,39 +388,36 @@ __global__ __launch_bounds__(256) void gat_bwd_dst_kernel(const int32_t *__restr
         for (int i = 0; i < 8; ++i) dbp[i] += g[i];
         const int b = indptr[v], e = min(indptr[v + 1], b + s.max_deg);
         const float4 st = stat[(int64_t)v * s.heads + li.h];
+        uint4 r[U];
+        fetch_edge_rows<U>(indices, b, b, e, z + li.colc, s.ld, r);
         // alpha and alpha * lrelu' of the row's edges, every LH-th edge per lane of the head
         float Cq = 0.f;
-        for (int j = b + sub; j < e; j += s.LH) {
-            const float x = el[(int64_t)indices[j] * s.heads + li.h] + st.x;
+        edge_scores(indices, el, s, li.h, sub, b, e, [&](int j, float x0) {
+            const float x = x0 + st.x;
             const bool pos = x > 0.f;
             const float a = expf((pos ? x : s.slope * x) - st.y) * st.z;
             const float alp = pos ? a : s.slope * a;
             gw[(j - b) * s.heads] = make_float2(a, alp);
             Cq += alp;
-        }
+        });
         Cq = head_sum(Cq, s.LH);
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
         float A = 0.f, Bq = 0.f;
         for (int j = b; j < e; j += U) {
-            int u[U];
-            float2 w[U];
-            float r[U][8];
-#pragma unroll
-            for (int k = 0; k < U; ++k) u[k] = indices[min(j + k, e - 1)];
-#pragma unroll
-            for (int k = 0; k < U; ++k) {
-                load_bf16x8(z + (int64_t)u[k] * s.ld + li.colc, li.mask, r[k]);
-                const float2 wk = gw[(min(j + k, e - 1) - b) * s.heads];
-                w[k] = j + k < e ? wk : make_float2(0.f, 0.f);
-            }
+            if (j > b) fetch_edge_rows<U>(indices, j, b, e, z + li.colc, s.ld, r);
             float da[U];
 #pragma unroll
-            for (int k = 0; k < U; ++k) da[k] = dot8(g, r[k]);
+            for (int k = 0; k < U; ++k) {
+                float x[8];
+                unpack_bf16x8(r[k], li.mask, x);
+                da[k] = dot8(g, x);
+            }
             head_sum_n<U>(da, s.LH);
 #pragma unroll
             for (int k = 0; k < U; ++k) {
-                A += w[k].x * da[k];
-                Bq += w[k].y * da[k];
+                const float2 wk = gw[(min(j + k, e - 1) - b) * s.heads];
+                A += (j + k < e ? wk.x : 0.f) * da[k];
+                Bq += (j + k < e ? wk.y : 0.f) * da[k];
             }
         }
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -482,40 +534,39 @@ __global__ __launch_bounds__(256) void gat_bwd_src_kernel(const int32_t *__restr
 
 // ---------------------------------------------------------------------------------------------------------------
 // Sums the workgroups' partial column sums (fixed order) and takes the SGD step on a_l, a_r (with weight decay) and
-// the bias (without, as for the dense layers' bias).  blockIdx.y = 0: a_l, 1: a_r, 2: bias; 64 columns per workgroup.
+// the bias (without, as for the dense layers' bias).  blockIdx.y = 0: a_l, 1: a_r, 2: bias; 16 columns per workgroup, so that 48
+// workgroups share the 3 MB of partial sums of 256 columns (with 64 columns, 12 workgroups: 8.4 us against 5.0); thread t takes
+// column t % 16 of rows t / 16, + 64, .., sixteen loads in flight.
 // ---------------------------------------------------------------------------------------------------------------
+constexpr int PARAM_COLS = 16;
 __global__ __launch_bounds__(1024) void gat_param_step_kernel(const float *__restrict__ partial_al, const float *__restrict__ partial_ar,
                                                               const float *__restrict__ partial_db, int nb_src, int nb_dst, int ld, int HD,
                                                               float lr, float wd, float *__restrict__ attn, float *__restrict__ d_attn_out)
 {
-    __shared__ float red[16][64];
+    constexpr int LANES = 1024 / PARAM_COLS, DEPTH = 16;
+    __shared__ float red[LANES][PARAM_COLS];
     const int which = (int)blockIdx.y;
     const float *p = which == 0 ? partial_al : (which == 1 ? partial_ar : partial_db);
     const int nb = which == 2 ? nb_dst : nb_src;
-    const int lane = (int)(threadIdx.x & 63), wave = (int)(threadIdx.x >> 6);
-    const int c = (int)blockIdx.x * 64 + lane;
-    float s0 = 0.f, s1 = 0.f, s2 = 0.f, s3 = 0.f;          // wave w takes rows w, w + 16, ...; four loads in flight
-    if (c < ld) {
-        const float *q = p + c;
-        int r = wave;
-        for (; r + 48 < nb; r += 64) {
-            s0 += q[(int64_t)r * ld];
-            s1 += q[(int64_t)(r + 16) * ld];
-            s2 += q[(int64_t)(r + 32) * ld];
-            s3 += q[(int64_t)(r + 48) * ld];
-        }
-        for (; r < nb; r += 16) s0 += q[(int64_t)r * ld];
+    const int col = (int)(threadIdx.x % PARAM_COLS), first = (int)(threadIdx.x / PARAM_COLS);
+    const int c = (int)blockIdx.x * PARAM_COLS + col;          // (the widths are multiples of 64: every column exists)
+    const float w0 = attn[(int64_t)which * ld + c];
+    float s = 0.f;
+    for (int r0 = first; r0 < nb; r0 += LANES * DEPTH) {
+        float x[DEPTH];
+#pragma unroll
+        for (int k = 0; k < DEPTH; ++k) x[k] = p[(int64_t)min(r0 + k * LANES, nb - 1) * ld + c];
+#pragma unroll
+        for (int k = 0; k < DEPTH; ++k) s += r0 + k * LANES < nb ? x[k] : 0.f;
     }
-    red[wave][lane] = (s0 + s1) + (s2 + s3);
+    red[first][col] = s;
     __syncthreads();
-    if (wave != 0 || c >= HD) return;
+    if (first != 0 || c >= HD) return;
     float g = 0.f;
 #pragma unroll
-    for (int w = 0; w < 16; ++w) g += red[w][lane];
+    for (int w = 0; w < LANES; ++w) g += red[w][col];
     if (d_attn_out) d_attn_out[(int64_t)which * ld + c] = g;
-    float w = attn[(int64_t)which * ld + c];
-    w -= lr * (g + (which == 2 ? 0.f : wd * w));
-    attn[(int64_t)which * ld + c] = w;
+    attn[(int64_t)which * ld + c] = w0 - lr * (g + (which == 2 ? 0.f : wd * w0));
 }
 
 }  // namespace cr
@@ -647,7 +698,7 @@ extern "C" cr_status cr_gat_attention_fwd(const cr_block_set *blocks, int32_t g,
     const int32_t *hdr = blocks->hdr + (int64_t)g * CR_HDR_WORDS;
     const int32_t *indptr = blocks->indptr + (int64_t)g * (blocks->cap_dst + 1);
     const int32_t *indices = blocks->indices + (int64_t)g * blocks->cap_nnz;
-    GAT_DISPATCH(lpr, gat_scores_kernel, grid_for(ceil_div(blocks->cap_src, 4), lpr, 768), 0, hs, hdr, s, z_bf16, params->attn, el, er);
+    GAT_DISPATCH(lpr, gat_scores_kernel, grid_for(ceil_div(blocks->cap_src, 8), lpr, 1024), 0, hs, hdr, s, z_bf16, params->attn, el, er);
     GAT_DISPATCH(lpr, gat_aggregate_fwd_kernel, grid_for(blocks->cap_dst, lpr, GAT_MAX_BLOCKS), edge_lds_bytes(lpr, s.heads, s.max_deg, 1), hs, hdr, indptr, indices, s, z_bf16, params->attn, el, er,
                  relu ? 1 : 0, out, out_bf16, reinterpret_cast<float4 *>(stat));
     CR_LAUNCH_CHECK();
@@ -694,7 +745,7 @@ extern "C" cr_status cr_gat_attention_bwd(const cr_block_set *blocks, int32_t g,
                  reinterpret_cast<float4 *>(stat), w.g_b, w.d_er, w.partial_db);
     GAT_DISPATCH(lpr, gat_bwd_src_kernel, nb_src, 0, hs, hdr, t_indptr, t_indices, s, z_bf16, params->attn, el,
                  reinterpret_cast<const float4 *>(stat), w.g_b, w.d_er, dz_bf16, w.partial_al, w.partial_ar);
-    hipLaunchKernelGGL(gat_param_step_kernel, dim3((unsigned)(s.ld / 64), 3), dim3(1024), 0, hs, w.partial_al, w.partial_ar, w.partial_db,
+    hipLaunchKernelGGL(gat_param_step_kernel, dim3((unsigned)(s.ld / PARAM_COLS), 3), dim3(1024), 0, hs, w.partial_al, w.partial_ar, w.partial_db,
                        nb_src, nb_dst, s.ld, s.heads * s.D, lr, weight_decay, params->attn, d_attn_out);
     CR_LAUNCH_CHECK();
     return CR_OK;

@@ -284,3 +284,10 @@ def test_gat_forward_at_benchmark_size(arxiv_workload):
     ref = oracle_train_step_gat(w.graph, w.features, cfg.n_feat, w.labels, roots[pick], cfg.fanouts, p, seed, epoch, g, params, heads,
                                 0.0, 0.0)
     assert_close(logits[pick, :cfg.n_classes], ref["logits"], 2e-2, "logits of sampled roots")
+
+
+@pytest.mark.parametrize("heads,D,ld", [(4, 8, 64), (2, 128, 256), (1, 300, 320)])
+def test_gat_head_widths(tiny_workload, heads, D, ld):
+    """Heads of 1, 16 and 64 lanes (the cases above have 2, 4, 8 and 32): every step of the reductions over a head."""
+    test_gat_attention_fwd(tiny_workload, heads, D, ld, True)
+    test_gat_attention_bwd(tiny_workload, heads, D, ld, True)
