@@ -519,14 +519,16 @@ cr_status cr_softmax_xent(const int32_t *hdr, int32_t max_rows, const float *log
 /* The layer next to the loss and the loss in one call: cr_sage_linear_fwd(relu = 0, out = logits, out_bf16 = NULL)
  * followed by cr_softmax_xent(hdr, max_rows, logits, N_pad, n_classes, ..., d_logits = NULL, d_logits_bf16).  When the
  * layer has at most 64 outputs and the block at most 2048 rows (by max_rows) this is one launch: a workgroup of the
- * product holds whole rows of logits and finishes their loss terms in place; otherwise the separate kernels run.
+ * product holds whole rows of logits and finishes their loss terms in place; otherwise separate kernels run (two for at
+ * most 2048 rows: the loss rows' kernel takes the mean as well).
  * Logits are bit-identical to cr_sage_linear_fwd's; the loss terms may differ from cr_softmax_xent's in the last
  * bits (sums are associated differently), never from run to run.
  *   logits        : device float [max_rows][N_pad];  d_logits_bf16 : device bf16 [max_rows][N_pad]
  *   scratch       : device, CR_XENT_SCRATCH_BYTES; zero before the first call, and every call leaves it zero again;
- *                   calls that share a scratch must not overlap.  In the one-launch form the mean loss is the sum of
+ *                   calls that share a scratch must not overlap.  For at most 2048 rows the mean loss is the sum of
  *                   per-workgroup shares rounded to 2^-20 (a device-side integer accumulator: reproducible whatever the
- *                   order of arrival), NaN if a share is not finite
+ *                   order of arrival); in the one-launch form it is NaN if a share is not finite, in the two-launch form
+ *                   shares of 8 rows that are not finite or larger than 2^14 are added in double, in order of arrival
  * The remaining arguments as in the two calls. */
 #define CR_XENT_SCRATCH_BYTES 512
 cr_status cr_sage_linear_fwd_xent(const cr_sage_layer *layer, const int32_t *hdr, int32_t max_rows,

@@ -300,6 +300,42 @@ def test_linear_fwd_with_loss(torch_mod, M, F_in, Cn, cap_extra):
         assert np.all(scratch.cpu().numpy()[:8] == 0)            # the accumulator is back at zero
 
 
+@pytest.mark.parametrize("M,Cn,case", [(1000, 128, "small"), (2048, 257, "small"), (9, 129, "large"), (1024, 172, "large"), (17, 172, "nan"),
+                                       (8, 65, "inf")])
+def test_linear_fwd_with_loss_shares(torch_mod, M, Cn, case):
+    """The mean loss of the rows' kernel: logits are the bias (weights of zero), column counts at and around what a wave
+    holds in registers, losses that do not fit the fixed-point accumulator, and ones that are no numbers."""
+    torch = torch_mod
+    from paper_2504_18082_amd import binding as B
+    rng = np.random.default_rng(M + Cn)
+    b = rng.standard_normal(Cn).astype(np.float32) * (1e5 if case == "large" else 1.0)
+    b[3] = {"nan": np.nan, "inf": -np.inf}.get(case, b[3])
+    layer = B.SageLayer(np.zeros((2 * 32, Cn), dtype=np.float32), b)
+    layer.refresh()
+    labels = rng.integers(0, Cn, size=M).astype(np.int32)
+    labels[: M // 2] = 3
+    x = torch.zeros((M, 32), dtype=torch.int16, device="cuda")
+    d_labels, ids = torch.from_numpy(labels).cuda(), torch.arange(M, dtype=torch.int32, device="cuda")
+    scratch = torch.zeros(B.CR_XENT_SCRATCH_BYTES, dtype=torch.uint8, device="cuda")
+    hdr = hdr_for(torch, M)
+    f32 = lambda *s: torch.zeros(s, dtype=torch.float32, device="cuda")
+    got = []
+    for _ in range(2):
+        print(f"case loss shares M={M} classes={Cn} {case}", flush=True)
+        loss = f32(1)
+        B.cr_sage_linear_fwd_xent(layer, C.c_void_p(hdr.data_ptr()), M, x, x, 32, f32(M, layer.N_pad), Cn, d_labels, C.c_void_p(ids.data_ptr()),
+                                  loss, f32(M), torch.zeros((M, layer.N_pad), dtype=torch.int16, device="cuda"), scratch)
+        torch.cuda.synchronize()
+        assert np.all(scratch.cpu().numpy() == 0)
+        got.append(float(loss.cpu()[0]))
+    if case in ("nan", "inf"):
+        assert all(np.isnan(x) if case == "nan" else x == np.inf for x in got)
+        return
+    want, _ = oracle.softmax_xent(np.tile(b.astype(np.float64), (M, 1)), labels, n_classes=Cn)
+    assert got[0] == got[1] or case == "large"
+    assert all(abs(x - want) <= RTOL_F32 * max(1.0, abs(want)) for x in got)
+
+
 @pytest.mark.parametrize("n,Cn", [(256, 10), (1024, 40), (1000, 172), (1, 7), (3, 1)])
 def test_count_correct(torch_mod, n, Cn):
     """Integer result: the same float32 logits go to both sides, so the counts must agree exactly
