@@ -1184,6 +1184,8 @@ struct ScanArgs {
     int32_t fanout;
     int32_t *head_ids;            // mode 4, input-side block in global ids: takes the destination nodes too, or NULL
     int64_t head_stride;
+    int32_t *zero;                // [G][n_zero] words to clear for a later kernel of the hop, or NULL
+    int32_t n_zero;               // at most SCAN_THREADS
 };
 
 // out[0..n] = exclusive prefix sums of in[0..n) per batch (blockIdx.y).  A workgroup owns one tile of 256 x 16
@@ -1199,6 +1201,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_kernel(ScanArgs a)
     __shared__ int lds[17];
     const int g = blockIdx.y;
     int32_t *hdr = a.hdr + (int64_t)g * CR_HDR_WORDS;
+    if (a.zero && blockIdx.x == 0 && threadIdx.x < a.n_zero) a.zero[(int64_t)g * a.n_zero + threadIdx.x] = 0;
     const int n_dst = group_n_dst(a.prev_hdr, g, a.n_roots_total, a.batch_size);
     const int n = a.mode == 3 ? a.n_fixed : (a.mode == 2 ? hdr[CR_HDR_N_SRC] : n_dst);
     const int first = (int)blockIdx.x * SCAN_TILE;
@@ -1580,6 +1583,14 @@ struct DedupArgs {
     int64_t first_stride;
     int32_t *edge_rows;       // [G][cap_nnz] destination row of every edge, for the transpose in LDS, or NULL
     int64_t edge_rows_stride;
+    // hops in several parts (frontier in LDS); all NULL otherwise
+    int32_t *counters;        // [G][HOP_COUNTERS]: entries of every part's list, then of every source range's
+    uint2 *lists;             // [G] x list_stride: [parts][LIST_CAP] (id, position)
+    int32_t *t_lists;         // the same room, later: [t_parts][T_LIST] row << 14 | source in its range
+    int64_t list_stride;      // in 8-byte words
+    unsigned long long *seen_bits;    // [G][NUMBER_WORDS]: edges whose neighbour has appeared before
+    int32_t *new_count;       // [G][HOP_CHUNKS_MAX]: edges whose neighbour has not, per stretch of words
+    int32_t t_parts;          // source ranges of the transpose
 };
 
 // maps a thread to (row, j): gw lanes per row
@@ -1751,12 +1762,16 @@ __global__ __launch_bounds__(256) void t_rank_kernel(DedupArgs a)
 // ---------------------------------------------------------------------------------------------
 // Frontier of a hop in LDS.  The tables above live in memory, where an atomic of one XCD is resolved behind the caches
 // all XCDs share; insert / mark / assign / relabel / reset, the scans between them and the clearing of a table were 335 us of
-// a group of 32 products-like batches (second hop).  Here the ids of a hop (destination nodes and chosen neighbours) are split
-// into parts of about LIST_MEAN entries; a workgroup reads all of the batch's ids, keeps those of its part in an LDS list and
-// finds every id's first appearance with an LDS table.  What bounds it is asking every id once per part (a dozen
-// instructions each, and an L2 read), so the asking is kept to shifts and xors and the parts to 32.
-// Then one kernel numbers the first appearances (a bit per edge in LDS) and relabels, and one transposes the block, each source
-// range in its own workgroup.  A hop that is one part (the hop at the roots) does all three in one workgroup and launch.
+// a group of 32 products-like batches (second hop).  Here the ids of a hop (destination nodes and chosen neighbours) are dealt
+// to parts of at most LIST_MEAN entries on average, by a hash (hop_part_kernel); a workgroup takes a part's list into LDS and
+// finds every id's first appearance with an LDS table (hop_first_kernel).  hop_mark_kernel marks the first appearances, a bit per
+// edge, and counts them; hop_number_kernel numbers them, relabels the edges, and deals these to ranges of sources;
+// hop_transpose_kernel transposes the block, each range in its own workgroup.  Every id and edge is looked at once per
+// kernel.  (Before, every part's workgroup went over all ids of the batch, every range's over all edges, and every stretch of the
+// numbering over all edges in front of it, 12 to 20 instructions each time: 41 of 50 us of a part, 39 of 60 of a range of the
+// reddit-like input hop.  8 batches of it: 92 us in five launches, 178 in three then; 32 products-like batches,
+// second hop: 83, 91 then.)
+// A hop that is one part (the hop at the roots) does all of this in one workgroup and launch, without leaving LDS.
 // The chosen neighbours are stored as the block's edges are (row pointers are known before the selection); position n_dst + e
 // is that of edge e.  Order, labels and transposes are those of the tables, bit for bit.
 // ---------------------------------------------------------------------------------------------
@@ -1767,11 +1782,16 @@ constexpr int LIST_MEAN = 9216;                 // ids a part is sized for; the 
 constexpr int PART_TABLE = 16384;
 constexpr int PARTS_MAX = 32;
 constexpr int PARTS_MIN = 8;                    // (a group of 32 batches then fills the 256 compute units)
+constexpr int PART_PER = 8;                     // ids that a thread of hop_part_kernel deals
+constexpr int PART_CHUNK = PART_PER * HOP_THREADS;
+constexpr int HOP_CHUNKS_MAX = 32;              // stretches that marking and numbering cut a batch's edges into
 constexpr int NUMBER_WORDS = 5120;              // 64 edges each (a multiple of HOP_THREADS words)
 constexpr int T_SOURCES = 11264;                // sources of one transposed range (at least LIST_CAP)
 constexpr int T_LIST = 14336;                   // edges of one transposed range
 constexpr int T_MEAN = 9216;
 constexpr int T_PARTS_MAX = 40;
+constexpr int HOP_COUNTERS = 128;               // words per batch: PARTS_MAX, then T_PARTS_MAX of them are used
+static_assert(PARTS_MAX + T_PARTS_MAX <= HOP_COUNTERS, "a counter per list");
 constexpr int T_RANK_WORK = 1 << 18;            // most comparisons that the rows of a range are ranked with (2^19 and 2^20 measure the
                                                 // same; with 2^21 hops on skewed graphs take up to 2.8 times as long in all)
 constexpr size_t DEDUP_LDS_BYTES = (size_t)(2 * LIST_CAP + PART_TABLE) * 4;
@@ -1779,7 +1799,7 @@ constexpr size_t NUMBER_LDS_BYTES = (size_t)NUMBER_WORDS * 12;
 constexpr size_t T_LDS_BYTES = (size_t)(T_SOURCES + 1 + 2 * T_LIST + 32) * 4;
 static_assert(PARTS_MAX * LIST_MEAN <= NUMBER_WORDS * 64, "the numbering pass holds a bit per edge");
 static_assert(T_SOURCES <= (1 << 14) && T_SOURCES >= LIST_CAP, "a list entry holds the source in 14 bits; a hop of one part is one range");
-static_assert(DEDUP_LDS_BYTES + 256 <= 160 * 1024 && T_LDS_BYTES + 256 <= 160 * 1024, "LDS of a compute unit");
+static_assert(DEDUP_LDS_BYTES + 512 <= 160 * 1024 && T_LDS_BYTES + 512 <= 160 * 1024, "LDS of a compute unit");
 
 // a bijection of the 32-bit integers whose every output bit depends on every input bit (the finaliser of MurmurHash3)
 __device__ __forceinline__ uint32_t mix32(uint32_t h)
@@ -1789,9 +1809,8 @@ __device__ __forceinline__ uint32_t mix32(uint32_t h)
     return h ^ (h >> 16);
 }
 
-// Which of `parts` (a power of two, at most 32) parts an id belongs to: its bits folded onto five.  Every id of the hop
-// is asked once per part, and 32-bit products run at a quarter of the rate of shifts and xors on this chip: with mix32 here the
-// asking was 60 % of the kernel.  Ids that all fold onto one value are not lost, they overflow the part's list.
+// Which of `parts` (a power of two, at most 32) parts an id belongs to: its bits folded onto five (shifts and xors; 32-bit
+// products run at a quarter of their rate).  Ids that all fold onto one value are not lost, they overflow the part's list.
 __device__ __forceinline__ uint32_t id_part(uint32_t id, uint32_t parts)
 {
     const uint32_t x = id ^ (id >> 15);
@@ -1803,72 +1822,48 @@ struct HopShared {
     int scan[17];
 };
 
-// A workgroup goes over src[0..n) and appends (value - `minus`, index + `plus`) of the entries that `mine` accepts to
-// two LDS lists of `cap` entries; *count keeps counting past their end.  The loop is what a hop costs per part: the bounds
-// are checked in the last round only, and a wave takes its place in the lists once per U entries of every lane.
-template <int U, typename Mine>
-__device__ __forceinline__ void collect(const int32_t *src, int n, Mine &&mine, int minus, int plus, uint32_t *values, uint32_t *places, int cap, int *count)
+// element i of an array that every lane has the same address of (fewer than 2^30 elements): base in scalar registers, one 32-bit offset
+template <typename T>
+__device__ __forceinline__ T &at32(T *p, int i)
 {
-    const int tid = threadIdx.x, lane = lane_id();
-    auto round = [&](int i0, auto checked) {
-        constexpr bool CHECKED = decltype(checked)::value;
-        int32_t x[U];
-#pragma unroll
-        for (int k = 0; k < U; ++k) x[k] = src[CHECKED ? min(i0 + k * HOP_THREADS + tid, n - 1) : i0 + k * HOP_THREADS + tid];
-        bool take[U];
-        int total = 0;
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            take[k] = mine(x[k], !CHECKED || i0 + k * HOP_THREADS + tid < n);
-            total += __popcll(__ballot(take[k]));
-        }
-        if (total == 0) return;
-        int at = 0;
-        if (lane == 0) at = atomicAdd(count, total);
-        at = __builtin_amdgcn_readfirstlane(at);
-#pragma unroll
-        for (int k = 0; k < U; ++k) {
-            const uint64_t m = __ballot(take[k]);
-            if (take[k]) {
-                const int slot = lanes_below(m, at);
-                if (slot < cap) {
-                    values[slot] = (uint32_t)(x[k] - minus);
-                    places[slot] = (uint32_t)(i0 + k * HOP_THREADS + tid + plus);
-                }
-            }
-            at += __popcll(m);
-        }
-    };
-    int i0 = 0;
-    for (; i0 + U * HOP_THREADS <= n; i0 += U * HOP_THREADS) round(i0, std::false_type{});
-    if (i0 < n) round(i0, std::true_type{});
+    return *reinterpret_cast<T *>(reinterpret_cast<uintptr_t>(p) + (uint32_t)i * (uint32_t)sizeof(T));
 }
 
+__device__ __forceinline__ uint32_t hop_id(const int32_t *dst, const int32_t *sel, int n_dst, int i) { return (uint32_t)*(i < n_dst ? dst + i : sel + (i - n_dst)); }
+
 // first[e] = smallest position (destination rows first, then edges) at which edge e's neighbour appears, for the edges whose
-// neighbour belongs to this part
+// neighbour belongs to this part.  ONE: the hop is one part; `first` is then in LDS (in the table's room).
+template <bool ONE>
 __device__ __forceinline__ void hop_first(const DedupArgs &a, int g, int n_dst, int nnz, uint32_t part, uint32_t parts, uint32_t *lds, HopShared &sh)
 {
     uint32_t *lid = lds, *lpos = lds + LIST_CAP, *table = lds + 2 * LIST_CAP;
     const int tid = threadIdx.x;
     const int32_t *dst = a.dst_ids + (int64_t)g * a.dst_stride, *sel = a.sel + (int64_t)g * a.sel_stride;
-    int32_t *first = a.first + (int64_t)g * a.first_stride;
+    int32_t *first = ONE ? reinterpret_cast<int32_t *>(table) : a.first + (int64_t)g * a.first_stride;
     const int total = n_dst + nnz;
-    auto id_at = [&](int i) { return (uint32_t)(i < n_dst ? dst[i] : sel[i - n_dst]); };
-    for (int i = tid; i < PART_TABLE; i += HOP_THREADS) table[i] = ~0u;
-    if (tid == 0) { sh.count = 0; sh.overflow = 0; }
-    __syncthreads();
-    auto mine = [&](int32_t id, bool have) { return have && id_part((uint32_t)id, parts) == part; };
-    collect<4>(dst, n_dst, mine, 0, 0, lid, lpos, LIST_CAP, &sh.count);
-    collect<16>(sel, nnz, mine, 0, n_dst, lid, lpos, LIST_CAP, &sh.count);
-    __syncthreads();
-    const int count = sh.count;
-    if (count <= LIST_CAP) {
+    auto id_at = [&](int i) { return hop_id(dst, sel, n_dst, i); };
+    const int count = ONE ? total : a.counters[(int64_t)g * HOP_COUNTERS + part];
+    if (ONE || count <= LIST_CAP) {
+        const uint2 *list = ONE ? nullptr : a.lists + (int64_t)g * a.list_stride + (int64_t)part * LIST_CAP;
+        for (int i = tid; i < PART_TABLE; i += HOP_THREADS) table[i] = ~0u;
+        // (bounds are rounded up to whole rounds of the workgroup, so that a round's loads stand alone)
+        uint32_t pos[LIST_PER], is_first = 0;
+#pragma unroll
+        for (int k = 0; k < LIST_PER; ++k) {
+            const int i = tid + k * HOP_THREADS;
+            pos[k] = 0;
+            if (k * HOP_THREADS < count) {                     // (uniform)
+                const int ic = min(i, count - 1);
+                const uint2 x = ONE ? make_uint2(id_at(ic), (uint32_t)ic) : list[ic];
+                pos[k] = x.y;
+                lid[i] = x.x;
+                lpos[i] = x.y;
+            }
+        }
+        __syncthreads();
         // An id's entries agree on the one that got the table's slot first and leave the smallest position there.  A lane
         // goes through its entries on its own, so a wave takes as many rounds as its slowest lane has probes in all (~30),
         // not the longest probe of every entry in turn (~90).
-        uint32_t pos[LIST_PER], is_first = 0;
-#pragma unroll
-        for (int k = 0; k < LIST_PER; ++k) pos[k] = lpos[tid + k * HOP_THREADS];
         {
             int i = tid, k = 0;
             uint32_t id = lid[i], h = mix32(id), s = h & (PART_TABLE - 1);
@@ -1890,7 +1885,7 @@ __device__ __forceinline__ void hop_first(const DedupArgs &a, int g, int n_dst, 
                 }
             }
         }
-        __syncthreads();                                       // (every own position has been read)
+        __syncthreads();                                       // (every own position has been read; the table is done with)
 #pragma unroll
         for (int k = 0; k < LIST_PER; ++k)
             if (tid + k * HOP_THREADS < count && !((is_first >> k) & 1u)) atomicMin(&lpos[lid[tid + k * HOP_THREADS]], pos[k]);
@@ -1940,86 +1935,161 @@ __device__ __forceinline__ void hop_first(const DedupArgs &a, int g, int n_dst, 
     }
 }
 
-// Positions of the first appearances in the frontier, and the relabelled edges of one stretch of the block: the workgroup
-// marks the first appearances of all edges up to the end of its stretch (an edge's first appearance never lies behind
-// it), so the stretches need nothing from each other.  Returns the frontier's length (last stretch only).
-__device__ __forceinline__ int hop_number(const DedupArgs &a, int g, int n_dst, int nnz, int chunk, int chunks, uint32_t *lds, HopShared &sh)
+// Words [w0, w1) of 64 edges each: a bit for the edges whose neighbour appears for the first time (SEEN: for the others); returns
+// how many of the former this wave met.
+template <bool SEEN>
+__device__ __forceinline__ int mark_words(const int32_t *first, int n_dst, int nnz, int w0, int w1, unsigned long long *bits)
 {
-    unsigned long long *bits = reinterpret_cast<unsigned long long *>(lds);
-    int *pre = reinterpret_cast<int *>(lds + 2 * NUMBER_WORDS);
-    const int tid = threadIdx.x, lane = lane_id(), wave = tid / WAVE;
-    const int32_t *dst = a.dst_ids + (int64_t)g * a.dst_stride, *sel = a.sel + (int64_t)g * a.sel_stride;
-    const int32_t *first = a.first + (int64_t)g * a.first_stride;
-    int32_t *src = a.src_ids + (int64_t)g * a.src_stride, *indices = a.indices + (int64_t)g * a.indices_stride;
-    const int32_t *indptr = a.indptr + (int64_t)g * a.indptr_stride;
-    const int r0 = (int)((int64_t)n_dst * chunk / chunks), r1 = (int)((int64_t)n_dst * (chunk + 1) / chunks);
-    const int e0 = chunk == 0 ? 0 : indptr[r0], e1 = chunk == chunks - 1 ? nnz : indptr[r1];
-    const int w1 = (e1 + 63) / 64;
-    constexpr int U = 16, NW = HOP_THREADS / WAVE;
-    for (int w = wave; w < w1; w += U * NW) {
+    constexpr int U = 8, NW = HOP_THREADS / WAVE;
+    const int lane = lane_id(), wave = (int)threadIdx.x / WAVE;
+    int met = 0;
+    for (int w = w0 + wave; w < w1; w += U * NW) {
         int32_t f[U];
 #pragma unroll
         for (int k = 0; k < U; ++k) f[k] = first[min((w + k * NW) * 64 + lane, nnz - 1)];
 #pragma unroll
         for (int k = 0; k < U; ++k) {
             const int e = (w + k * NW) * 64 + lane;
-            const uint64_t m = __ballot(e < nnz && f[k] == n_dst + e);
-            if (lane == 0 && w + k * NW < w1) bits[w + k * NW] = m;
+            const bool have = w + k * NW < w1 && e < nnz;
+            const uint64_t m = __ballot(have && f[k] == n_dst + e), all = __ballot(have);
+            if (lane == 0 && w + k * NW < w1) bits[w + k * NW] = SEEN ? all & ~m : m;
+            met += (int)__popcll(m);
+        }
+    }
+    return met;
+}
+
+// A workgroup takes U edges (row, source) of every thread to the lists of their ranges of sources; count is zero before and after.
+template <int U>
+__device__ __forceinline__ void deal_edges(const DedupArgs &a, int g, uint32_t range, const bool (&ok)[U], const int (&row)[U], const int (&source)[U],
+                                           int *count, int *base)
+{
+    const int tid = threadIdx.x;
+    int at[U], packed[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        const uint32_t q = (uint32_t)source[k] / range;
+        at[k] = 0;
+        if (ok[k]) at[k] = atomicAdd(&count[q], 1);
+        packed[k] = (int)(q << 14) | (int)((uint32_t)source[k] - q * range);
+    }
+    __syncthreads();
+    if (tid < a.t_parts) {
+        const int c = count[tid];
+        base[tid] = c ? atomicAdd(&a.counters[(int64_t)g * HOP_COUNTERS + PARTS_MAX + tid], c) : 0;
+        count[tid] = 0;
+    }
+    __syncthreads();
+    int32_t *lists = a.t_lists + (int64_t)g * 2 * a.list_stride;
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+        if (!ok[k]) continue;
+        const int q = packed[k] >> 14, slot = base[q] + at[k];
+        if (slot < T_LIST) at32(lists, q * T_LIST + slot) = (row[k] << 14) | (packed[k] & 16383);      // (rows < 2^17)
+    }
+}
+
+// Numbers the first appearances and relabels the edges of one stretch of rows.  Returns the frontier's length.
+// ONE: the hop is one part: `first` and the edges for the transpose (`list`, row << 14 | source by edge) are in LDS, at the
+// places where hop_first leaves the one and hop_transpose looks for the others.  Otherwise the marks come from hop_mark_kernel
+// and the edges go to the lists of their ranges of sources, if a transpose is wanted.
+constexpr int ONE_FIRST = 2 * LIST_CAP, ONE_BITS = ONE_FIRST + LIST_CAP, ONE_LIST = T_SOURCES + 1;     // (places in LDS, in words)
+static_assert(ONE_BITS % 2 == 0 && (size_t)(ONE_BITS + 3 * (LIST_CAP / 64)) * 4 <= T_LDS_BYTES, "marks of one part behind its first appearances");
+static_assert(ONE_LIST + LIST_CAP - 1 <= ONE_FIRST, "the edges of one part (at least one id is a root) end in front of its first appearances");
+template <bool ONE>
+__device__ __forceinline__ int hop_number(const DedupArgs &a, int g, int n_dst, int nnz, int chunk, int chunks, uint32_t *lds, HopShared &sh)
+{
+    constexpr int WORDS = ONE ? LIST_CAP / 64 : NUMBER_WORDS, PER = (WORDS + HOP_THREADS - 1) / HOP_THREADS;
+    constexpr int U = ONE ? 4 : 12;
+    __shared__ int t_count[T_PARTS_MAX], t_base[T_PARTS_MAX];
+    unsigned long long *bits = reinterpret_cast<unsigned long long *>(lds + (ONE ? ONE_BITS : 0));
+    int *pre = reinterpret_cast<int *>(lds + (ONE ? ONE_BITS : 0) + 2 * WORDS);
+    int32_t *list = reinterpret_cast<int32_t *>(lds + ONE_LIST);
+    const int tid = threadIdx.x;
+    const int32_t *dst = a.dst_ids + (int64_t)g * a.dst_stride, *sel = a.sel + (int64_t)g * a.sel_stride;
+    const int32_t *first = ONE ? reinterpret_cast<const int32_t *>(lds + ONE_FIRST) : a.first + (int64_t)g * a.first_stride;
+    int32_t *src = a.src_ids + (int64_t)g * a.src_stride, *indices = a.indices + (int64_t)g * a.indices_stride;
+    const int32_t *indptr = a.indptr + (int64_t)g * a.indptr_stride;
+    const int r0 = (int)((int64_t)n_dst * chunk / chunks), r1 = (int)((int64_t)n_dst * (chunk + 1) / chunks);
+    const int words = (nnz + 63) / 64;
+    // an edge's first appearance never lies behind it: the words up to the stretch's end are enough
+    const int w1 = ONE || chunk == chunks - 1 ? words : (indptr[r1] + 63) / 64;
+    if constexpr (ONE) {
+        mark_words<false>(first, n_dst, nnz, 0, words, bits);
+    } else {
+        const unsigned long long *seen = a.seen_bits + (int64_t)g * NUMBER_WORDS;
+        for (int w = tid; w < w1; w += HOP_THREADS) bits[w] = ~seen[w] & (nnz - w * 64 < 64 ? (1ull << (nnz - w * 64)) - 1ull : ~0ull);
+        if (tid < T_PARTS_MAX) t_count[tid] = 0;
+        if (tid < WAVE) {                                      // the number of first appearances of the whole hop
+            int n = tid < chunks ? a.new_count[(int64_t)g * HOP_CHUNKS_MAX + tid] : 0;
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) n += __shfl_xor(n, off);
+            if (tid == 0) sh.count = n;
         }
     }
     __syncthreads();
-    constexpr int PER = NUMBER_WORDS / HOP_THREADS;
     int x[PER], sum = 0, total;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        x[k] = tid * PER + k < w1 ? __popcll(bits[tid * PER + k]) : 0;
+        x[k] = tid * PER + k < w1 ? (int)__popcll(bits[tid * PER + k]) : 0;
         sum += x[k];
     }
     int run = block_exclusive_scan_1024(sum, sh.scan, total);
+    if (!ONE) total = sh.count;
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
-        pre[tid * PER + k] = run;
+        if (tid * PER + k < WORDS) pre[tid * PER + k] = run;
         run += x[k];
     }
+    const int need = n_dst + total, n_src = min(need, a.cap_src);
     __syncthreads();
     for (int i = r0 + tid; i < r1; i += HOP_THREADS) src[i] = dst[i];
-#pragma unroll 4
-    for (int e = e0 + tid; e < e1; e += HOP_THREADS) {
-        const int f = first[e];
-        const int32_t u = sel[e];
-        int local = f;
-        if (f >= n_dst) {
-            const int q = f - n_dst;
-            local = n_dst + pre[q >> 6] + __popcll(bits[q >> 6] & ((1ull << (q & 63)) - 1ull));
-            if (q == e && local < a.cap_src) src[local] = u;           // (a frontier cut short: the block is marked invalid)
+    const bool deal = !ONE && a.t_lists != nullptr;
+    const uint32_t range = deal ? (uint32_t)((n_src + a.t_parts - 1) / a.t_parts) : 1u;
+    // lanes by row: the edge's row is known, and it takes the place of the neighbour's id (which no other lane reads)
+    const int gw_bits = a.fanout > 1 ? 32 - __builtin_clz((uint32_t)(a.fanout - 1)) : 0, gw = 1 << gw_bits, lanes = (r1 - r0) << gw_bits;
+    for (int t0 = 0; t0 < lanes; t0 += U * HOP_THREADS) {
+        int row[U], e[U], f[U], local[U];
+        int32_t u[U];
+        bool ok[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int t = t0 + k * HOP_THREADS + tid;
+            row[k] = r0 + min(t >> gw_bits, r1 - r0 - 1);
+            e[k] = at32(indptr, row[k]) + (t & (gw - 1));
+            ok[k] = t < lanes && e[k] < at32(indptr, row[k] + 1);
         }
-        if (local >= a.cap_src) local = 0;                             // only in a block that is marked invalid
-        indices[e] = local;
-        if (a.gather_ids) a.gather_ids[(int64_t)g * a.indices_stride + e] = u;
-    }
-    // the destination row of every edge of the stretch takes the place of its neighbour's id (which no other stretch reads)
-    if (a.edge_rows) {
-        __syncthreads();
-        const int gw_bits = __builtin_ctz(a.gw), lanes = (r1 - r0) << gw_bits;
-#pragma unroll 4
-        for (int t = tid; t < lanes; t += HOP_THREADS) {
-            const int row = r0 + (t >> gw_bits), e = indptr[row] + (t & (a.gw - 1));
-            if (e < indptr[row + 1]) a.edge_rows[(int64_t)g * a.edge_rows_stride + e] = row;
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if constexpr (ONE) f[k] = first[ok[k] ? e[k] : 0];
+            else f[k] = at32(first, ok[k] ? e[k] : 0);
+            u[k] = at32(sel, ok[k] ? e[k] : 0);
         }
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            local[k] = f[k];
+            if (!ok[k]) continue;
+            if (f[k] >= n_dst) {
+                const int q = f[k] - n_dst;
+                local[k] = n_dst + pre[q >> 6] + (int)__popcll(bits[q >> 6] & ((1ull << (q & 63)) - 1ull));
+                if (q == e[k] && local[k] < a.cap_src) at32(src, local[k]) = u[k];      // (a frontier cut short: the block is marked invalid)
+            }
+            if (local[k] >= a.cap_src) local[k] = 0;                              // only in a block that is marked invalid
+            at32(indices, e[k]) = local[k];
+            if (a.gather_ids) at32(a.gather_ids + (int64_t)g * a.indices_stride, e[k]) = u[k];
+            if (a.edge_rows) at32(a.edge_rows + (int64_t)g * a.edge_rows_stride, e[k]) = row[k];
+            if constexpr (ONE) list[e[k]] = (row[k] << 14) | local[k];
+        }
+        if (deal) deal_edges<U>(a, g, range, ok, row, local, t_count, t_base);
     }
-    int n_src = 0;
-    if (chunk == chunks - 1) {
-        const int need = n_dst + total;
-        n_src = min(need, a.cap_src);
-        if (tid == 0) {
-            int32_t *hdr = a.hdr + (int64_t)g * CR_HDR_WORDS;
-            hdr[CR_HDR_N_SRC] = n_src;
-            if (need > a.cap_src) {            // only possible with capacities below the bound
-                atomicOr(&hdr[CR_HDR_STATUS], CR_ASYNC_FRONTIER_OVERFLOW);
-                if (a.async_status) {
-                    atomicOr(reinterpret_cast<unsigned long long *>(a.async_status), (unsigned long long)CR_ASYNC_FRONTIER_OVERFLOW);
-                    atomicMax(reinterpret_cast<long long *>(a.async_status + 1), (long long)need);
-                }
+    if (chunk == chunks - 1 && tid == 0) {
+        int32_t *hdr = a.hdr + (int64_t)g * CR_HDR_WORDS;
+        hdr[CR_HDR_N_SRC] = n_src;
+        if (need > a.cap_src) {                // only possible with capacities below the bound
+            atomicOr(&hdr[CR_HDR_STATUS], CR_ASYNC_FRONTIER_OVERFLOW);
+            if (a.async_status) {
+                atomicOr(reinterpret_cast<unsigned long long *>(a.async_status), (unsigned long long)CR_ASYNC_FRONTIER_OVERFLOW);
+                atomicMax(reinterpret_cast<long long *>(a.async_status + 1), (long long)need);
             }
         }
     }
@@ -2137,9 +2207,10 @@ __device__ __forceinline__ void transpose_windows(const int32_t *indices, const 
     }
 }
 
-// Transposed block of one range of sources: row pointers and, per source, the destination rows that use it, ascending.  ANY_SIZE:
-// the range may have more edges than the lists hold.
-template <bool ANY_SIZE>
+// Transposed block of one range of sources: row pointers and, per source, the destination rows that use it, ascending.  ONE: the
+// whole block is one range and its edges are in the list already (hop_number).  Otherwise they come from the range's list in
+// memory; a range may have more edges than that holds.
+template <bool ONE>
 __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_dst, int n_src, int nnz, int part, int parts, uint32_t *lds, HopShared &sh)
 {
     int *start = reinterpret_cast<int *>(lds);                                  // [T_SOURCES + 1]
@@ -2153,22 +2224,21 @@ __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_d
     const int lo = min(n_src, part * range), hi = min(n_src, lo + range), n = hi - lo;
     if (part == parts - 1 && tid == 0) t_indptr[n_src] = nnz;
     if (n <= 0) return;                                                        // (uniform)
-    for (int i = tid; i <= n; i += HOP_THREADS) start[i] = 0;
-    if (tid == 0) { sh.count = 0; sh.below = 0; sh.work = 0; }
-    __syncthreads();
-    // the range's edges: source and place of every edge into the lists (the lists' two arrays, for now), then the row in its
-    // place's stead, both packed into one word
     const int32_t *edge_rows = a.edge_rows + (int64_t)g * a.edge_rows_stride;
-    int below = 0;
-    collect<16>(indices, nnz, [&](int32_t s, bool have) {
-        below += have && s < lo ? 1 : 0;
-        return have && (uint32_t)(s - lo) < (uint32_t)n;
-    }, lo, 0, reinterpret_cast<uint32_t *>(sorted), reinterpret_cast<uint32_t *>(list), T_LIST, &sh.count);
-#pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) below += __shfl_xor(below, off);
-    if (lane == 0) atomicAdd(&sh.below, below);
+    for (int i = tid; i <= n; i += HOP_THREADS) start[i] = 0;
+    if (tid == 0) sh.work = 0;
+    int count = nnz, base = 0;
     __syncthreads();
-    const int count = sh.count, base = sh.below;
+    if constexpr (!ONE) {
+        const int32_t *sizes = a.counters + (int64_t)g * HOP_COUNTERS + PARTS_MAX;
+        int below = tid < part ? sizes[tid] : 0;               // (at most T_PARTS_MAX ranges: the first wave's lanes)
+        count = sizes[part];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) below += __shfl_xor(below, off);
+        if (tid == 0) sh.below = below;
+        __syncthreads();
+        base = sh.below;
+    }
     // starts of the segments from their lengths (a thread owns consecutive sources)
     auto scan_starts = [&]() {
         constexpr int PER = T_SOURCES / HOP_THREADS;
@@ -2186,18 +2256,21 @@ __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_d
         int run = block_exclusive_scan_1024(sum, sh.scan, total);
 #pragma unroll
         for (int k = 0; k < PER; ++k) {
-            if (s0 + k < n) {
-                start[s0 + k] = run;
-                t_indptr[lo + s0 + k] = base + run;
-            }
+            if (s0 + k < n) start[s0 + k] = run;
             run += x[k];
         }
         if (tid == 0) start[n] = total;
         __syncthreads();
+        // (a thread's own stretch straight to memory would make every store touch 64 lines)
+        for (int i = tid; i < n; i += HOP_THREADS) t_indptr[lo + i] = base + start[i];
+        __syncthreads();
     };
-    if (!ANY_SIZE || count <= T_LIST) {
-#pragma unroll 4
-        for (int i = tid; i < count; i += HOP_THREADS) list[i] = (edge_rows[list[i]] << 14) | sorted[i];      // (rows < 2^17)
+    if (ONE || count <= T_LIST) {
+        if constexpr (!ONE) {
+            const int32_t *from = a.t_lists + (int64_t)g * 2 * a.list_stride + (int64_t)part * T_LIST;
+#pragma unroll 8
+            for (int i = tid; i < count; i += HOP_THREADS) list[i] = from[i];
+        }
         __syncthreads();
         // (rolled loops: unrolled over the list, this function was 40 KB of code, most of which ran once per workgroup straight
         // from memory)
@@ -2251,33 +2324,105 @@ __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_d
     const int n_dst = group_n_dst(a.prev_hdr, g, a.n_roots_total, a.batch_size);      \
     const int nnz = a.hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_NNZ]
 
+// deals the ids of a hop (destination nodes, then chosen neighbours) to the lists of their parts, each with its position
+__global__ __launch_bounds__(HOP_THREADS) void hop_part_kernel(DedupArgs a, uint32_t parts)
+{
+    __shared__ int count[PARTS_MAX], base[PARTS_MAX];
+    const int g = blockIdx.y;
+    const int n_dst = group_n_dst(a.prev_hdr, g, a.n_roots_total, a.batch_size);
+    const int total = n_dst + a.hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_NNZ];
+    const int tid = threadIdx.x, i0 = (int)blockIdx.x * PART_CHUNK + tid;
+    if (i0 - tid >= total) return;
+    const int32_t *dst = a.dst_ids + (int64_t)g * a.dst_stride, *sel = a.sel + (int64_t)g * a.sel_stride;
+    if (tid < PARTS_MAX) count[tid] = 0;
+    uint32_t id[PART_PER];
+    int at[PART_PER];
+#pragma unroll
+    for (int k = 0; k < PART_PER; ++k) id[k] = hop_id(dst, sel, n_dst, min(i0 + k * HOP_THREADS, total - 1));
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < PART_PER; ++k) {
+        at[k] = 0;
+        if (i0 + k * HOP_THREADS < total) at[k] = atomicAdd(&count[id_part(id[k], parts)], 1);
+    }
+    __syncthreads();
+    if (tid < (int)parts) base[tid] = atomicAdd(&a.counters[(int64_t)g * HOP_COUNTERS + tid], count[tid]);
+    __syncthreads();
+    uint2 *lists = a.lists + (int64_t)g * a.list_stride;
+#pragma unroll
+    for (int k = 0; k < PART_PER; ++k) {
+        const uint32_t p = id_part(id[k], parts);
+        const int i = i0 + k * HOP_THREADS, slot = base[p] + at[k];
+        if (i < total && slot < LIST_CAP) at32(lists, (int)p * LIST_CAP + slot) = make_uint2(id[k], (uint32_t)i);
+    }
+}
+
 __global__ __launch_bounds__(HOP_THREADS) void hop_first_kernel(DedupArgs a)
 {
     CR_HOP();
-    hop_first(a, g, n_dst, nnz, blockIdx.x, gridDim.x, hop_lds, sh);
+    hop_first<false>(a, g, n_dst, nnz, blockIdx.x, gridDim.x, hop_lds, sh);
+}
+
+__global__ __launch_bounds__(HOP_THREADS) void hop_mark_kernel(DedupArgs a)
+{
+    __shared__ int sum;
+    const int g = blockIdx.y;
+    const int n_dst = group_n_dst(a.prev_hdr, g, a.n_roots_total, a.batch_size);
+    const int nnz = a.hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_NNZ];
+    const int words = (nnz + 63) / 64, per = (words + (int)gridDim.x - 1) / (int)gridDim.x, w0 = min(words, (int)blockIdx.x * per);
+    if (threadIdx.x == 0) sum = 0;
+    __syncthreads();
+    const int met = mark_words<true>(a.first + (int64_t)g * a.first_stride, n_dst, nnz, w0, min(words, w0 + per), a.seen_bits + (int64_t)g * NUMBER_WORDS);
+    if (lane_id() == 0 && met) atomicAdd(&sum, met);
+    __syncthreads();
+    if (threadIdx.x == 0) a.new_count[(int64_t)g * HOP_CHUNKS_MAX + blockIdx.x] = sum;
 }
 
 __global__ __launch_bounds__(HOP_THREADS) void hop_number_kernel(DedupArgs a)
 {
     CR_HOP();
-    hop_number(a, g, n_dst, nnz, (int)blockIdx.x, (int)gridDim.x, hop_lds, sh);
+    hop_number<false>(a, g, n_dst, nnz, (int)blockIdx.x, (int)gridDim.x, hop_lds, sh);
+}
+
+// behind a frontier from the tables: the edges to the lists of their ranges of sources
+constexpr int DEAL_PER = 8;
+__global__ __launch_bounds__(HOP_THREADS) void hop_deal_kernel(DedupArgs a)
+{
+    __shared__ int count[T_PARTS_MAX], base[T_PARTS_MAX];
+    const int g = blockIdx.y, tid = threadIdx.x;
+    const int32_t *hdr = a.hdr + (int64_t)g * CR_HDR_WORDS;
+    const int nnz = hdr[CR_HDR_NNZ], n_src = hdr[CR_HDR_N_SRC], e0 = (int)blockIdx.x * DEAL_PER * HOP_THREADS + tid;
+    if (e0 - tid >= nnz) return;
+    const int32_t *indices = a.indices + (int64_t)g * a.indices_stride, *edge_rows = a.edge_rows + (int64_t)g * a.edge_rows_stride;
+    if (tid < T_PARTS_MAX) count[tid] = 0;
+    int row[DEAL_PER], source[DEAL_PER];
+    bool ok[DEAL_PER];
+#pragma unroll
+    for (int k = 0; k < DEAL_PER; ++k) {
+        const int e = min(e0 + k * HOP_THREADS, nnz - 1);
+        ok[k] = e0 + k * HOP_THREADS < nnz;
+        source[k] = at32(indices, e);
+        row[k] = at32(edge_rows, e);
+    }
+    __syncthreads();
+    deal_edges<DEAL_PER>(a, g, (uint32_t)((n_src + a.t_parts - 1) / a.t_parts), ok, row, source, count, base);
 }
 
 __global__ __launch_bounds__(HOP_THREADS) void hop_transpose_kernel(DedupArgs a)
 {
     CR_HOP();
-    hop_transpose<true>(a, g, n_dst, a.hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_N_SRC], nnz, (int)blockIdx.x, (int)gridDim.x, hop_lds, sh);
+    hop_transpose<false>(a, g, n_dst, a.hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_N_SRC], nnz, (int)blockIdx.x, (int)gridDim.x, hop_lds, sh);
 }
 
-// the three of them for a hop that is one part
+// all of them for a hop that is one part
 __global__ __launch_bounds__(HOP_THREADS) void hop_kernel(DedupArgs a)
 {
     CR_HOP();
-    hop_first(a, g, n_dst, nnz, 0u, 1u, hop_lds, sh);
+    hop_first<true>(a, g, n_dst, nnz, 0u, 1u, hop_lds, sh);
     __syncthreads();
-    const int n_src = hop_number(a, g, n_dst, nnz, 0, 1, hop_lds, sh);
+    const int n_src = hop_number<true>(a, g, n_dst, nnz, 0, 1, hop_lds, sh);
     __syncthreads();
-    if (a.t_indptr) hop_transpose<false>(a, g, n_dst, n_src, nnz, 0, 1, hop_lds, sh);
+    if (a.t_indptr) hop_transpose<true>(a, g, n_dst, n_src, nnz, 0, 1, hop_lds, sh);
 }
 
 // one thread per 32 adjacency entries: find the row of the first one, then walk
@@ -2318,8 +2463,29 @@ struct SamplePlan {
     int32_t *sel, *cnt, *newoff, *tcount, *tfill, *t_tmp, *t_pos, *order_hist, *order_cursor, *order_tiles;
     uint16_t *order_bucket;
     unsigned long long *newmask, *table;
+    int32_t *hop_counters = nullptr, *hop_new_count = nullptr;      // hops in several parts (frontier in LDS)
+    unsigned long long *hop_bits = nullptr;
+    uint2 *hop_lists = nullptr;
+    int64_t list_stride = 0;  // per batch, in entries
     size_t bytes;
 };
+
+// How a hop in several parts is cut up.  Small groups are cut finer, or most compute units sit idle.
+static int hop_chunks_for(int n_batches) { return n_batches >= 32 ? PARTS_MIN : (n_batches <= 8 ? HOP_CHUNKS_MAX : 256 / n_batches); }
+static int64_t hop_items_max(int n_batches) { return (n_batches < PARTS_MAX / PARTS_MIN ? PARTS_MIN * n_batches : PARTS_MAX) * (int64_t)LIST_MEAN; }
+static int hop_parts_for(int64_t items, int n_batches)
+{
+    int parts = PARTS_MIN;
+    while (parts * (int64_t)LIST_MEAN < items) parts *= 2;
+    while (parts < PARTS_MAX && 2 * parts * (int64_t)n_batches <= 256) parts *= 2;
+    return parts;
+}
+static int64_t hop_t_parts_for(int64_t cap_nnz, int64_t cap_src, int n_batches)
+{
+    int64_t parts = ceil_div(cap_nnz, T_MEAN);
+    if (parts < ceil_div(cap_src, T_SOURCES)) parts = ceil_div(cap_src, T_SOURCES);
+    return parts < hop_chunks_for(n_batches) ? hop_chunks_for(n_batches) : parts;
+}
 
 static bool hop_lds_ready()
 {
@@ -2391,6 +2557,20 @@ static cr_status make_plan(const cr_sample_cfg *cfg, int64_t n_nodes, int32_t ba
     } else {
         p.order_hist = p.order_cursor = p.order_tiles = nullptr;
         p.order_bucket = nullptr;
+    }
+    for (int l = 0; l < p.L; ++l) {                  // lists of the hops in several parts
+        if (p.cap_nnz[l] > p.max_nnz_t) continue;    // (neither a frontier in LDS nor a transpose)
+        const int64_t items = (int64_t)p.cap_dst[l] + p.cap_nnz[l], t_parts = hop_t_parts_for(p.cap_nnz[l], p.cap_src[l], n_batches);
+        const int64_t lists = items > LIST_CAP && items <= hop_items_max(n_batches) ? (int64_t)hop_parts_for(items, n_batches) * LIST_CAP : 0;
+        const int64_t t_lists = t_parts <= T_PARTS_MAX ? t_parts * T_LIST / 2 : 0;      // (behind the tables also where a hop is one part)
+        if (p.list_stride < lists) p.list_stride = lists;
+        if (p.list_stride < t_lists) p.list_stride = t_lists;
+    }
+    if (p.list_stride > 0) {
+        p.hop_counters = c.take<int32_t>(G * HOP_COUNTERS);
+        p.hop_new_count = c.take<int32_t>(G * HOP_CHUNKS_MAX);
+        p.hop_bits = c.take<unsigned long long>(G * NUMBER_WORDS);
+        p.hop_lists = c.take<uint2>(G * (size_t)p.list_stride);
     }
     p.bytes = c.bytes();
     return CR_OK;
@@ -2554,26 +2734,18 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         const bool global_ids = l == 0 && (cfg->flags & CR_SAMPLE_INPUT_GLOBAL_IDS), tr = !global_ids && b.t_indptr != nullptr;
         const bool direct_out = global_ids && !sa.strict_p1;
         // Frontier in LDS: hops of at most 32 parts of ids (294912) whose row pointers are known before the selection, that is
-        // all but the strict setting (CR_SAMPLE_HASH_DEDUP asks for the table in so many words).  Measured against the tables in
-        // memory (all kernels of the hop except its selection):
-        // 32 x 67 K ids (products-like, second hop) 335 -> 90 us, 32 x 6 K ids (its root hop, one workgroup per batch and
-        // one launch instead of nine) 95 -> 33 us, 8 x 280 K ids (reddit-like input hop, 32 parts) 310 -> 177 us.  The cost
-        // grows with ids times parts, the tables' with ids: beyond this the ratio that is left is used up (the 1.1 M ids of
-        // a relabelled products-like input hop would be read 128 times), and the tables serve.  The transpose reads every
-        // edge once per range of sources and is cut off at forty ranges for the same reason.
-        // Eight parts per batch of the group and no more: all parts of a batch read all of its ids, which takes as long for
-        // one batch as for eight, while the tables' kernels get shorter.  The whole call, tables over this, one batch of
-        // 55 / 74 / 110 / 147 / 295 K ids: 1.04 to 1.12, 0.96 to 1.01, 0.94 to 1.04, 0.88 to 0.95, 0.75 to 0.87; two of 110 / 147 /
-        // 220 / 295 K: 1.02 to 1.10, 0.97 to 1.01, 0.94 to 1.06, 0.88 to 1.01; four of 295 K: 1.04 to 1.18.
+        // all but the strict setting (CR_SAMPLE_HASH_DEDUP asks for the table in so many words).  Against the tables in memory, all
+        // kernels of the hop except its selection: 32 x 67 K ids (products-like, second hop) 335 -> 83 us, 32 x 6 K ids (its root
+        // hop, one workgroup per batch and one launch instead of nine) 95 -> 23 us, 8 x 280 K ids (reddit-like input hop) 310 -> 92.
+        // Eight parts per batch of the group and no more: the line was drawn when every part's workgroup went over all ids of its
+        // batch, and the tables' kernels get shorter with fewer batches.  Whole calls beyond it, which take the tables, now against
+        // this: one batch of 280 K ids (reddit-like) 162 us, 159 here; two 199, 176; one of 150 roots (products-like, transposed
+        // input) 175, 150.
         const int64_t hop_items = (int64_t)cap_dst + p.cap_nnz[l];
-        // (workgroups per batch that a hop is cut into at least: small groups are cut finer, or most compute units sit idle)
-        const int hop_chunks = n_batches >= 32 ? PARTS_MIN : (n_batches <= 8 ? 32 : 256 / n_batches);
-        int64_t t_parts = ceil_div(p.cap_nnz[l], T_MEAN);
-        if (t_parts < ceil_div(b.cap_src, T_SOURCES)) t_parts = ceil_div(b.cap_src, T_SOURCES);
-        if (t_parts < hop_chunks) t_parts = hop_chunks;
+        const int hop_chunks = hop_chunks_for(n_batches);
+        const int64_t t_parts = hop_t_parts_for(p.cap_nnz[l], p.cap_src[l], n_batches);
         const bool lds_transpose = tr && t_parts <= T_PARTS_MAX && cap_dst < (1 << 17) && hop_lds_ready();
-        const int64_t parts_max = PARTS_MIN * (int64_t)n_batches < PARTS_MAX ? PARTS_MIN * n_batches : PARTS_MAX;
-        const bool lds_hop = !global_ids && !sa.strict_p1 && !(cfg->flags & CR_SAMPLE_HASH_DEDUP) && hop_items <= parts_max * LIST_MEAN &&
+        const bool lds_hop = !global_ids && !sa.strict_p1 && !(cfg->flags & CR_SAMPLE_HASH_DEDUP) && hop_items <= hop_items_max(n_batches) &&
                              p.max_nnz_t >= p.cap_nnz[l] && (!tr || lds_transpose) && hop_lds_ready();
         const bool one_part = lds_hop && hop_items <= LIST_CAP;
         ScanArgs sc;
@@ -2584,6 +2756,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         sc.cap_src = b.cap_src; sc.async_status = async_status();
         sc.g_indptr = graph->indptr; sc.dst_ids = dst_ids; sc.dst_stride = dst_stride; sc.fanout = f;
         sc.head_ids = nullptr; sc.head_stride = 0;
+        sc.zero = (lds_hop || lds_transpose) && !one_part ? p.hop_counters : nullptr; sc.n_zero = HOP_COUNTERS;
         const dim3 scan_grid((unsigned)ceil_div(cap_dst, SCAN_TILE), n_batches);
         sa.out_indptr = nullptr; sa.out_indptr_stride = 0; sa.out_ids = nullptr; sa.out_stride = 0;
         if (direct_out || lds_hop) {
@@ -2627,7 +2800,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
             so.prev_hdr = prev_hdr; so.n_roots_total = n_roots_total; so.batch_size = batch_size;
             so.mode = 3; so.n_fixed = n_cells; so.in = p.order_hist; so.in_stride = n_cells + 1; so.out = p.order_cursor;
             so.out_stride = n_cells + 1; so.out_copy = nullptr; so.copy_stride = 0; so.hdr = b.hdr;
-            so.tile_before = nullptr; so.cap_src = 0; so.async_status = nullptr; so.head_ids = nullptr;
+            so.tile_before = nullptr; so.cap_src = 0; so.async_status = nullptr; so.head_ids = nullptr; so.zero = nullptr; so.n_zero = 0;
             const int scan_tiles = (int)ceil_div(n_cells, SCAN_TILE);
             if (grouped && scan_tiles > 8 && scan_tiles <= 16384) {
                 hipLaunchKernelGGL(scan_tile_sums_kernel, dim3((unsigned)scan_tiles), dim3(SCAN_THREADS), 0, s, p.order_hist, n_cells, p.order_tiles);
@@ -2651,6 +2824,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         da.newcnt = p.cnt; da.newoff = p.newoff; da.newmask = p.newmask; da.row_stride = p.max_dst; da.off_stride = p.max_dst + 1;
         const dim3 grid((unsigned)ceil_div((int64_t)cap_dst * da.gw, 256), n_batches);
         da.first = p.t_pos; da.first_stride = p.max_nnz_t + 1;
+        da.counters = nullptr; da.lists = nullptr; da.t_lists = nullptr; da.list_stride = 0; da.seen_bits = nullptr; da.new_count = nullptr; da.t_parts = 0;
         da.edge_rows = !lds_transpose ? nullptr : (lds_hop ? p.sel : p.t_pos); da.edge_rows_stride = lds_hop ? p.max_nnz : p.max_nnz_t + 1;
         if (global_ids) {
             da.tcount = nullptr; da.tfill = nullptr; da.t_stride = 0; da.t_indptr = nullptr; da.t_indptr_stride = 0;
@@ -2669,9 +2843,12 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
             continue;
         }
         if (lds_hop) {
-            int parts = PARTS_MIN;
-            while (parts * (int64_t)LIST_MEAN < hop_items) parts *= 2;
+            const int parts = hop_parts_for(hop_items, n_batches);
+            da.counters = p.hop_counters; da.lists = p.hop_lists; da.list_stride = p.list_stride; da.seen_bits = p.hop_bits; da.new_count = p.hop_new_count;
+            da.t_lists = lds_transpose ? reinterpret_cast<int32_t *>(p.hop_lists) : nullptr; da.t_parts = (int32_t)t_parts;
+            hipLaunchKernelGGL(hop_part_kernel, dim3((unsigned)ceil_div(hop_items, PART_CHUNK), n_batches), dim3(HOP_THREADS), 0, s, da, (uint32_t)parts);
             hipLaunchKernelGGL(hop_first_kernel, dim3((unsigned)parts, n_batches), dim3(HOP_THREADS), DEDUP_LDS_BYTES, s, da);
+            hipLaunchKernelGGL(hop_mark_kernel, dim3((unsigned)hop_chunks, n_batches), dim3(HOP_THREADS), 0, s, da);
             hipLaunchKernelGGL(hop_number_kernel, dim3((unsigned)hop_chunks, n_batches), dim3(HOP_THREADS), NUMBER_LDS_BYTES, s, da);
         } else {
             if (!p.direct) {
@@ -2693,6 +2870,11 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
                 hipLaunchKernelGGL(reset_kernel, dim3((unsigned)ceil_div(p.cap_src[l], 1024), n_batches), blk, 0, s, da);
         }
         if (lds_transpose) {
+            if (!lds_hop) {
+                da.counters = p.hop_counters; da.list_stride = p.list_stride;
+                da.t_lists = reinterpret_cast<int32_t *>(p.hop_lists); da.t_parts = (int32_t)t_parts;
+                hipLaunchKernelGGL(hop_deal_kernel, dim3((unsigned)ceil_div(p.cap_nnz[l], DEAL_PER * HOP_THREADS), n_batches), dim3(HOP_THREADS), 0, s, da);
+            }
             hipLaunchKernelGGL(hop_transpose_kernel, dim3((unsigned)t_parts, n_batches), dim3(HOP_THREADS), T_LDS_BYTES, s, da);
         } else if (tr) {
             sc.mode = 2; sc.in = p.tcount; sc.in_stride = p.max_src_t + 1; sc.out = b.t_indptr; sc.out_stride = b.cap_src + 1;

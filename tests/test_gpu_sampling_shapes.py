@@ -189,6 +189,21 @@ def test_one_part_gets_every_id(torch_mod):
     check(torch_mod, graph, 16_000, 8000, [2, 15], 0.5, "one part")
 
 
+@pytest.mark.parametrize("n_batches,parts", [(1, 32), (2, 32), (32, 8)])
+def test_one_part_gets_every_id_of_a_group(torch_mod, n_batches, parts):
+    """The same with as many parts as small groups (32) and large ones (8) are cut into, and batches without an edge behind them."""
+    n, batch_size = 27_000 * parts, 4000 if n_batches < 32 else 900
+    ids = np.arange(n, dtype=np.uint32)
+    fold = ids ^ (ids >> 15)
+    part0 = ids[((fold ^ (fold >> 5) ^ (fold >> 10)) & (parts - 1)) == 0].astype(np.int32)
+    assert len(part0) > 20_000
+    rng = np.random.default_rng(parts)
+    picks = np.sort(part0[(rng.integers(0, len(part0) - 20, size=(n, 1)) + np.arange(15))], axis=1)
+    degree = np.where(np.arange(n) % 7 == 3, 0, 15)
+    graph = (np.concatenate([[0], np.cumsum(degree)]).astype(np.int64), picks[degree > 0].reshape(-1), (np.arange(n) // (n // 4 + 1)).astype(np.int32))
+    check(torch_mod, graph, n_batches * batch_size - 5, batch_size, [2, 15], 0.5, "one part of a group")
+
+
 # destination rows of a whole group in community order: one workgroup (at most 8192 rows by capacity), just not, many buckets
 @pytest.mark.parametrize("batch_size,n_batches,n_comm", [(64, 1, 5), (409, 4, 4096), (410, 4, 9000), (1024, 8, 70)])
 def test_group_order(torch_mod, batch_size, n_batches, n_comm):
