@@ -246,12 +246,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(CH == 4 ? 3
 // ------------------------------------------------------------------------------------------------
 // The same product for blocks of few rows (the layers next to the roots: about a thousand rows), where the tiled
 // kernel above leaves most of the chip idle and spends its time in K steps taken one after another.  Workgroup tile
-// 32 (m) x 64 (n); the four waves split K between them (wave w takes the 16-wide steps w, w + 4, ...) and fetch
-// their MFMA operands straight from memory in the layout the matrix cores want (both operands are contiguous along
-// k: a lane's fragment is one 16-byte load), up to eight steps in flight, no staging and no barrier inside the
-// loop.  The four partial tiles meet in LDS and are added in a fixed order.
+// 32 (m) x 64 (n); K is taken in chunks of 256 columns, two of them on their way at once, which are K = 512's single round trip
+// to memory.  They travel as whole rows (half a wave reads 512 contiguous bytes) and through LDS: with the MFMA fragments straight
+// from memory, 16 bytes of 32 rows per load, the kernel was bound by the address unit (4.5 of 7.5 us for 1024 x 512 -> 192; the
+// kernel now takes 5.0; 64 rows x 128 -> 64 with the loss 8.1 -> 5.8).  The loads do not wait for the row count.  The four waves split a chunk between them (wave w takes the
+// 16-wide steps w, w + 4, ...); their partial tiles meet in LDS and are added in a fixed order.
 // ------------------------------------------------------------------------------------------------
-constexpr int SMALL_DEPTH = 8;
+constexpr int SMALL_KC = 256;
+constexpr int SMALL_LROW = SMALL_KC + 8;        // staged row: 256 bf16 + 8 of padding
 constexpr int SMALL_ROW = 68;     // floats per staged row: 64 + 4 of padding (272 bytes, keeps 16-byte alignment)
 
 // loss part of the fused top-layer launch (XENT == true): the product's rows are the roots, its columns the classes
@@ -269,10 +271,31 @@ struct XentArgs {
 template <bool XENT>
 __global__ __launch_bounds__(256) void gemm_nt_small_kernel(NtArgs a, XentArgs x)
 {
-    __shared__ __attribute__((aligned(16))) float red[4][32][SMALL_ROW];
+    __shared__ __attribute__((aligned(16))) uint16_t tile[(32 + 64) * SMALL_LROW];      // A's rows, then B's
     __shared__ float wg_loss[32];
-    const int M = min(a.hdr[CR_HDR_N_DST], a.max_rows);
+    float (*red)[32][SMALL_ROW] = reinterpret_cast<float (*)[32][SMALL_ROW]>(tile);      // [4], once the staged rows are done with
+    static_assert(4 * 32 * SMALL_ROW * sizeof(float) <= sizeof(tile), "the partial tiles fit the staged rows' room");
     const int m0 = (int)blockIdx.y * 32, n0 = (int)blockIdx.x * 64;
+    const int K = a.K, nchunk = (K + SMALL_KC - 1) / SMALL_KC;
+    // staging: piece p = i * 256 + thread = (row p / 32, 16-byte piece p % 32): four of A and eight of B per thread; pieces past
+    // the end of K repeat the first one and are not used
+    const int srow = (int)threadIdx.x >> 5, spiece = ((int)threadIdx.x & 31) * 8;
+    auto fetch = [&](u32x4v (&f)[12], int c) {
+        const int k = c * SMALL_KC + spiece < K ? c * SMALL_KC + spiece : 0;
+        const uint16_t *src = k < a.K0 ? a.A0 + k : a.A1 + (k - a.K0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) f[i] = *reinterpret_cast<const u32x4v *>(src + (int64_t)min(m0 + i * 8 + srow, a.max_rows - 1) * a.lda);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) f[4 + i] = *reinterpret_cast<const u32x4v *>(a.B + (int64_t)(n0 + i * 8 + srow) * K + k);
+    };
+    auto stage = [&](const u32x4v (&f)[12]) {
+#pragma unroll
+        for (int i = 0; i < 12; ++i) *reinterpret_cast<u32x4v *>(&tile[(i * 8 + srow) * SMALL_LROW + spiece]) = f[i];
+    };
+    u32x4v f0[12], f1[12];
+    fetch(f0, 0);
+    if (nchunk > 1) fetch(f1, 1);
+    const int M = min(a.hdr[CR_HDR_N_DST], a.max_rows);
     if (XENT && M <= 0) {
         if (blockIdx.y == 0 && threadIdx.x == 0) x.loss[0] = 0.f;
         return;
@@ -284,9 +307,12 @@ __global__ __launch_bounds__(256) void gemm_nt_small_kernel(NtArgs a, XentArgs x
     // the label of the row this thread will finish: requested now (two dependent loads), used after the product
     int label = 0;
     if constexpr (XENT) label = x.labels[x.root_ids[min(m0 + (tid >> 3), M - 1)]];
-    const int64_t arow = (int64_t)min(m0 + lr, M - 1) * a.lda + 8 * half;
-    const uint16_t *b0 = a.B + (int64_t)(n0 + lr) * a.K + 8 * half;
-    const uint16_t *b1 = b0 + (int64_t)32 * a.K;
+    const int c8 = (tid & 7) * 8, n = n0 + c8;
+    float4 q0 = make_float4(0.f, 0.f, 0.f, 0.f), q1 = q0;
+    if (a.bias) {
+        q0 = *reinterpret_cast<const float4 *>(a.bias + n);
+        q1 = *reinterpret_cast<const float4 *>(a.bias + n + 4);
+    }
 
     f32x16 acc[2];
 #pragma unroll
@@ -294,24 +320,29 @@ __global__ __launch_bounds__(256) void gemm_nt_small_kernel(NtArgs a, XentArgs x
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
 
-    for (int s0 = wave; s0 < nk; s0 += 4 * SMALL_DEPTH) {
-        u32x4v xa[SMALL_DEPTH], xb0[SMALL_DEPTH], xb1[SMALL_DEPTH];
+    auto multiply = [&](int c) {
+        const int steps = min(SMALL_KC / 16, nk - c * (SMALL_KC / 16));
 #pragma unroll
-        for (int i = 0; i < SMALL_DEPTH; ++i) {
-            const int k0 = min(s0 + 4 * i, nk - 1) * 16;       // a step past the end re-reads the last one and is not used
-            const uint16_t *src = k0 < a.K0 ? a.A0 + k0 : a.A1 + (k0 - a.K0);
-            xa[i] = *reinterpret_cast<const u32x4v *>(src + arow);
-            xb0[i] = *reinterpret_cast<const u32x4v *>(b0 + k0);
-            xb1[i] = *reinterpret_cast<const u32x4v *>(b1 + k0);
+        for (int i = 0; i < SMALL_KC / 64; ++i) {
+            const int s = wave + 4 * i;
+            if (s >= steps) break;                              // (uniform over the wave)
+            const uint16_t *p = tile + s * 16 + 8 * half;
+            const bf16x8 act = lds_read8(p + lr * SMALL_LROW);
+            acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read8(p + (32 + lr) * SMALL_LROW), act, acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds_read8(p + (64 + lr) * SMALL_LROW), act, acc[1], 0, 0, 0);
         }
-#pragma unroll
-        for (int i = 0; i < SMALL_DEPTH; ++i) {
-            if (s0 + 4 * i < nk) {                              // (uniform over the wave)
-                const bf16x8 act = __builtin_bit_cast(bf16x8, xa[i]);
-                acc[0] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xb0[i]), act, acc[0], 0, 0, 0);
-                acc[1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xb1[i]), act, acc[1], 0, 0, 0);
-            }
-        }
+        __syncthreads();                                        // the staged rows are done with
+    };
+    for (int c = 0; c < nchunk; c += 2) {
+        stage(f0);
+        __syncthreads();
+        if (c + 2 < nchunk) fetch(f0, c + 2);
+        multiply(c);
+        if (c + 1 >= nchunk) break;
+        stage(f1);
+        __syncthreads();
+        if (c + 3 < nchunk) fetch(f1, c + 3);
+        multiply(c + 1);
     }
     // a lane holds, for row lr, the columns t*32 + 8*grp + 4*half .. + 4
 #pragma unroll
@@ -321,7 +352,7 @@ __global__ __launch_bounds__(256) void gemm_nt_small_kernel(NtArgs a, XentArgs x
             *reinterpret_cast<float4 *>(&red[wave][lr][t * 32 + 8 * grp + 4 * half]) =
                 make_float4(acc[t][grp * 4 + 0], acc[t][grp * 4 + 1], acc[t][grp * 4 + 2], acc[t][grp * 4 + 3]);
     __syncthreads();
-    const int row = tid >> 3, c8 = (tid & 7) * 8;
+    const int row = tid >> 3;
     if (!XENT && m0 + row >= M) return;
     const bool row_ok = m0 + row < M;
     float v[8];
@@ -332,9 +363,7 @@ __global__ __launch_bounds__(256) void gemm_nt_small_kernel(NtArgs a, XentArgs x
         v[4 * h + 0] = (p0.x + p1.x) + (p2.x + p3.x); v[4 * h + 1] = (p0.y + p1.y) + (p2.y + p3.y);
         v[4 * h + 2] = (p0.z + p1.z) + (p2.z + p3.z); v[4 * h + 3] = (p0.w + p1.w) + (p2.w + p3.w);
     }
-    const int n = n0 + c8;
     if (a.bias) {
-        const float4 q0 = *reinterpret_cast<const float4 *>(a.bias + n), q1 = *reinterpret_cast<const float4 *>(a.bias + n + 4);
         v[0] += q0.x; v[1] += q0.y; v[2] += q0.z; v[3] += q0.w; v[4] += q1.x; v[5] += q1.y; v[6] += q1.z; v[7] += q1.w;
     }
     if (a.relu) {

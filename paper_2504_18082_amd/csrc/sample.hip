@@ -2217,7 +2217,7 @@ __device__ __forceinline__ void hop_transpose(const DedupArgs &a, int g, int n_d
     int32_t *list = reinterpret_cast<int32_t *>(lds) + T_SOURCES + 1;           // [T_LIST] row << 14 | source, as they come
     int32_t *sorted = list + T_LIST;                                            // [T_LIST] ... source by source
     int *wave_sum = reinterpret_cast<int *>(sorted + T_LIST);                   // [32] of the windows
-    const int tid = threadIdx.x, lane = lane_id();
+    const int tid = threadIdx.x;
     const int32_t *indices = a.indices + (int64_t)g * a.indices_stride;
     int32_t *t_indptr = a.t_indptr + (int64_t)g * a.t_indptr_stride, *t_indices = a.t_indices + (int64_t)g * a.indices_stride;
     const int range = (n_src + parts - 1) / parts;
