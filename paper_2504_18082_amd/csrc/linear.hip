@@ -1056,18 +1056,21 @@ __device__ __forceinline__ void gemm_tn_body(const TnArgs &a, uint32_t bid, uint
             }
     }
 
-    // (store_out: the reduction reads a split's sums on every XCD.  The same pass 44.4 -> 42.8 us)
     float *P = a.partial + (int64_t)split * (a.K2 + 1) * a.N;
+    // (store_out: the reduction reads a split's sums on every XCD.  The same pass 44.4 -> 42.8 us.  A row's address is scalar and
+    // the lane's place in it one 32-bit offset: with an address and two comparisons per value this was 2 of 18 us.  Widths are
+    // multiples of 32 and 64: a 32-row piece of a wave's tile is inside or outside as a whole.)
+    {
+        const int row0 = __builtin_amdgcn_readfirstlane(wk) * 64, col0 = n0 + __builtin_amdgcn_readfirstlane(wn) * 64;
+        const uint32_t lane_off = (uint32_t)(4 * half * a.N + lr) * 4u;
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        if (SUBS > 1 && i != sub) continue;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            const int n = n0 + wn * 64 + j * 32 + lr;
+        for (int i = 0; i < 2; ++i) {
+            if ((SUBS > 1 && i != sub) || row0 + i * 32 >= k_valid || col0 >= a.N) continue;
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const int kl = wk * 64 + i * 32 + 8 * (r >> 2) + 4 * half + (r & 3);
-                if (kl < k_valid && n < a.N) store_out(P + (int64_t)(k0 + kl) * a.N + n, acc[i][j][r]);
+                char *row = reinterpret_cast<char *>(P + (int64_t)(k0 + row0 + i * 32 + 8 * (r >> 2) + (r & 3)) * a.N + col0);
+#pragma unroll
+                for (int j = 0; j < 2; ++j) store_out(reinterpret_cast<float *>(row + 128 * j + lane_off), acc[i][j][r]);
             }
         }
     }
