@@ -629,7 +629,7 @@ constexpr size_t STREAM_LDS_BYTES = ((size_t)2 * STREAM_ROWS * STREAM_LROW + (si
 // changes, so no address registers are computed per tile (the compiler puts such temporaries into the registers the
 // previous tile's loads went to, and then waits for loads that have long been consumed).
 template <int KS, bool FULL, bool UNIFORM>
-__device__ __forceinline__ void nt_stream_body(const NtArgs &a, const int M, uint16_t *stream_lds, const bf16x8 (&wf)[2][KS])
+__device__ __forceinline__ void nt_stream_body(const NtArgs &a, const int M, uint16_t *stream_lds, u32x4v (&wraw)[KS])
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int half = lane >> 5, lr = lane & 31;
@@ -683,6 +683,36 @@ __device__ __forceinline__ void nt_stream_body(const NtArgs &a, const int M, uin
 #pragma unroll
         for (int i = 0; i < 8; ++i) *reinterpret_cast<u32x4v *>(&As[(8 * i + srow) * STREAM_LROW + kp * 8]) = r[i];
     };
+    const int step = (int)gridDim.x;
+    int t = (int)blockIdx.x;
+    u32x4v ra[8], rb[8];
+    fetch(ra, t);
+    fetch(rb, t + step);
+    // The wave's weights, which came as whole rows, through its quarter of the activations' buffers into registers: columns
+    // 64 wave + 32 cb + lr, eight k from 16 ks + 8 half on.
+    bf16x8 wf[2][KS];
+    {
+        uint16_t *w = stream_lds + wave * 32 * STREAM_LROW;
+        static_assert(4 * 32 == 2 * STREAM_ROWS, "32 weight rows per wave fill the two buffers");
+        const int wrow = lane / (2 * KS), wcol = lane % (2 * KS) * 8;
+        const u32x4v zero = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int cb = 0; cb < 2; ++cb) {
+#pragma unroll
+            for (int i = 0; i < KS; ++i)
+                *reinterpret_cast<u32x4v *>(&w[(i * (32 / KS) + wrow) * STREAM_LROW + wcol]) = wcol < K ? wraw[i] : zero;
+            if (cb == 0) {
+#pragma unroll
+                for (int i = 0; i < KS; ++i)
+                    wraw[i] = *reinterpret_cast<const u32x4v *>(a.B + (int64_t)(64 * wave + (KS + i) * (32 / KS) + wrow) * a.K + (wcol < a.K ? wcol : 0));
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) wf[cb][ks] = lds_read8(&w[lr * STREAM_LROW + ks * 16 + 8 * half]);
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        }
+        __syncthreads();
+    }
     const float floor_v = a.relu ? 0.f : -INFINITY;
     // Two sets of accumulators: while the MFMAs of a tile fill one, the other -- the tile before -- is converted and
     // written to the wave's LDS patch, a sixteenth (K <= 128: an eighth) per K step, in the shadow of that step's MFMAs;
@@ -749,11 +779,6 @@ __device__ __forceinline__ void nt_stream_body(const NtArgs &a, const int M, uin
         for (int piece = 0; piece < 16; ++piece) convert_piece(acc, piece);
     };
 
-    const int step = (int)gridDim.x;
-    int t = (int)blockIdx.x;
-    u32x4v ra[8], rb[8];
-    fetch(ra, t);
-    fetch(rb, t + step);
     if (tid < WIDE_N / 4)
         *reinterpret_cast<float4 *>(&bias_s[tid * 4]) = a.bias ? *reinterpret_cast<const float4 *>(a.bias + tid * 4) : make_float4(0.f, 0.f, 0.f, 0.f);
     if (!mine) {                 // columns from K on stay zero in both buffers
@@ -799,31 +824,25 @@ __device__ __forceinline__ void nt_stream_body(const NtArgs &a, const int M, uin
 }
 
 // The wave's weights are requested before the row count is read (they do not depend on it): the two round trips to
-// memory overlap.  Columns 64 wave + 32 cb + lr, eight k from 16 ks + 8 half on (K is a multiple of 8).
+// memory overlap.  They are requested as whole rows of the transposed weights (a load covers two to four of them) and take their
+// places in the body: as MFMA fragments, 16 bytes of 32 rows per load, they kept the address unit busy for 4.2 us of 18, and the
+// first activations were requested behind them.
 template <int KS>
 __device__ __forceinline__ void nt_stream_run(const NtArgs &a, uint16_t *stream_lds)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int half = lane >> 5, lr = lane & 31;
-    const int K = a.K;
-    bf16x8 wf[2][KS];
+    const int wrow = lane / (2 * KS), wcol = lane % (2 * KS) * 8;      // 2 KS pieces of 16 bytes per row, 32 / KS rows per load
+    u32x4v wraw[KS];
 #pragma unroll
-    for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-        for (int ks = 0; ks < KS; ++ks) {
-            const int k = ks * 16 + 8 * half;
-            const uint16_t *src = a.B + (int64_t)(64 * wave + 32 * cb + lr) * K + (k < K ? k : 0);
-            const u32x4v x = *reinterpret_cast<const u32x4v *>(src);
-            const u32x4v zero = {0u, 0u, 0u, 0u};
-            wf[cb][ks] = __builtin_bit_cast(bf16x8, k < K ? x : zero);
-        }
+    for (int i = 0; i < KS; ++i)
+        wraw[i] = *reinterpret_cast<const u32x4v *>(a.B + (int64_t)(64 * wave + i * (32 / KS) + wrow) * a.K + (wcol < a.K ? wcol : 0));
     asm volatile("" ::: "memory");      // (keeps the loads above from being moved below the branch on the row count)
     const int M = min(a.hdr[CR_HDR_N_DST], a.max_rows);
     if ((int)blockIdx.x * STREAM_ROWS >= M) return;
     const bool uniform = a.K0 == a.K || a.K0 % 128 == 0;
-    if (M < STREAM_ROWS) nt_stream_body<KS, false, false>(a, M, stream_lds, wf);
-    else if (uniform) nt_stream_body<KS, true, true>(a, M, stream_lds, wf);
-    else nt_stream_body<KS, true, false>(a, M, stream_lds, wf);
+    if (M < STREAM_ROWS) nt_stream_body<KS, false, false>(a, M, stream_lds, wraw);
+    else if (uniform) nt_stream_body<KS, true, true>(a, M, stream_lds, wraw);
+    else nt_stream_body<KS, true, false>(a, M, stream_lds, wraw);
 }
 
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(1, 1))) void gemm_nt_stream_kernel(NtArgs a)
