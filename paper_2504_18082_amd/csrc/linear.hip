@@ -141,11 +141,15 @@ __device__ __forceinline__ void gemm_nt_body(const NtArgs &a, uint32_t bid, uint
     const int64_t ga1 = (int64_t)min(m0 + a_row1, M - 1) * a.lda;
     const uint16_t *gb = a.B + (int64_t)(n0 + (tid >> 2)) * a.K + kc * 8;
 
+    // (the accumulators start from the bias, which travels with the first chunk; added behind the loop it was a round trip of its own)
     f32x16 acc[NTILES];
 #pragma unroll
     for (int t = 0; t < NTILES; ++t)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[t][r] = 0.f;
+        for (int grp = 0; grp < 4; ++grp) {
+            const float4 bq = a.bias ? *reinterpret_cast<const float4 *>(a.bias + n0 + t * 32 + 8 * grp + 4 * half) : make_float4(0.f, 0.f, 0.f, 0.f);
+            acc[t][grp * 4 + 0] = bq.x; acc[t][grp * 4 + 1] = bq.y; acc[t][grp * 4 + 2] = bq.z; acc[t][grp * 4 + 3] = bq.w;
+        }
 
     const int nsteps = a.K / 32;
     int buf = 0;
@@ -180,10 +184,8 @@ __device__ __forceinline__ void gemm_nt_body(const NtArgs &a, uint32_t bid, uint
     for (int t = 0; t < 2; ++t)
 #pragma unroll
         for (int grp = 0; grp < 4; ++grp) {
-            const int n = n0 + t * 32 + 8 * grp + 4 * half;
-            const float4 bq = a.bias ? *reinterpret_cast<const float4 *>(a.bias + n) : make_float4(0.f, 0.f, 0.f, 0.f);
-            v[t][grp][0] = acc[t][grp * 4 + 0] + bq.x; v[t][grp][1] = acc[t][grp * 4 + 1] + bq.y;
-            v[t][grp][2] = acc[t][grp * 4 + 2] + bq.z; v[t][grp][3] = acc[t][grp * 4 + 3] + bq.w;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) v[t][grp][i] = acc[t][grp * 4 + i];
             if (a.relu) {
 #pragma unroll
                 for (int i = 0; i < 4; ++i) v[t][grp][i] = v[t][grp][i] < 0.f ? 0.f : v[t][grp][i];
