@@ -640,11 +640,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 //                  kept and the pool is the inter-community slots with m = fanout - n_in (0 in strict mode).
 // The kept slots are those below a bound T with exactly m words of the pool below it.  T is found by search: it is moved
 // inside a bracket to where evenly spread words would put it, and the words below it are counted per row with four ballots
-// and population counts under the row's mask of lanes (about 40 instructions a step, no LDS; simulated on random words: 3 to 4
+// and population counts under the row's mask of lanes (about 30 instructions a step, no LDS; simulated on random words: 3 to 4
 // steps a row, 5 to 6 for the slowest row of a pass).  The kernel is bound by vector instruction issue; ranking every slot
 // against a list of its row's candidates in LDS, which this replaces, took 426 M vector instructions in the input-side hop of a
 // products-like group of 32 batches against 312 M.  Selection of that group (uniform, three hops): 792 -> 630 us; of a
-// papers-like one 910 -> 804 us; weighted, a reddit-like group of 8: 222 -> 193 us.  A row without such a bound in SEARCH_STEPS steps (equal words at the boundary) is
+// papers-like one 910 -> 804 us; weighted, a reddit-like group of 8: 222 -> 193 us.  Then three of a step's ballots added up as masks,
+// the bracket's counts kept as distances and a quad's ids in one load: 647 -> 622 us for the first of these.  A row without such a bound in SEARCH_STEPS steps (equal words at the boundary) is
 // redone with (word, slot) pairs compared in full, so the result is exact in every case.
 //
 // Weighted sampling (0.5 < p < 1) takes the same passes with single-precision keys: approx_clock(r) * m_class, compared
@@ -687,6 +688,14 @@ constexpr int QUAD_FILL_WAVES = 8192;    // until there are this many waves (eig
 constexpr int QUAD_MAX_DEG = 4 * WAVE;   // longest row a pass holds
 constexpr int SEARCH_STEPS = 24;         // bounds tried before a row is ranked in full
 
+// acc + number of set bits, in one instruction (the compiler takes two and an addition apart)
+__device__ __forceinline__ uint32_t bits_onto(uint32_t bits, uint32_t acc)
+{
+    uint32_t n;
+    asm("v_bcnt_u32_b32 %0, %1, %2" : "=v"(n) : "v"(bits), "v"(acc));
+    return n;
+}
+
 struct alignas(16) QuadRow {
     int32_t v, deg;                      // node, degree
     int64_t base;                        // first adjacency entry
@@ -713,13 +722,19 @@ __device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int ro
 
     // the row's lanes of this pass; counts over a row are population counts of ballots under this mask: no LDS round trips
     const uint64_t row_lanes = active ? (nq >= WAVE ? ~0ull : ((1ull << nq) - 1ull) << first) : 0ull;
-    auto count4 = [&](bool f0, bool f1, bool f2, bool f3) -> int {          // set flags in the whole row
+    // (three of the four ballots are first added up bit by bit, in scalar registers: two counted bits fewer per lane)
+    const uint32_t lanes_lo = (uint32_t)row_lanes, lanes_hi = (uint32_t)(row_lanes >> 32);
+    auto count4_onto = [&](int base, bool f0, bool f1, bool f2, bool f3) -> int {          // base + set flags in the whole row
         const uint64_t b0 = __ballot(f0), b1 = __ballot(f1), b2 = __ballot(f2), b3 = __ballot(f3);
-        return __popcll(b0 & row_lanes) + __popcll(b1 & row_lanes) + __popcll(b2 & row_lanes) + __popcll(b3 & row_lanes);
+        const uint64_t half = b0 ^ b1, ones = half ^ b2, twos = (b0 & b1) | (half & b2);
+        auto onto = [&](uint64_t b, uint32_t acc) { return bits_onto((uint32_t)(b >> 32) & lanes_hi, bits_onto((uint32_t)b & lanes_lo, acc)); };
+        return (int)((onto(twos, 0u) << 1) + onto(b3, onto(ones, (uint32_t)base)));
     };
+    auto count4 = [&](bool f0, bool f1, bool f2, bool f3) -> int { return count4_onto(0, f0, f1, f2, f3); };
     auto before4 = [&](bool f0, bool f1, bool f2, bool f3) -> int {         // ... and in the row's lanes before this one
         const uint64_t b0 = __ballot(f0), b1 = __ballot(f1), b2 = __ballot(f2), b3 = __ballot(f3);
-        return lanes_below(b3 & row_lanes, lanes_below(b2 & row_lanes, lanes_below(b1 & row_lanes, lanes_below(b0 & row_lanes, 0))));
+        const uint64_t half = b0 ^ b1, ones = half ^ b2, twos = (b0 & b1) | (half & b2);
+        return 2 * lanes_below(twos & row_lanes, 0) + lanes_below(b3 & row_lanes, lanes_below(ones & row_lanes, 0));
     };
     auto count_bits = [&](uint32_t m4) { return count4(m4 & 1u, m4 & 2u, m4 & 4u, m4 & 8u); };
     auto before_bits = [&](uint32_t m4) { return before4(m4 & 1u, m4 & 2u, m4 & 4u, m4 & 8u); };
@@ -766,18 +781,17 @@ __device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int ro
         const uint32_t none = ~(pool | take);
 #pragma unroll
         for (int i = 0; i < 4; ++i) kw[i] = (kw[i] & (uint32_t)((int32_t)(pool << (31 - i)) >> 31)) | (uint32_t)((int32_t)(none << (31 - i)) >> 31);
-        // A bound T with `expect` words of the row below it: T is moved inside a bracket (lo: cl words below, hi: ch) to where
-        // evenly spread words would put it.  x runs over [0, 1] (weighted: the bound's place in a single exponential law of the
-        // row's mean rate); float arithmetic only steers T, the counts are what decides.  A row that is done has lo = hi and
-        // keeps its T.
-        const float want = (float)expect + 0.5f;
-        float lo = 0.0f, cl = MODE == 1 ? (float)(expect - m) : 0.0f, hi = 1.0f, ch = cl + (float)P;
-        float to_key = 4294967296.0f;
+        // A bound T with `expect` words of the row below it: T is moved inside a bracket to where evenly spread words would put it
+        // (lo, hi: the bracket's ends; at_lo, at_hi: how many words, and half a word, their counts are off).  x is T itself
+        // (weighted: the bound's place in a single exponential law of the row's mean rate); float arithmetic only steers T, the
+        // counts are what decides.  A row that is done has lo = hi and keeps its T.
+        float lo = 0.0f, at_lo = (float)m + 0.5f, hi = 4294967296.0f, at_hi = (float)(P - m) + 0.5f;
+        float to_key = 1.0f;
         if (MODE == 2) {
             // the law's rate: the slots' mean rate for the first of them, that of the mean waiting time for the last (with the
             // mean rate alone, rows of few slots more than the fanout take 8 to 20 steps at p = 0.97, with this 3 to 5)
             const float fi = (float)n_in, fo = (float)(P - n_in), w_in = (float)a.q_out, w_out = (float)a.q_in;
-            const float fr = want * __builtin_amdgcn_rcpf((float)P + 1.0f), p_f = (float)P;
+            const float fr = at_lo * __builtin_amdgcn_rcpf((float)P + 1.0f), p_f = (float)P;
             const float rate = (fi * __builtin_amdgcn_rcpf(w_in) + fo * __builtin_amdgcn_rcpf(w_out)) * __builtin_amdgcn_rcpf(p_f);
             const float late = p_f * __builtin_amdgcn_rcpf(fi * w_in + fo * w_out);
             to_key = __builtin_amdgcn_rcpf(rate + fr * (late - rate));
@@ -786,16 +800,16 @@ __device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int ro
         uint32_t T = 0u;
         uint64_t open = __ballot(ranked);
         for (int step = 0; step < SEARCH_STEPS && open != 0; ++step) {
-            const float x = lo + (hi - lo) * ((want - cl) * __builtin_amdgcn_rcpf(ch - cl + 1.0f));
-            T = MODE == 2 ? __float_as_uint(fmaxf(0.0f, -__builtin_amdgcn_logf(x) * to_key)) : (uint32_t)(x * to_key);
-            const int c = count4(kw[0] < T, kw[1] < T, kw[2] < T, kw[3] < T);
-            const float cf = (float)c;
-            const bool low = c <= expect, high = c >= expect;
-            lo = low ? x : lo;
-            cl = low ? cf : cl;
-            hi = high ? x : hi;
-            ch = high ? cf : ch;
-            open &= ~__ballot(low && high);
+            const float x = lo + (hi - lo) * (at_lo * __builtin_amdgcn_rcpf(at_lo + at_hi));
+            T = MODE == 2 ? __float_as_uint(fmaxf(0.0f, -__builtin_amdgcn_logf(x) * to_key)) : (uint32_t)x;
+            const int off = count4_onto(-expect, kw[0] < T, kw[1] < T, kw[2] < T, kw[3] < T);
+            const float at = 0.5f + __builtin_fabsf((float)off);
+            const bool above = off > 0, below = off < 0;
+            lo = above ? lo : x;
+            at_lo = above ? at_lo : at;
+            hi = below ? hi : x;
+            at_hi = below ? at_hi : at;
+            open &= __ballot(above) | __ballot(below);
         }
         ok = ((open >> lane) & 1u) == 0;
         T = ranked ? T : 1u;
@@ -883,10 +897,19 @@ __device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int ro
     }
     if (active && ok) {
         const int32_t *from = a.g_indices + R.base + jb;
-        int32_t id[4];
+        int32_t id[4] = {0, 0, 0, 0};
+        if (R.base + jb + 4 <= a.n_entries) {            // the quad's ids in one load (four bytes of alignment are enough for it)
+            if (emit) {
+                struct __attribute__((packed, aligned(4))) Quad { int32_t x[4]; };
+                const Quad v = *reinterpret_cast<const Quad *>(from);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            if ((emit >> i) & 1u) id[i] = from[i];
+                for (int i = 0; i < 4; ++i) id[i] = v.x[i];
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if ((emit >> i) & 1u) id[i] = from[i];
+        }
         int32_t *to = out + R.out + epos;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
