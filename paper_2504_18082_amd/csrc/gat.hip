@@ -306,7 +306,7 @@ __global__ __launch_bounds__(256) void gat_aggregate_fwd_kernel(const int32_t *_
                 const float wk = gw[(min(j + k, e - 1) - b) * s.heads];
                 const float w = j + k < e ? wk : 0.f;
                 float x[8];
-                unpack_bf16x8(r[k], li.mask, x);
+                unpack_bf16x8(r[k], ~0u, x);              // (a lane past the row's end stores nothing)
 #pragma unroll
                 for (int i = 0; i < 8; ++i) acc[i] += w * x[i];
             }
@@ -409,7 +409,7 @@ __global__ __launch_bounds__(256) void gat_bwd_dst_kernel(const int32_t *__restr
 #pragma unroll
             for (int k = 0; k < U; ++k) {
                 float x[8];
-                unpack_bf16x8(r[k], li.mask, x);
+                unpack_bf16x8(r[k], ~0u, x);              // (a lane past the row's end has g = 0)
                 da[k] = dot8(g, x);
             }
             head_sum_n<U>(da, s.LH);
@@ -482,7 +482,6 @@ __global__ __launch_bounds__(256) void gat_bwd_src_kernel(const int32_t *__restr
             for (int k = 0; k < U; ++k) nv[k] = t_indices[max(min(nb + k, ne - 1), 0)];
             float zr[8];
             unpack_bf16x8(z_raw, li.mask, zr);
-            const float der = u < n_dst ? der_any : 0.f;
             int v[U];
 #pragma unroll
             for (int k = 0; k < U; ++k) v[k] = v0[k];
@@ -493,7 +492,7 @@ __global__ __launch_bounds__(256) void gat_bwd_src_kernel(const int32_t *__restr
 #pragma unroll
                 for (int k = 0; k < U; ++k) {
                     st[k] = stat[(int64_t)v[k] * s.heads + li.h];
-                    load_bf16x8(g_b + (int64_t)v[k] * s.ld + li.colc, li.mask, g[k]);
+                    load_bf16x8(g_b + (int64_t)v[k] * s.ld + li.colc, g[k]);      // (a lane past the row's end has z = 0 and stores nothing)
                 }
 #pragma unroll
                 for (int k = 0; k < U; ++k) v[k] = t_indices[min(j + U + k, e - 1)];      // the next chunk, if any
@@ -514,9 +513,15 @@ __global__ __launch_bounds__(256) void gat_bwd_src_kernel(const int32_t *__restr
             float dz[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
-                dz[i] = acc[i] + del * al[i] + der * ar[i];
+                dz[i] = acc[i] + del * al[i];
                 pal[i] += del * zr[i];
-                par[i] += der * zr[i];
+            }
+            if (u < n_dst) {                                    // (the destinations come first: most waves have none)
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    dz[i] += der_any * ar[i];
+                    par[i] += der_any * zr[i];
+                }
             }
             if (li.live) store_bf16x8(dz_bf16 + (int64_t)u * s.ld + li.col, dz);
             b = nb;
