@@ -257,26 +257,38 @@ __device__ __forceinline__ void select_big_row(const SelectArgs &a, int g, int r
 // general path, which needs no threshold).
 constexpr int CAND_CAP = 128;
 
-// rk[i] += (w[i] < k) for four words at once.  Written out by hand so that the four comparisons land in four different
-// scalar register pairs and the four add-with-carry instructions follow them: the compiler routes every comparison
-// through VCC and has to wait two cycles between each comparison and its add (three instructions lie between a
-// comparison and the add that reads its result here, more than the two wait states the hardware asks for).
-__device__ __forceinline__ void rank4_below(uint32_t k, const uint32_t (&w)[4], int (&rk)[4])
+// sum over the wave, the same in all lanes: operand modifiers inside rows of sixteen lanes, four lane reads across them (no LDS)
+__device__ __forceinline__ int wave_sum(int x)
 {
-    uint64_t s0, s1, s2, s3;
-    asm("v_cmp_gt_u32_e64 %4, %8, %9\n\t"
-        "v_cmp_gt_u32_e64 %5, %8, %10\n\t"
-        "v_cmp_gt_u32_e64 %6, %8, %11\n\t"
-        "v_cmp_gt_u32_e64 %7, %8, %12\n\t"
-        "v_addc_co_u32_e64 %0, %4, 0, %0, %4\n\t"
-        "v_addc_co_u32_e64 %1, %5, 0, %1, %5\n\t"
-        "v_addc_co_u32_e64 %2, %6, 0, %2, %6\n\t"
-        "v_addc_co_u32_e64 %3, %7, 0, %3, %7"
-        : "+v"(rk[0]), "+v"(rk[1]), "+v"(rk[2]), "+v"(rk[3]), "=&s"(s0), "=&s"(s1), "=&s"(s2), "=&s"(s3)
-        : "v"(k), "v"(w[0]), "v"(w[1]), "v"(w[2]), "v"(w[3]));
+    x += __builtin_amdgcn_update_dpp(0, x, 0xB1, 0xF, 0xF, true);      // quad [1 0 3 2]
+    x += __builtin_amdgcn_update_dpp(0, x, 0x4E, 0xF, 0xF, true);      // quad [2 3 0 1]
+    x += __builtin_amdgcn_update_dpp(0, x, 0x141, 0xF, 0xF, true);     // half mirror
+    x += __builtin_amdgcn_update_dpp(0, x, 0x140, 0xF, 0xF, true);     // mirror
+    return (__builtin_amdgcn_readlane(x, 0) + __builtin_amdgcn_readlane(x, 16)) + (__builtin_amdgcn_readlane(x, 32) + __builtin_amdgcn_readlane(x, 48));
 }
 
-//
+// (Rows of more than 256 neighbours ranked each of their ~50 to 100 candidates against all of them, about 150 issue slots, and when
+// weighted reduced four extremes over the wave by shuffles.  A bound found by search, and one look for keys too near to it, in
+// their place: reddit-like, 8 batches, p = 0.9, the call 343 -> 317 us; products-like, 32 batches, uniform 867 -> 835,
+// p = 0.9 1309 -> 1236; papers-like 931 -> 895.)
+// A bound with exactly k of the wave's words below it, searched as in the passes of short rows (see quad_pass): moved inside
+// (0, hi) to where evenly spread words would put it.  count(T): words below the bound that x stands for; to_word(x): that bound.
+// All arguments and results are the same in every lane.  false: no such bound found (equal words around it, or too many steps).
+template <typename ToWord, typename Count>
+__device__ __forceinline__ bool search_bound(int n, int k, float hi, ToWord &&to_word, Count &&count, uint32_t &T)
+{
+    float lo = 0.0f, at_lo = (float)k + 0.5f, at_hi = (float)(n - k) + 0.5f;
+    for (int step = 0; step < 24; ++step) {
+        const float x = lo + (hi - lo) * (at_lo * __builtin_amdgcn_rcpf(at_lo + at_hi));
+        T = to_word(x);
+        const int off = count(T) - k;
+        if (off == 0) return true;
+        if (off < 0) { lo = x; at_lo = 0.5f - (float)off; }
+        else { hi = x; at_hi = 0.5f + (float)off; }
+    }
+    return false;
+}
+
 // INTRA_ONLY is the same for p = 1 when the graph carries its edge-class bits: the pool is the row's
 // intra-community slots (counted from the bits first); with fewer of them than the fanout the caller's general
 // path fills up with inter-community ones.
@@ -297,8 +309,7 @@ __device__ __forceinline__ bool select_big_row_filtered(const SelectArgs &a, int
             if (w == w_last && (e_last & 31)) bits &= (1u << (e_last & 31)) - 1u;
             n_in += __popc(bits);
         }
-#pragma unroll
-        for (int o = 32; o; o >>= 1) n_in += __shfl_xor(n_in, o);
+        n_in = wave_sum(n_in);
         if (n_in < k) return false;
         pool = n_in;
     }
@@ -355,32 +366,17 @@ __device__ __forceinline__ bool select_big_row_filtered(const SelectArgs &a, int
     // (a word of all ones is never below the threshold: with every slot wanted, leave such a row to the general path)
     if (keep_all && n != pool) return false;
     if (n < k) return false;
-    if (lane < 4) ckey[n + lane] = ~0u;            // pad the words to a multiple of four with the largest one
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
     // candidate t sits at index t in slot order; a lane owns candidates lane and lane + 64.  Words only are compared: with
-    // equal words at the boundary the kept count is off and the caller's general path takes the row.
+    // equal words at the boundary there is no bound, and the caller's general path takes the row.
     const bool have0 = lane < n, have1 = lane + WAVE < n;
-    const uint32_t w0 = ckey[min(lane, n - 1)], w1 = ckey[min(lane + WAVE, n - 1)];
-    int ra[4] = {0, 0, 0, 0}, rb[4] = {0, 0, 0, 0};
-    if (n <= WAVE) {
-        for (int t0 = 0; t0 < n; t0 += 4) {
-            const uint4 kt = *reinterpret_cast<const uint4 *>(ckey + t0);
-            const uint32_t ks[4] = {kt.x, kt.y, kt.z, kt.w};
-            rank4_below(w0, ks, ra);
-        }
-    } else {
-        for (int t0 = 0; t0 < n; t0 += 4) {
-            const uint4 kt = *reinterpret_cast<const uint4 *>(ckey + t0);
-            const uint32_t ks[4] = {kt.x, kt.y, kt.z, kt.w};
-            rank4_below(w0, ks, ra);
-            rank4_below(w1, ks, rb);
-        }
-    }
-    const int r0 = ra[0] + ra[1] + ra[2] + ra[3], r1 = rb[0] + rb[1] + rb[2] + rb[3];
-    const bool s0 = have0 && r0 < k, s1 = have1 && r1 < k;
+    const uint32_t w0 = have0 ? ckey[lane] : ~0u, w1 = have1 ? ckey[lane + WAVE] : ~0u;
+    uint32_t T;
+    const bool exact = search_bound(n, k, thr_f, [](float x) { return (uint32_t)x; },
+                                    [&](uint32_t t) { return (int)__popcll(__ballot(w0 < t)) + (n > WAVE ? (int)__popcll(__ballot(w1 < t)) : 0); }, T);
+    const bool s0 = w0 < T, s1 = w1 < T;
     const uint64_t m0 = __ballot(s0), m1 = __ballot(s1);
-    const bool exact = __popcll(m0) + __popcll(m1) == k;
     if (exact) {
         int32_t *sel_row = sel_row_ptr(a, g, row);
         if (s0) sel_row[__popcll(m0 & lt_mask)] = a.g_indices[base + cslot[lane]];
@@ -944,14 +940,13 @@ __device__ __forceinline__ bool select_big_row_weighted_f32(const SelectArgs &a,
         if (w == w_last && (e_last & 31)) bits &= (1u << (e_last & 31)) - 1u;
         n_in += __popc(bits);
     }
-#pragma unroll
-    for (int o = 32; o; o >>= 1) n_in += __shfl_xor(n_in, o);
+    n_in = wave_sum(n_in);
     const int n_out = deg - n_in;
     const float m_in = (float)a.q_out, m_out = (float)a.q_in;       // an intra-community slot's clock is scaled by 1 - p
 
     // candidate iff r >= t_class; lo_non: the smallest key a slot below its class's threshold can have
     uint32_t t_in = 0u, t_out = 0u;
-    float non_in = INFINITY, non_out = INFINITY;
+    float non_in = INFINITY, non_out = INFINITY, most = INFINITY;      // most: the candidates' keys end about here
     if ((int)a.cand_target < deg) {
         const float ln2 = 0.69314718f, target = (float)a.cand_target, fi = (float)n_in, fo = (float)n_out;
         const float s_in = __builtin_amdgcn_rcpf(m_in), s_out = __builtin_amdgcn_rcpf(m_out);
@@ -963,6 +958,7 @@ __device__ __forceinline__ bool select_big_row_weighted_f32(const SelectArgs &a,
             const float gd = ln2 * (fi * s_in * ei + fo * s_out * eo);
             if (gd > 0.0f) kp -= gv / gd;
         }
+        most = kp;
         const float pi = __builtin_amdgcn_exp2f(-kp * s_in) * 4294967296.0f, po = __builtin_amdgcn_exp2f(-kp * s_out) * 4294967296.0f;
         t_in = pi >= 4294967040.0f ? 0xFFFFFFFFu : (uint32_t)(pi > 0.0f ? pi : 0.0f);
         t_out = po >= 4294967040.0f ? 0xFFFFFFFFu : (uint32_t)(po > 0.0f ? po : 0.0f);
@@ -1012,47 +1008,42 @@ __device__ __forceinline__ bool select_big_row_weighted_f32(const SelectArgs &a,
     for (; j0 + 4 * WAVE <= deg; j0 += 4 * WAVE)
         if (!stretch(j0, std::false_type{})) return false;
     if (j0 < deg && !stretch(j0, std::true_type{})) return false;
-    if (n < k) return false;
+    if (n < k || !(most < INFINITY)) return false;
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
 
     // candidate t sits at index t in slot order; a lane owns candidates lane and lane + 64 and turns their random words
     // into keys
-    const bool have0 = lane < n, have1 = lane + WAVE < n;
+    const bool have0 = lane < n, have1 = lane + WAVE < n, two = n > WAVE;
     const uint32_t q0 = cslot[min(lane, n - 1)], q1 = cslot[min(lane + WAVE, n - 1)];
     const bool in0 = q0 >> 31, in1 = q1 >> 31;
-    const uint32_t w0 = __float_as_uint(approx_clock(ckey[min(lane, n - 1)]) * (in0 ? m_in : m_out));
+    const uint32_t w0 = have0 ? __float_as_uint(approx_clock(ckey[lane]) * (in0 ? m_in : m_out)) : 0x7F800000u;
     uint32_t w1 = 0x7F800000u;
-    if (n > WAVE) w1 = __float_as_uint(approx_clock(ckey[min(lane + WAVE, n - 1)]) * (in1 ? m_in : m_out));
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // every lane has read its words
-    if (have0) ckey[lane] = w0;
-    if (have1) ckey[lane + WAVE] = w1;
-    if (lane < 4) ckey[n + lane] = ~0u;            // pad the keys to a multiple of four with the largest pattern
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    int ra[4] = {0, 0, 0, 0}, rb[4] = {0, 0, 0, 0};
-    for (int t0 = 0; t0 < n; t0 += 4) {
-        const uint4 kt = *reinterpret_cast<const uint4 *>(ckey + t0);
-        const uint32_t ks[4] = {kt.x, kt.y, kt.z, kt.w};
-        rank4_below(w0, ks, ra);
-        if (n > WAVE) rank4_below(w1, ks, rb);
+    if (two && have1) w1 = __float_as_uint(approx_clock(ckey[lane + WAVE]) * (in1 ? m_in : m_out));
+    // A bound with k candidates below it, and no key -- a candidate's, or one that a filtered-out slot can have -- within its error
+    // bound of it: then every kept slot's exact key is below every other's.  A row that fails tries again a few bounds higher
+    // and lower, as in the passes of short rows.
+    auto below = [&](uint32_t t) { return (int)__popcll(__ballot(w0 < t)) + (two ? (int)__popcll(__ballot(w1 < t)) : 0); };
+    auto apart = [&](float t) -> bool {
+        const float rel = t * (CLOCK_ERR_REL + 0x1p-20f);
+        const float near_in = rel + (CLOCK_ERR_ABS + 0.25f) * 0x1p-24f * m_in, near_out = rel + (CLOCK_ERR_ABS + 0.25f) * 0x1p-24f * m_out;
+        const bool near0 = __builtin_fabsf(__uint_as_float(w0) - t) <= (in0 ? near_in : near_out);
+        const bool near1 = __builtin_fabsf(__uint_as_float(w1) - t) <= (in1 ? near_in : near_out);
+        return __ballot(near0 || near1) == 0 && keys_apart(t, m_in, non_in, m_in) && keys_apart(t, m_out, non_out, m_out);
+    };
+    uint32_t T;
+    bool exact = search_bound(n, k, most, [](float x) { return __float_as_uint(x); }, below, T);
+    if (exact && !apart(__uint_as_float(T))) {
+        const float tf = __uint_as_float(T);
+        const float shift = 2.5f * (tf * (CLOCK_ERR_REL + 0x1p-20f) + (CLOCK_ERR_ABS + 0.25f) * 0x1p-24f * fmaxf(m_in, m_out));
+        exact = false;
+#pragma unroll 1
+        for (int i = 0; i < 2 && !exact; ++i) {
+            T = __float_as_uint(fmaxf(0.0f, i ? tf - shift : tf + shift));
+            exact = below(T) == k && apart(__uint_as_float(T));
+        }
     }
-    const int r0 = ra[0] + ra[1] + ra[2] + ra[3], r1 = rb[0] + rb[1] + rb[2] + rb[3];
-    const bool s0 = have0 && r0 < k, s1 = have1 && r1 < k;
+    const bool s0 = w0 < T, s1 = w1 < T;
     const uint64_t m0 = __ballot(s0), m1 = __ballot(s1);
-    // largest kept key and smallest candidate key left out, per class (x: intra, y: inter)
-    uint32_t hi_x = max((s0 && in0) ? w0 : 0u, (s1 && in1) ? w1 : 0u), hi_y = max((s0 && !in0) ? w0 : 0u, (s1 && !in1) ? w1 : 0u);
-    uint32_t lo_x = min((have0 && !s0 && in0) ? w0 : 0x7F800000u, (have1 && !s1 && in1) ? w1 : 0x7F800000u);
-    uint32_t lo_y = min((have0 && !s0 && !in0) ? w0 : 0x7F800000u, (have1 && !s1 && !in1) ? w1 : 0x7F800000u);
-#pragma unroll
-    for (int o = 32; o; o >>= 1) {
-        hi_x = max(hi_x, (uint32_t)__shfl_xor((int)hi_x, o));
-        hi_y = max(hi_y, (uint32_t)__shfl_xor((int)hi_y, o));
-        lo_x = min(lo_x, (uint32_t)__shfl_xor((int)lo_x, o));
-        lo_y = min(lo_y, (uint32_t)__shfl_xor((int)lo_y, o));
-    }
-    const float hx = __uint_as_float(hi_x), hy = __uint_as_float(hi_y);
-    const float lx = fminf(__uint_as_float(lo_x), non_in), ly = fminf(__uint_as_float(lo_y), non_out);
-    const bool exact = __popcll(m0) + __popcll(m1) == k && keys_apart(hx, m_in, lx, m_in) && keys_apart(hx, m_in, ly, m_out) &&
-                       keys_apart(hy, m_out, lx, m_in) && keys_apart(hy, m_out, ly, m_out);
     if (exact) {
         int32_t *sel_row = sel_row_ptr(a, g, row);
         if (s0) sel_row[__popcll(m0 & lt_mask)] = a.g_indices[base + (q0 & 0x7FFFFFFFu)];

@@ -247,3 +247,23 @@ def test_rows_just_above_the_fanout(torch_mod, fanout, p):
         return np.concatenate([rng.choice(own, near, replace=False), rng.choice(other, deg - near, replace=False)])
 
     check(torch_mod, fixed_rows(n, rows), n - 3, 1000, [fanout], p, f"rows of about {fanout} neighbours, p={p}")
+
+
+# rows longer than a pass: one slot more than a pass, whole stretches and one slot more, candidates of one and of two per lane
+@pytest.mark.parametrize("p", [0.5, 0.51, 0.9, 0.97, 1.0])
+@pytest.mark.parametrize("fanout", [1, 25, 64])
+def test_long_rows(torch_mod, fanout, p):
+    rng = np.random.default_rng(fanout)
+    n, degrees = 4096, [257, 300, 511, 512, 513, 1000, 3000]
+    home = np.arange(n) // (n // 4 + 1)
+
+    def rows(i):
+        if i >= 280:
+            return rng.choice(n, i % 3, replace=False)
+        deg = degrees[i % len(degrees)]
+        own, other = np.flatnonzero(home == home[i]), np.flatnonzero(home != home[i])
+        near = min(len(own), [deg // 2, fanout, fanout - 1, deg - 1, 0][i // len(degrees) % 5])      # how many lie in the node's own community
+        near = max(near, deg - len(other))
+        return np.concatenate([rng.choice(own, near, replace=False), rng.choice(other, deg - near, replace=False)])
+
+    check(torch_mod, fixed_rows(n, rows), n - 3, 1000, [fanout], p, f"long rows, fanout {fanout}, p={p}")
