@@ -33,6 +33,34 @@ __device__ __forceinline__ uint32_t exp_clock_q24(uint32_t r)
     return ((uint32_t)(33 - t) << 24) - frac;
 }
 
+struct ScanArgs {
+    const int32_t *prev_hdr;
+    int64_t n_roots_total;
+    int32_t batch_size;
+    int32_t mode;          // 0: row counts -> indptr ; 1: new-node counts -> offsets ; 2: source counts -> t_indptr ;
+                           // 3: n_fixed values per batch, no header involved ;
+                           // 4: as 0, the counts min(fanout, degree) taken here (blocks of one tile)
+    const int32_t *in;
+    int64_t in_stride;
+    int32_t *out;
+    int64_t out_stride;
+    int32_t *out_copy;     // mode 2: fill cursors
+    int64_t copy_stride;
+    int32_t *hdr;
+    int32_t n_fixed;
+    const int32_t *tile_before;   // optional (one batch only): sum of everything in front of each tile, computed beforehand
+    int32_t cap_src;              // mode 1: entries the frontier array holds
+    int64_t *async_status;        // mode 1: status words of the caller's context, or NULL
+    const int64_t *g_indptr;      // mode 4
+    const int32_t *dst_ids;
+    int64_t dst_stride;
+    int32_t fanout;
+    int32_t *head_ids;            // mode 4, input-side block in global ids: takes the destination nodes too, or NULL
+    int64_t head_stride;
+    int32_t *zero;                // [G][n_zero] words to clear for a later kernel of the hop, or NULL
+    int32_t n_zero;               // at most SCAN_THREADS
+};
+
 struct SelectArgs {
     const int64_t *g_indptr;
     const int32_t *g_indices;
@@ -62,6 +90,8 @@ struct SelectArgs {
     int64_t out_stride;
     int32_t rows_per_wave;       // destination rows a wave of select_quad_kernel takes (at most QUAD_ROWS)
     uint32_t exact_select;       // verification aid: no pre-filter thresholds, every ranking on full (key, slot) pairs
+    int32_t scan_here;           // 1: select_quad_kernel works out the row pointers itself (`scan`, as mode 4 of scan_kernel)
+    ScanArgs scan;
 };
 
 // where the chosen neighbours of a row go, and (when they go to the intermediate array) the row's count
@@ -124,12 +154,11 @@ __device__ __forceinline__ uint32_t slot_word(const SelectArgs &a, int j, int32_
 // by counting and permuted into place, later chunks of 64 slots are tested against the k-th pair and
 // inserted by shifting.  Every pair is distinct, so the surviving set is unique.
 template <int MODE, bool COMPACT = false>
-__device__ __forceinline__ void select_big_row(const SelectArgs &a, int g, int row, int32_t v, int64_t base, int deg, int32_t cv,
+__device__ __forceinline__ void select_big_row(const SelectArgs &a, int g, int row, int32_t *sel_row, int32_t v, int64_t base, int deg, int32_t cv,
                                             int lane)
 {
     constexpr bool WIDE = MODE != 0;
     const int f = a.fanout;
-    int32_t *sel_row = sel_row_ptr(a, g, row);
     const int k = f;
     const uint32_t batch = a.first_batch + (uint32_t)g;
     auto less = [&](uint64_t ka, uint32_t sa, uint64_t kb, uint32_t sb) -> bool {
@@ -293,7 +322,7 @@ __device__ __forceinline__ bool search_bound(int n, int k, float hi, ToWord &&to
 // intra-community slots (counted from the bits first); with fewer of them than the fanout the caller's general
 // path fills up with inter-community ones.
 template <bool INTRA_ONLY>
-__device__ __forceinline__ bool select_big_row_filtered(const SelectArgs &a, int g, int row, int32_t v, int64_t base, int deg,
+__device__ __forceinline__ bool select_big_row_filtered(const SelectArgs &a, int g, int row, int32_t *sel_row, int32_t v, int64_t base, int deg,
                                                         int lane, uint32_t *ckey /*[CAND_CAP + 4]*/, uint32_t *cslot /*[CAND_CAP]*/)
 {
     const int k = a.fanout;
@@ -378,7 +407,6 @@ __device__ __forceinline__ bool select_big_row_filtered(const SelectArgs &a, int
     const bool s0 = w0 < T, s1 = w1 < T;
     const uint64_t m0 = __ballot(s0), m1 = __ballot(s1);
     if (exact) {
-        int32_t *sel_row = sel_row_ptr(a, g, row);
         if (s0) sel_row[__popcll(m0 & lt_mask)] = a.g_indices[base + cslot[lane]];
         if (s1) sel_row[__popcll(m0) + __popcll(m1 & lt_mask)] = a.g_indices[base + cslot[lane + WAVE]];
         if (lane == 0) set_row_count(a, g, row, k);
@@ -395,7 +423,7 @@ __device__ __forceinline__ bool select_big_row_filtered(const SelectArgs &a, int
 // is below the smallest key any left-out slot can have, E(threshold - 1) * m per class in integer arithmetic: that is
 // checked, and otherwise (or with too few / too many candidates) the caller takes the general path.
 template <bool COMPACT = false>
-__device__ __forceinline__ bool select_big_row_weighted(const SelectArgs &a, int g, int row, int32_t v, int64_t base, int deg,
+__device__ __forceinline__ bool select_big_row_weighted(const SelectArgs &a, int g, int row, int32_t *sel_row, int32_t v, int64_t base, int deg,
                                                         int lane, uint2 *cand, unsigned long long *ckey)
 {
     const int k = a.fanout;
@@ -504,7 +532,6 @@ __device__ __forceinline__ bool select_big_row_weighted(const SelectArgs &a, int
 
     const bool s0 = have0 && r0 < k, s1 = have1 && r1 < k;
     const uint64_t m0 = __ballot(s0), m1 = __ballot(s1);
-    int32_t *sel_row = sel_row_ptr(a, g, row);
     if (s0) sel_row[__popcll(m0 & lt_mask)] = a.g_indices[base + (c0.y & 0x7FFFFFFFu)];
     if (s1) sel_row[__popcll(m0) + __popcll(m1 & lt_mask)] = a.g_indices[base + (c1.y & 0x7FFFFFFFu)];
     if (lane == 0) set_row_count(a, g, row, k);
@@ -620,8 +647,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         if (deg[i] > WAVE) {
             uint2 *buf = cand[threadIdx.x / WAVE];
             if (MODE == 2 && !a.exact_select && a.edge_intra &&
-                select_big_row_weighted(a, g, row0 + i, v[i], base[i], deg[i], lane, buf, ckey[threadIdx.x / WAVE])) continue;
-            select_big_row<MODE>(a, g, row0 + i, v[i], base[i], deg[i], cv[i], lane);
+                select_big_row_weighted(a, g, row0 + i, sel_row_ptr(a, g, row0 + i), v[i], base[i], deg[i], lane, buf, ckey[threadIdx.x / WAVE])) continue;
+            select_big_row<MODE>(a, g, row0 + i, sel_row_ptr(a, g, row0 + i), v[i], base[i], deg[i], cv[i], lane);
         }
 }
 
@@ -926,7 +953,7 @@ __device__ __forceinline__ uint32_t quad_pass(const SelectArgs &a, int g, int ro
 // ranked through their bit patterns, and the result is accepted if the largest kept key and the smallest key left out
 // (among the candidates, and the smallest a filtered-out slot can have) are further apart than the keys' error bounds.
 // Returns false otherwise (too few or too many candidates, check failed): the caller goes on to the exact paths.
-__device__ __forceinline__ bool select_big_row_weighted_f32(const SelectArgs &a, int g, int row, int32_t v, int64_t base, int deg,
+__device__ __forceinline__ bool select_big_row_weighted_f32(const SelectArgs &a, int g, int row, int32_t *sel_row, int32_t v, int64_t base, int deg,
                                                             int lane, uint32_t *ckey /*[CAND_CAP + 4]*/, uint32_t *cslot /*[CAND_CAP]*/)
 {
     const int k = a.fanout;
@@ -1045,13 +1072,71 @@ __device__ __forceinline__ bool select_big_row_weighted_f32(const SelectArgs &a,
     const bool s0 = w0 < T, s1 = w1 < T;
     const uint64_t m0 = __ballot(s0), m1 = __ballot(s1);
     if (exact) {
-        int32_t *sel_row = sel_row_ptr(a, g, row);
         if (s0) sel_row[__popcll(m0 & lt_mask)] = a.g_indices[base + (q0 & 0x7FFFFFFFu)];
         if (s1) sel_row[__popcll(m0) + __popcll(m1 & lt_mask)] = a.g_indices[base + (q1 & 0x7FFFFFFFu)];
         if (lane == 0) set_row_count(a, g, row, k);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");      // the buffers are reused by this wave's next long row
     return exact;
+}
+
+// Row pointers of a block of few rows, worked out by the first wave of every workgroup of the selection (they need degrees only):
+// a launch of their own is 4.5 us for 64 rows (a group of one batch of 64 roots: 32.8 -> 28.2 us, with its training step 74.5 ->
+// 66.3).  Every workgroup reads all of the batch's degrees, so only where that is a few loads a lane.  pre: exclusive prefix sums;
+// `writer` also writes what scan_kernel does in mode 4.
+constexpr int SELECT_SCAN_ROWS = 512;
+__device__ __forceinline__ void select_scan(const SelectArgs &a, int g, int n_dst, bool writer, int *pre)
+{
+    constexpr int CHUNKS = SELECT_SCAN_ROWS / WAVE;
+    const int lane = lane_id();
+    const ScanArgs &sc = a.scan;
+    const int32_t *dst = a.dst_ids + (int64_t)g * a.dst_stride;
+    int32_t node[CHUNKS];
+    int cnt[CHUNKS];
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c)
+        if (c * WAVE < n_dst) node[c] = dst[min(c * WAVE + lane, n_dst - 1)];
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+        cnt[c] = 0;
+        if (c * WAVE < n_dst) {
+            const int64_t d = a.g_indptr[node[c] + 1] - a.g_indptr[node[c]];
+            cnt[c] = c * WAVE + lane < n_dst ? (int)(d < a.fanout ? d : a.fanout) : 0;
+        }
+    }
+    int total = 0;
+    int32_t *out = sc.out + (int64_t)g * sc.out_stride;
+#pragma unroll
+    for (int c = 0; c < CHUNKS; ++c) {
+        if (c * WAVE >= n_dst) break;
+        const int r = c * WAVE + lane;
+        int incl = cnt[c];
+#pragma unroll
+        for (int off = 1; off < WAVE; off <<= 1) {
+            const int y = __shfl_up(incl, off);
+            if (lane >= off) incl += y;
+        }
+        const int before = total + incl - cnt[c];
+        pre[r] = before;
+        if (writer && r < n_dst) {
+            out[r] = before;
+            if (sc.head_ids) sc.head_ids[(int64_t)g * sc.head_stride + r] = node[c];
+        }
+        total += __builtin_amdgcn_readlane(incl, WAVE - 1);
+    }
+    if (!writer) return;
+    if (sc.zero) {
+        for (int i = lane; i < sc.n_zero; i += WAVE) sc.zero[(int64_t)g * sc.n_zero + i] = 0;
+    }
+    if (lane == 0) {
+        int32_t *hdr = sc.hdr + (int64_t)g * CR_HDR_WORDS;
+        out[n_dst] = total;
+        hdr[CR_HDR_N_DST] = n_dst;
+        hdr[CR_HDR_NNZ] = total;
+        hdr[CR_HDR_STATUS] = sc.prev_hdr ? sc.prev_hdr[(int64_t)g * CR_HDR_WORDS + CR_HDR_STATUS] : 0;
+        hdr[4] = hdr[5] = hdr[6] = hdr[7] = 0;
+        if (sc.head_ids) hdr[CR_HDR_N_SRC] = -1;
+    }
 }
 
 // (occupancy targets: the weighted instantiation takes 85 registers when left alone, which leaves five waves per SIMD and
@@ -1068,8 +1153,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 2 ?
     const int g = blockIdx.y;
     const int n_dst = group_n_dst(a.prev_hdr, g, a.n_roots_total, a.batch_size);
     const int row0 = (int)(blockIdx.x * 4 + wv) * a.rows_per_wave;
-    if (row0 >= n_dst) return;
     const int lane = lane_id();
+    __shared__ int pre_s[SELECT_SCAN_ROWS];
+    if (a.scan_here) {
+        if (wv == 0) select_scan(a, g, n_dst, blockIdx.x == 0, pre_s);
+        __syncthreads();
+    }
+    if (row0 >= n_dst) return;
 
     // lanes 0..QUAD_ROWS-1 fetch one row's node id, adjacency range and output place each
     int32_t mv = 0;
@@ -1082,7 +1172,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 2 ?
         mbase = a.g_indptr[mv];
         const int64_t d = a.g_indptr[mv + 1] - mbase;
         mdeg = (int)(d > 0x7FFFFFFF ? 0x7FFFFFFF : d);
-        mout = a.out_indptr ? (int64_t)a.out_indptr[(int64_t)g * a.out_indptr_stride + row0 + lane] : (int64_t)(row0 + lane) * a.fanout;
+        mout = a.scan_here ? (int64_t)pre_s[row0 + lane]
+                           : (a.out_indptr ? (int64_t)a.out_indptr[(int64_t)g * a.out_indptr_stride + row0 + lane] : (int64_t)(row0 + lane) * a.fanout);
         if (mdeg == 0) set_row_count(a, g, row0 + lane, 0);
     }
     const int mq = (mdeg > 0 && mdeg <= QUAD_MAX_DEG) ? (mdeg + 3) >> 2 : 0;
@@ -1125,14 +1216,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MODE == 2 ?
         if (deg <= QUAD_MAX_DEG) continue;
         const int32_t v = (int32_t)rl32((uint32_t)mv, i);
         const int64_t base = (int64_t)rl64((uint64_t)mbase, i);
+        int32_t *sel_row = out + (int64_t)rl64((uint64_t)mout, i);
         if constexpr (MODE == 2) {
-            if (!a.exact_select && select_big_row_weighted_f32(a, g, row0 + i, v, base, deg, lane, klist_s[wv], cslot_s[wv])) continue;
+            if (!a.exact_select && select_big_row_weighted_f32(a, g, row0 + i, sel_row, v, base, deg, lane, klist_s[wv], cslot_s[wv])) continue;
             if (!a.exact_select &&
-                select_big_row_weighted<true>(a, g, row0 + i, v, base, deg, lane, reinterpret_cast<uint2 *>(klist_s[wv]), k64)) continue;
+                select_big_row_weighted<true>(a, g, row0 + i, sel_row, v, base, deg, lane, reinterpret_cast<uint2 *>(klist_s[wv]), k64)) continue;
         } else {
-            if (!a.exact_select && select_big_row_filtered<MODE == 1>(a, g, row0 + i, v, base, deg, lane, klist_s[wv], cslot_s[wv])) continue;
+            if (!a.exact_select && select_big_row_filtered<MODE == 1>(a, g, row0 + i, sel_row, v, base, deg, lane, klist_s[wv], cslot_s[wv])) continue;
         }
-        select_big_row<MODE, true>(a, g, row0 + i, v, base, deg, MODE >= 1 ? a.comm[v] : 0, lane);
+        select_big_row<MODE, true>(a, g, row0 + i, sel_row, v, base, deg, MODE >= 1 ? a.comm[v] : 0, lane);
     }
 }
 
@@ -1173,34 +1265,6 @@ __global__ __launch_bounds__(256) void clock_selftest_kernel(float *out)
     atomicMax(reinterpret_cast<unsigned int *>(out + 1), __float_as_uint(worst_rel));
     atomicMax(reinterpret_cast<unsigned int *>(out + 2), __float_as_uint(worst_ratio));
 }
-
-struct ScanArgs {
-    const int32_t *prev_hdr;
-    int64_t n_roots_total;
-    int32_t batch_size;
-    int32_t mode;          // 0: row counts -> indptr ; 1: new-node counts -> offsets ; 2: source counts -> t_indptr ;
-                           // 3: n_fixed values per batch, no header involved ;
-                           // 4: as 0, the counts min(fanout, degree) taken here (blocks of one tile)
-    const int32_t *in;
-    int64_t in_stride;
-    int32_t *out;
-    int64_t out_stride;
-    int32_t *out_copy;     // mode 2: fill cursors
-    int64_t copy_stride;
-    int32_t *hdr;
-    int32_t n_fixed;
-    const int32_t *tile_before;   // optional (one batch only): sum of everything in front of each tile, computed beforehand
-    int32_t cap_src;              // mode 1: entries the frontier array holds
-    int64_t *async_status;        // mode 1: status words of the caller's context, or NULL
-    const int64_t *g_indptr;      // mode 4
-    const int32_t *dst_ids;
-    int64_t dst_stride;
-    int32_t fanout;
-    int32_t *head_ids;            // mode 4, input-side block in global ids: takes the destination nodes too, or NULL
-    int64_t head_stride;
-    int32_t *zero;                // [G][n_zero] words to clear for a later kernel of the hop, or NULL
-    int32_t n_zero;               // at most SCAN_THREADS
-};
 
 // out[0..n] = exclusive prefix sums of in[0..n) per batch (blockIdx.y).  A workgroup owns one tile of 256 x 16
 // elements (blockIdx.x): it first adds up everything in front of its tile (the input is a few hundred KB at most and
@@ -2773,6 +2837,7 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
         sc.zero = (lds_hop || lds_transpose) && !one_part ? p.hop_counters : nullptr; sc.n_zero = HOP_COUNTERS;
         const dim3 scan_grid((unsigned)ceil_div(cap_dst, SCAN_TILE), n_batches);
         sa.out_indptr = nullptr; sa.out_indptr_stride = 0; sa.out_ids = nullptr; sa.out_stride = 0;
+        sa.scan_here = (direct_out || lds_hop) && cap_dst <= SELECT_SCAN_ROWS && (q_in == q_out || graph->edge_intra) ? 1 : 0;
         if (direct_out || lds_hop) {
             if (cap_dst <= SCAN_TILE) {
                 sc.mode = 4;
@@ -2781,10 +2846,11 @@ extern "C" cr_status cr_sample_blocks(const cr_graph *graph, const cr_sample_cfg
                 hipLaunchKernelGGL(row_counts_kernel, dim3((unsigned)ceil_div(cap_dst, 256), n_batches), blk, 0, s, graph->indptr, dst_ids, dst_stride,
                                    prev_hdr, n_roots_total, batch_size, f, p.cnt, (int64_t)p.max_dst);
             }
-            hipLaunchKernelGGL(scan_kernel, scan_grid, dim3(SCAN_THREADS), 0, s, sc);
+            if (!sa.scan_here) hipLaunchKernelGGL(scan_kernel, scan_grid, dim3(SCAN_THREADS), 0, s, sc);
             sa.out_indptr = b.indptr; sa.out_indptr_stride = b.cap_dst + 1;
             sa.out_ids = direct_out ? b.gather_ids : p.sel; sa.out_stride = direct_out ? b.cap_nnz : p.max_nnz;
         }
+        sa.scan = sc;
         if (q_in == q_out) hipLaunchKernelGGL(select_quad_kernel<0>, quad_grid, blk, 0, s, sa);
         else if (q_out == 0 && graph->edge_intra) hipLaunchKernelGGL(select_quad_kernel<1>, quad_grid, blk, 0, s, sa);
         else if (graph->edge_intra) hipLaunchKernelGGL(select_quad_kernel<2>, quad_grid, blk, 0, s, sa);

@@ -36,6 +36,27 @@ def test_rows_per_wave(torch_mod, batch_size, n_batches, p):
     compare(layers, nb, graph, roots, [4, 7], p, False, 3, 1, 2, batch_size, f"rows per wave p={p}")
 
 
+# blocks whose row pointers the selection works out itself (at most 512 rows by capacity) and just not: rows at the root and one hop on,
+# empty and long rows among them, a short last batch, with the input block in global ids and relabelled
+@pytest.mark.parametrize("batch_size,n_batches,p", [(1, 3, 0.5), (63, 2, 0.9), (64, 1, 1.0), (102, 5, 0.5), (103, 5, 0.9), (512, 3, 1.0), (513, 2, 0.5)])
+@pytest.mark.parametrize("input_global", [False, True])
+def test_row_pointers_in_the_selection(torch_mod, batch_size, n_batches, p, input_global):
+    from paper_2504_18082_amd import binding as B
+    torch = torch_mod
+    n = 3000
+    graph = mixed_graph(n)
+    dg = DeviceGraph(torch, graph, 8, edge_classes=True)
+    n_roots = batch_size * n_batches - batch_size // 2
+    roots = np.random.default_rng(4).permutation(n).astype(np.int32)[:n_roots]
+    print(f"case row pointers in the selection: {n_batches} batches of {batch_size}, p={p}, global {input_global}", flush=True)
+    cfg = B.make_sample_cfg([7, 4], p, 3, 1, 2, B.CR_SAMPLE_INPUT_GLOBAL_IDS if input_global else 0)
+    layers = B.alloc_block_sets(cfg, n, batch_size, n_batches)
+    ws = torch.full((B.cr_sample_blocks_workspace_bytes(cfg, n, batch_size, n_batches),), 0xAB, dtype=torch.uint8, device="cuda")
+    B.cr_sample_blocks(dg.c, cfg, torch.from_numpy(roots).cuda(), n_roots, batch_size, n_batches, ws, layers)
+    torch.cuda.synchronize()
+    compare(layers, n_batches, graph, roots, [7, 4], p, False, 3, 1, 2, batch_size, f"row pointers p={p}", input_global=input_global)
+
+
 def fixed_rows(n_nodes, rows):
     """Graph whose node i has the neighbours rows(i) (ascending, distinct)."""
     r = [np.sort(np.asarray(rows(i), dtype=np.int32)) for i in range(n_nodes)]
