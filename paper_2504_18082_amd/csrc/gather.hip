@@ -106,8 +106,10 @@ __global__ __launch_bounds__(256) void gather_mean_fwd_kernel(
 {
     constexpr int VEC = Vec16<T>::N;
     // independent row loads in flight per lane: five go into the fanouts in use (5, 10, 15, 25) without a rest, and fewer rows in
-    // flight leave more of what neighbouring rows share in the L2s (see launch_fwd_group)
-    constexpr int U = NCHUNK == 1 ? 5 : (NCHUNK <= 3 ? 4 : 2);
+    // flight leave more of what neighbouring rows share in the L2s (see launch_fwd_group).  GCN's rows wait for their weights
+    // too, and eight are better where the table fits the caches (arxiv-like at 0.3 of its size, 28 batches: 313 us, 334 with
+    // five; products-like at 0.06, 6 batches 140, 145) and no worse beyond them.
+    constexpr int U = NCHUNK == 1 ? (GCN ? 8 : 5) : (NCHUNK <= 3 ? 4 : 2);
     constexpr int GPB = 256 / LPR;                                // groups (rows in progress) per workgroup
     const int n_dst = GROUPED ? min(order[(int64_t)grp.n_batches * grp.cap_dst], grp.n_batches * grp.cap_dst) : hdr[CR_HDR_N_DST];
     const int n_src = GROUPED ? grp.cap_src : hdr[CR_HDR_N_SRC];
