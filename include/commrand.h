@@ -522,7 +522,7 @@ cr_status cr_softmax_xent(const int32_t *hdr, int32_t max_rows, const float *log
  * product holds whole rows of logits and finishes their loss terms in place; otherwise separate kernels run (two for at
  * most 2048 rows: the loss rows' kernel takes the mean as well).
  * Logits are bit-identical to cr_sage_linear_fwd's; the loss terms may differ from cr_softmax_xent's in the last
- * bits (sums are associated differently), never from run to run.
+ * bits (sums are associated differently), never from run to run (losses beyond 2^14: see scratch).
  *   logits        : device float [max_rows][N_pad];  d_logits_bf16 : device bf16 [max_rows][N_pad]
  *   scratch       : device, CR_XENT_SCRATCH_BYTES; zero before the first call, and every call leaves it zero again;
  *                   calls that share a scratch must not overlap.  For at most 2048 rows the mean loss is the sum of
